@@ -421,6 +421,9 @@ int lens_deflect(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* gri
     if (prec == LENS_FP64)
         e = launch_field64((const double*)ctx->buf[B_TAB64], pot->n, g, (double*)ax, (double*)ay, st, nullptr, 5, 1,
                            ev, stream);
+    else if (const int side = tiled_side(g, pot->n))
+        e = launch_tiled32(side, (const double*)ctx->buf[B_TAB64], (const float*)ctx->buf[B_TAB32], pot->n, g,
+                           (float*)ax, (float*)ay, st, nullptr, nullptr, ev, stream);
     else
         e = launch_field32((const float*)ctx->buf[B_TAB32], pot->n, g, (float*)ax, (float*)ay, st, field_npl(g),
                            nullptr, 5, 1, ev, stream);
@@ -538,6 +541,7 @@ struct Chi2Plan {
     ObsPtrs o;
     int np;
     bool mixed, fused;
+    int side;  // tiled field: nodes per tile side (0: direct field)
     int shape, npl, tiles_x, tx_shift, n_cull, tpw, n_parts, fb_blocks;
     long long region, flag_cap;
     size_t nn, vbytes;
@@ -593,7 +597,8 @@ int chi2_plan(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* grid, 
     pl.vbytes = pl.mixed ? 4 : 8;
     pl.flag_cap = pl.mixed ? flag_cap : 0;
     // the head's source-plane part runs inside the field launch when the grid allows
-    pl.fused = fused_head_fits(pl.g, pl.o, pl.npl, pl.mixed) != 0;
+    pl.side = pl.mixed ? tiled_side(pl.g, pl.np) : 0;
+    pl.fused = pl.side || fused_head_fits(pl.g, pl.o, pl.npl, pl.mixed) != 0;
     size_t* b = pl.bytes;
     b[CB_STATE] = sizeof(EvalState);
     b[CB_TAB64] = (size_t)pl.np * T64_STRIDE * 8;
@@ -608,7 +613,8 @@ int chi2_plan(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* grid, 
     b[CB_POS] = (size_t)kHitScratch * 4 * 8;
     b[CB_FLAGS] = (size_t)(pl.mixed ? pl.flag_cap : 1) * 8;
     b[CB_PART] = (size_t)pl.n_parts * 2 * 4;
-    b[CB_RR] = (size_t)pl.g.ny * (pl.tiles_x + 1) * kRR * pl.vbytes;
+    b[CB_RR] = pl.side ? (size_t)rec_nbx(pl.g) * rec_nby(pl.g) * kRec * pl.vbytes
+                       : (size_t)pl.g.ny * (pl.tiles_x + 1) * kRR * pl.vbytes;
     b[CB_PAIRS] = (size_t)pl.region * pl.n_cull * 8 + (size_t)pl.n_cull * 4;
     return LENS_OK;
 }
@@ -662,7 +668,10 @@ int chi2_run(lens_ctx* ctx, const Chi2Plan& pl, const Chi2Bufs& b, const lens_po
     ha.by = by;
     ha.sysrow = sysrow;
     ha.st = st;
-    if (mixed && pl.fused)
+    if (mixed && pl.side)
+        e = launch_tiled32(pl.side, tab64, tab32, np, g, (float*)field, (float*)field + nn, nullptr, (float*)rr, &ha,
+                           ev, stream);
+    else if (mixed && pl.fused)
         e = launch_field32h(tab32, np, g, (float*)field, (float*)field + nn, pl.npl, (float*)rr, pl.tx_shift,
                             pl.tiles_x, ha, ev, stream);
     else if (mixed)
@@ -678,7 +687,7 @@ int chi2_run(lens_ctx* ctx, const Chi2Plan& pl, const Chi2Bufs& b, const lens_po
     if (ctx) timing_end(ctx, slot);
 
     const float tau = (float)(opts->fb_tau * g.h * g.h);
-    e = launch_cull(mixed, rr, g, o.n_sys, sysrow, pairs, pl.region, counts, part, pl.shape, stream);
+    e = launch_cull(mixed, pl.side != 0, rr, g, o.n_sys, sysrow, pairs, pl.region, counts, part, pl.shape, stream);
     if (e == hipSuccess)
         e = launch_pairs(mixed, fx, fy, g, sysrow, st, opts->fb_mode, tau, pairs, pl.region, counts, pl.n_cull, hits,
                          kHitScratch, flags, pl.flag_cap, part, pl.n_cull, pl.shape, stream);

@@ -108,6 +108,15 @@ inline bool bfield_code_ok(int code)
     return code == 1 || code == 2 || code == 4 || code == 0x21 || code == 0x22 || code == 0x41;
 }
 
+// Field by tiles of side x side nodes (lens_tiles.hpp); rec: 32 x 8 block
+// records or null; h: the head's arguments (fused head) or null.
+int tiled_side(const GridDesc& g, int np);  // 0: direct field
+inline int rec_nbx(const GridDesc& g) { return (g.nx + 31) / 32; }
+inline int rec_nby(const GridDesc& g) { return (g.ny + 7) / 8; }
+hipError_t launch_tiled32(int side, const double* tab64, const float* tab32, int np, const GridDesc& g, float* ax,
+                          float* ay, const EvalState* st, float* rec, const HeadArgs* h, const KernelEvents* ev,
+                          hipStream_t s);
+
 hipError_t launch_field32h(const float* tab32, int np, const GridDesc& g, float* ax, float* ay, int npl, float* rr,
                            int tx_shift, int tiles_x, const HeadArgs& h, const KernelEvents* ev, hipStream_t s);
 hipError_t launch_field64h(const double* tab64, int np, const GridDesc& g, double* ax, double* ay, double* rr,
@@ -121,13 +130,14 @@ hipError_t launch_field64(const double* tab64, int np, const GridDesc& g, double
                           const EvalState* st, double* rr, int tx_shift, int tiles_x, const KernelEvents* ev,
                           hipStream_t s);
 constexpr int kRR = 8;                     // values per (row, column group) of the tile range partials
+constexpr int kRec = 16;                   // values per 32 x 8 block record of a tiled field
 constexpr int kPairBlocks = 512;           // persistent workgroups of the pair kernel
 constexpr int kMaxCull = 4096;             // culling waves (64 tiles per round)
 int fbpos_blocks(long long n_tiles);       // persistent workgroups of the positions / fallback kernel
 void tile_dims(int shape, int& tx, int& ty);
 long long tri_tiles(const GridDesc& g, int shape, int* tiles_x);
 void cull_shape(const GridDesc& g, int shape, int nsys, int* n_cull, int* tpw, int* sc, int* n_chunks);
-hipError_t launch_cull(bool fp32, const void* rr, const GridDesc& g, int nsys,
+hipError_t launch_cull(bool fp32, bool tiled, const void* rr, const GridDesc& g, int nsys,
                        const double* sysrow, unsigned long long* pairs, long long region, unsigned* counts,
                        unsigned* part, int shape, hipStream_t s);
 hipError_t launch_pairs(bool fp32, const void* ax, const void* ay, const GridDesc& g, const double* sysrow,

@@ -20,6 +20,7 @@
 // lens_source_positions, and the chi^2 path when the fused grid would exceed
 // 65535 rows of workgroups.
 #include "lens_path.hpp"
+#include "lens_tiles.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -340,11 +341,9 @@ __global__ __launch_bounds__(256) void k_field64(const double* __restrict__ tab6
 // one wave per observed image reads the prepared FP64 table; the last of these
 // workgroups runs head_finish.  The field workgroups do not depend on it (they
 // read only the FP32 / FP64 tables); the triangle stage after the launch does.
-__device__ __forceinline__ void fused_head(HeadLds& L, const HeadArgs& h, int head_rows)
+__device__ __forceinline__ void fused_head(HeadLds& L, const HeadArgs& h, int b, int nblk)
 {
     __shared__ int last;
-    const int nblk = head_rows * gridDim.x;
-    const int b = blockIdx.y * gridDim.x + blockIdx.x;
     head_images<true>(h.pot, h.tab64, h.obs, h.bx, h.by, b * 4 + (threadIdx.x >> 6), nblk * 4);
     if (!last_of(&h.st->head_ticket, (unsigned)nblk, &last)) return;
     head_finish(L, h.pot.n, h.g, h.obs, h.bterm, h.bx, h.by, h.sysrow, h.st);
@@ -370,7 +369,7 @@ __global__ __launch_bounds__(256) void k_field32h(const float* __restrict__ tab3
 {
     __shared__ FusedLds<fused_lds_bytes(NR * 256 * (int)sizeof(float4))> lds;
     if ((int)blockIdx.y < head_rows) {
-        fused_head(*reinterpret_cast<HeadLds*>(lds.raw), h, head_rows);
+        fused_head(*reinterpret_cast<HeadLds*>(lds.raw), h, blockIdx.y * gridDim.x + blockIdx.x, head_rows * gridDim.x);
         return;
     }
     field32_block<NPL, NR>(tab32, np, nx, ny, (blockIdx.y - head_rows) * NR, blockIdx.x, ax, ay, nullptr, rr,
@@ -384,10 +383,31 @@ __global__ __launch_bounds__(256) void k_field64h(const double* __restrict__ tab
 {
     __shared__ HeadLds hl;
     if ((int)blockIdx.y < head_rows) {
-        fused_head(hl, h, head_rows);
+        fused_head(hl, h, blockIdx.y * gridDim.x + blockIdx.x, head_rows * gridDim.x);
         return;
     }
     field64_row(tab64, np, g, blockIdx.y - head_rows, blockIdx.x, ax, ay, nullptr, rr, tx_shift, tiles_x);
+}
+
+// ============================================================== tiled field
+
+// One workgroup per tile, in row-major order; the first head_blocks workgroups
+// run the head (as k_field32h's).
+template <int T>
+__global__ __launch_bounds__(256) void k_tiled32(const double* __restrict__ tab64, const float* __restrict__ tab32,
+                                                 int np, GridDesc g, int ntx, float* __restrict__ ax,
+                                                 float* __restrict__ ay, const EvalState* __restrict__ st,
+                                                 float* __restrict__ rec, int nbx, HeadArgs h, int head_blocks)
+{
+    using Lds = typename Tile32<T>::Lds;
+    __shared__ FusedLds<fused_lds_bytes((int)sizeof(Lds))> lds;
+    if ((int)blockIdx.x < head_blocks) {
+        fused_head(*reinterpret_cast<HeadLds*>(lds.raw), h, blockIdx.x, head_blocks);
+        return;
+    }
+    const int tile = blockIdx.x - head_blocks, tj = tile / ntx, ti = tile - tj * ntx;
+    const bool bad = st != nullptr && st->status != kStatusOk;
+    tile32_body<T>(*reinterpret_cast<Lds*>(lds.raw), tab64, tab32, np, g, ti * T, tj * T, ax, ay, bad, rec, nbx);
 }
 
 // ============================================================== triangle stage
@@ -403,7 +423,7 @@ __global__ __launch_bounds__(256) void k_field64h(const double* __restrict__ tab
 // appended to the wave's own region (ballot and lane prefix) and the wave's
 // count written to counts[wave]: no atomic, no barrier.  Small grids split the
 // systems over more waves, large grids give a wave several blocks.
-template <class S, typename V>
+template <class S, typename V, bool REC>
 __global__ __launch_bounds__(256) void k_cull(const V* __restrict__ rr, GridDesc g, int tiles_x, int n_tiles,
                                               int tpw, int sc, int n_chunks, int n_cull, int nsys,
                                               const double* __restrict__ sysrow, unsigned long long* __restrict__ pairs,
@@ -433,7 +453,10 @@ __global__ __launch_bounds__(256) void k_cull(const V* __restrict__ rr, GridDesc
         double rng[4] = {0.0, 0.0, 0.0, 0.0};
         if (act) {
             T = tile_of<S>(g, tiles_x, tile);
-            tile_range_lane<S, V>(rr, tiles_x, T, rng);
+            if constexpr (REC)
+                tile_range_rec<S, V>(rr, (g.nx + 31) >> 5, (g.ny + 7) >> 3, T, rng);
+            else
+                tile_range_lane<S, V>(rr, tiles_x, T, rng);
         }
         for (int c = 0; c < ns; c++) {
             const bool pass =
@@ -1103,6 +1126,56 @@ hipError_t launch_field64h(const double* tab64, int np, const GridDesc& g, doubl
                      rr, tx_shift, tiles_x, h, hr);
 }
 
+// Workgroups of the fused head in a tiled launch: one wave per observed image.
+static int head_blocks_for(const ObsPtrs& obs) { return obs.n_img > 0 ? (int)cdiv(obs.n_img, 4) : 1; }
+
+// Tile side of the tiled FP32 field, 0 for the direct field.  The tiled kernel
+// has about 10 us of its own chain (lists, Chebyshev points, transforms), so it
+// pays from about 2^24 node-potential terms on (512^2 x 50: 11.8 us against 11.7
+// direct; 1024^2 x 50: 13.5 against 31.1; 411 x 300 x 50: 14.1 against 10.2), and
+// with fewer than 4 potentials there is nothing to share.  The side trades far
+// work (P 64 / T^2 profile evaluations per node, at 116 cycles per 64) against
+// near work (potentials within 3.6 half widths, taken as uniform over the grid,
+// at 75 cycles) with the rest at 60, and must leave enough workgroups: the
+// longer of the chip's throughput and one workgroup's own chain counts.
+int tiled_side(const GridDesc& g, int np)
+{
+    const double nodes = (double)g.nx * g.ny;
+    if (np < 4 || np > kTileMaxP || nodes * np < (double)(1 << 24)) return 0;
+    int best = 0;
+    double cost = 0.0;
+    for (int t = 32; t <= 128; t *= 2) {
+        const double near = std::min((double)np, 1.0 + np * kPi * 3.24 * t * t / nodes);
+        const double units = std::max(1.0, t * t / 2048.0);  // units of 512 nodes per wave
+        const double all = nodes / 64.0 * (75.0 * near + 116.0 * 64.0 * np / ((double)t * t) + 60.0) / 1024.0;
+        const double chain = 6000.0 + 62.0 * np + units * (600.0 + 640.0 * near);
+        const double c = std::max(all, chain);
+        if (!best || c < cost) {
+            best = t;
+            cost = c;
+        }
+    }
+    return best;
+}
+
+hipError_t launch_tiled32(int side, const double* tab64, const float* tab32, int np, const GridDesc& g, float* ax,
+                          float* ay, const EvalState* st, float* rec, const HeadArgs* h, const KernelEvents* ev,
+                          hipStream_t s)
+{
+    const int ntx = (int)cdiv(g.nx, side), n_tiles = ntx * (int)cdiv(g.ny, side);
+    const int hb = h ? head_blocks_for(h->obs) : 0;
+    const HeadArgs ha = h ? *h : HeadArgs{};
+    auto go = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        return launch_ev(ev, k_tiled32<T>, dim3(n_tiles + hb), dim3(256), s, tab64, tab32, np, g, ntx, ax, ay, st, rec, rec_nbx(g), ha, hb);
+    };
+    switch (side) {
+    case 32: return go(std::integral_constant<int, 32>());
+    case 64: return go(std::integral_constant<int, 64>());
+    default: return go(std::integral_constant<int, 128>());
+    }
+}
+
 hipError_t launch_field64(const double* tab64, int np, const GridDesc& g, double* ax, double* ay,
                           const EvalState* st, double* rr, int tx_shift, int tiles_x, const KernelEvents* ev,
                           hipStream_t s)
@@ -1175,7 +1248,7 @@ void cull_shape(const GridDesc& g, int shape, int nsys, int* n_cull, int* tpw, i
 // wave, at least the count that serves small grids best.
 int fbpos_blocks(long long n_tiles) { return (int)std::min(1024ll, std::max(256ll, n_tiles / 64)); }
 
-hipError_t launch_cull(bool fp32, const void* rr, const GridDesc& g, int nsys,
+hipError_t launch_cull(bool fp32, bool tiled, const void* rr, const GridDesc& g, int nsys,
                        const double* sysrow, unsigned long long* pairs, long long region, unsigned* counts,
                        unsigned* part, int shape, hipStream_t s)
 {
@@ -1185,12 +1258,18 @@ hipError_t launch_cull(bool fp32, const void* rr, const GridDesc& g, int nsys,
         const int n_tiles = (int)tri_tiles(g, shape, &tiles_x);
         cull_shape(g, shape, nsys, &nw, &tpw, &sc, &nch);
         const unsigned nb = (unsigned)cdiv(nw, 4);
-        if (fp32)
-            k_cull<S, float><<<nb, 256, 0, s>>>((const float*)rr, g, tiles_x, n_tiles, tpw, sc, nch, nw, nsys, sysrow,
-                                                pairs, region, counts, part);
+        auto go = [&](auto kernel, auto* r) {
+            kernel<<<nb, 256, 0, s>>>(r, g, tiles_x, n_tiles, tpw, sc, nch, nw, nsys, sysrow, pairs, region, counts,
+                                      part);
+        };
+        if (fp32 && tiled)
+            go(k_cull<S, float, true>, (const float*)rr);
+        else if (fp32)
+            go(k_cull<S, float, false>, (const float*)rr);
+        else if (tiled)
+            go(k_cull<S, double, true>, (const double*)rr);
         else
-            k_cull<S, double><<<nb, 256, 0, s>>>((const double*)rr, g, tiles_x, n_tiles, tpw, sc, nch, nw, nsys,
-                                                 sysrow, pairs, region, counts, part);
+            go(k_cull<S, double, false>, (const double*)rr);
         return hipGetLastError();
     });
 }

@@ -523,6 +523,40 @@ __device__ __forceinline__ void tile_range_lane(const V* __restrict__ rr, int ti
     rng[3] = mxy;
 }
 
+// The same from the 32 x 8 block records of a tiled field (kRec values per
+// block, nbx blocks per block row): the blocks of the lane's own tile, the
+// first columns of the blocks to its right, the first rows of the blocks
+// above, the first node of the block diagonally above.
+template <class S, typename V>
+__device__ __forceinline__ void tile_range_rec(const V* __restrict__ rec, int nbx, int nby, const Tile& T, double* rng)
+{
+    constexpr int BX = S::TX / 32, BY = S::TY / 8;
+    const int bx = T.ci0 >> 5, by = T.cj0 >> 3;
+    V mnx = V(INFINITY), mxx = V(-INFINITY), mny = V(INFINITY), mxy = V(-INFINITY);
+    // a fixed trip count, clamped: a repeated block leaves the range unchanged
+#pragma unroll
+    for (int v = 0; v <= BY; v++) {
+#pragma unroll
+        for (int u = 0; u <= BX; u++) {
+            const bool in = bx + u < nbx && by + v < nby;
+            const bool right = u == BX, above = v == BY;
+            const V* q = rec + ((size_t)(in ? by + v : by) * nbx + (in ? bx + u : bx)) * kRec;
+            // own blocks: values 0..3; above: 4..7; right: 8..11; diagonal: the node (12, 13)
+            const int o = !in ? 0 : right ? (above ? 12 : 8) : above ? 4 : 0;
+            const bool node = right && above && in;
+            const V a0 = q[o], a1 = q[o + (node ? 0 : 1)], a2 = q[o + (node ? 1 : 2)], a3 = q[o + (node ? 1 : 3)];
+            mnx = fmin(mnx, a0);
+            mxx = fmax(mxx, a1);
+            mny = fmin(mny, a2);
+            mxy = fmax(mxy, a3);
+        }
+    }
+    rng[0] = mnx;
+    rng[1] = mxx;
+    rng[2] = mny;
+    rng[3] = mxy;
+}
+
 // Loads tile T's nodes (with the halo) into a wave-private LDS tile.
 template <class S, typename V>
 __device__ __forceinline__ void stage_tile_wave(const V* __restrict__ ax, const V* __restrict__ ay, const GridDesc& g,

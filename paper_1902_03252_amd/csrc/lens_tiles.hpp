@@ -1,0 +1,466 @@
+// Deflection field by tiles: near potentials summed directly at every node, the
+// far ones through one polynomial per tile.
+//
+// A potential's deflection is analytic away from a^2 + R^2 = 0 (a the core
+// radius, R the pseudo-elliptical radius), so over a tile of T x T nodes that
+// lies far enough from its centre it is a polynomial to working precision.
+// For every tile, the potentials are split by a geometric criterion; the sum of
+// the far ones is evaluated at N x N Chebyshev points only and interpolated to
+// the T x T nodes, the near ones (a handful) are evaluated at every node as in
+// the direct field.  Work per node: about (near + far N^2 / T^2 + 1) profile
+// evaluations instead of P.
+//
+// Criterion.  Along a line in x (the same in y with A and C exchanged) R^2 =
+// A X^2 + E', X the complex abscissa from the point of least R, so the nearest
+// singularity of the deflection is at X = -X_c +- i sqrt((E' + a^2)/A) from
+// the tile's centre line, at distance sqrt((a^2 + R^2)/A) from the centre of
+// the interval.  With q^2 = min over the tile's vertical centre line of a^2 +
+// R^2 (a quadratic, minimised exactly), every singularity lies outside the
+// ellipse with foci at the interval's ends and semi-major axis c half widths
+// when q^2 >= A (c hw)^2: the sum of a point's distances to the two ends is at
+// least twice its distance to the centre.  Then interpolation in N Chebyshev
+// points converges as rho^-N, rho = c + sqrt(c^2 - 1).  Largest tensor
+// interpolation error found over the family (eps up to 0.95, any position
+// angle and direction, core and cut radii from 0 to infinity, the potential
+// exactly at the criterion), in units of w_p = K (1 + eps)/sqrt(1 - eps):
+//     N = 8:  c = 3: 5.2e-7    c = 3.5: 1.3e-7
+//     N = 16: c = 4: 1.9e-15   c = 4.5: 3e-16     c = 5: 5e-17
+// (circular singular profiles are the worst; the NFW profile's are alike).
+#pragma once
+
+#include "lens_path.hpp"
+
+namespace lens {
+
+constexpr int kTileMaxP = 2048;  // potentials of a tiled field (LDS lists)
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// DCT row a of N Chebyshev samples f(cos(pi (2k + 1) / 2N)): coefficient a is
+// sum_k kDct[a][k] f_k.  Filled at compile time from a cosine series.
+constexpr double cos_const(double x)
+{
+    // range reduction to [0, pi/4] on the quarter circle, then the Taylor series
+    // to order 22 (below 1e-17 there)
+    const double pi = 3.14159265358979323846264338327950288;
+    while (x > pi) x -= 2.0 * pi;
+    if (x < 0.0) x = -x;
+    const bool neg = x > 0.5 * pi;
+    if (neg) x = pi - x;
+    const bool sn = x > 0.25 * pi;
+    if (sn) x = 0.5 * pi - x;
+    double term = sn ? x : 1.0, sum = term;
+    for (int k = sn ? 2 : 1; k < 24; k += 2) {
+        term *= -x * x / (double(k) * double(k + 1));
+        sum += term;
+    }
+    return neg ? -sum : sum;
+}
+
+template <int N>
+struct Dct {
+    double d[N * N];  // [a][k]
+    double xi[N];     // Chebyshev points
+    constexpr Dct() : d(), xi()
+    {
+        const double pi = 3.14159265358979323846264338327950288;
+        for (int k = 0; k < N; k++) xi[k] = cos_const(pi * (2 * k + 1) / (2.0 * N));
+        for (int a = 0; a < N; a++)
+            for (int k = 0; k < N; k++) {
+                // cos(a (2k+1) pi / 2N) with the angle reduced exactly in units of pi / 2N
+                const int m = (a * (2 * k + 1)) % (4 * N);
+                const int r = m > 2 * N ? 4 * N - m : m;
+                d[a * N + k] = (a ? 2.0 : 1.0) / N * cos_const(pi * r / (2.0 * N));
+            }
+    }
+};
+// per translation unit: static device copies
+static __device__ const Dct<8> kDct8;
+static __device__ const Dct<16> kDct16;
+
+// Criterion constants (c of the file comment).
+constexpr float kFarC32 = 3.0f;
+constexpr float kFarC64 = 4.5f;
+
+// Orders a wave's LDS writes before its following LDS reads.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Whether a potential (node-unit FP32 table row: centre, M h^2, a^2) is far from
+// the tile whose centre is (xc, yc) and half width hw (node units).  A NaN
+// (a degenerate row) leaves the potential near.
+__device__ __forceinline__ bool tile_far(float dx, float dy, float A, float B, float C, float a2, float hw, float c)
+{
+    const float t = fminf(fmaxf(-B * dx * __builtin_amdgcn_rcpf(C), dy - hw), dy + hw);
+    const float u = fminf(fmaxf(-B * dy * __builtin_amdgcn_rcpf(A), dx - hw), dx + hw);
+    const float qv = fmaf(A * dx, dx, fmaf(2.0f * B * dx, t, fmaf(C * t, t, a2)));
+    const float qh = fmaf(A * u, u, fmaf(2.0f * B * dy, u, fmaf(C * dy, dy, a2)));
+    const float lim = c * c * hw * hw * 1.0001f;
+    return qv >= A * lim && qh >= C * lim && A > 0.0f && C > 0.0f;
+}
+
+// Near/far lists of one tile: near potentials first (in order), then the far
+// ones (in order).  Called by all 256 threads of the workgroup (two
+// barriers); isfar(p) is evaluated once per potential.
+struct TileLists {
+    unsigned long long near[kTileMaxP / 64];
+    unsigned short list[kTileMaxP];
+    int n_near;
+};
+
+template <class F>
+__device__ __forceinline__ void tile_lists(TileLists& L, int np, F&& isfar)
+{
+    constexpr int NTH = 256;
+    const int tid = threadIdx.x;
+    const int words = (np + 63) >> 6;
+    for (int p0 = 0; p0 < np; p0 += NTH) {  // uniform trip count
+        const int p = p0 + tid;
+        const bool nr = p < np && !isfar(p);
+        const unsigned long long m = __ballot(nr);
+        if (lane_id() == 0 && (p >> 6) < words) L.near[p >> 6] = m;
+    }
+    __syncthreads();
+    int total = 0;
+    for (int w = 0; w < words; w++) total += __popcll(L.near[w]);
+    for (int p = tid; p < np; p += NTH) {
+        const int w = p >> 6;
+        int before = 0;
+        for (int k = 0; k < w; k++) before += __popcll(L.near[k]);
+        const unsigned long long m = L.near[w];
+        before += __popcll(m & ((1ull << (p & 63)) - 1ull));
+        if ((m >> (p & 63)) & 1ull)
+            L.list[before] = (unsigned short)p;
+        else
+            L.list[total + p - before] = (unsigned short)p;
+    }
+    if (tid == 0) L.n_near = total;
+    __syncthreads();
+}
+
+// Runs f(p) for the list entries [k0, k1) with a wave-uniform p; all 64 lanes
+// call it.  64 entries are loaded at a time, one per lane.
+template <class F>
+__device__ __forceinline__ void for_list(const unsigned short* list, int k0, int k1, F&& f)
+{
+    for (int b = k0; b < k1; b += 64) {
+        const int cnt = min(64, k1 - b);
+        const int mine = lane_id() < cnt ? (int)list[b + lane_id()] : 0;
+        for (int k = 0; k < cnt; k++) f(__builtin_amdgcn_readlane(mine, k));
+    }
+}
+
+// FP64 constants of one potential in wave-uniform registers (the first ten
+// values of its table row; the cut radius is 0 for an uncut profile only).
+struct Far64 {
+    double xc, yc, A, B, C, a2, s2, ra, rs, K;
+};
+static_assert(T64_K == 9 && T64_RS == 8, "ten leading values");
+
+__device__ __forceinline__ Far64 load_far(const double* __restrict__ t)
+{
+    return {t[T64_XC], t[T64_YC], t[T64_A],  t[T64_B],  t[T64_C],
+            t[T64_A2], t[T64_S2], t[T64_RA], t[T64_RS], t[T64_K]};
+}
+
+// FP64 deflection of a far potential with the hardware root and reciprocal
+// estimates unrefined (relative error 2^-24, the FP32 unit roundoff): the far
+// part of an FP32 field.  Three such factors and no other rounding above 2^-52
+// leave it within about 4 u w_p.
+__device__ __forceinline__ void add_alpha_est(const Far64& p, double t1, double t2, double& s1, double& s2)
+{
+    const double d1 = t1 - p.xc, d2 = t2 - p.yc;
+    const double m1 = fma(p.A, d1, p.B * d2);
+    const double m2 = fma(p.B, d1, p.C * d2);
+    const double R2 = fma(d1, m1, d2 * m2);
+    const double a2 = p.a2 + R2;
+    const double qa = fma(a2, __builtin_amdgcn_rsq(a2), p.ra);
+    double f;
+    if (__double_as_longlong(p.rs) == 0) {  // uncut (a scalar test)
+        f = __builtin_amdgcn_rcp(qa);
+    } else {
+        const double b2 = p.s2 + R2;
+        const double qs = fma(b2, __builtin_amdgcn_rsq(b2), p.rs);
+        f = (qs - qa) * __builtin_amdgcn_rcp(qa * qs);
+    }
+    const double kf = p.K * f;
+    s1 = fma(kf, m1, s1);
+    s2 = fma(kf, m2, s2);
+}
+
+// Sum of the far potentials list[k0..k1) at (t1, t2), two at a time: the next
+// pair's constants (scalar loads, a few hundred cycles away) are requested
+// before the current pair is evaluated.
+__device__ __forceinline__ void far_sum(const double* __restrict__ tab64, const unsigned short* list, int k0, int k1,
+                                        double t1, double t2, double& s1, double& s2)
+{
+    for (int b = k0; b < k1; b += 64) {
+        const int cnt = min(64, k1 - b), last = cnt - 1;
+        const int mine = lane_id() < cnt ? (int)list[b + lane_id()] : 0;
+        auto row = [&](int k) { return tab64 + (size_t)__builtin_amdgcn_readlane(mine, min(k, last)) * T64_STRIDE; };
+        Far64 n0 = load_far(row(0)), n1 = load_far(row(1));
+        for (int k = 0; k < cnt; k += 2) {
+            const Far64 c0 = n0, c1 = n1;
+            n0 = load_far(row(k + 2));
+            n1 = load_far(row(k + 3));
+            add_alpha_est(c0, t1, t2, s1, s2);
+            if (k < last) add_alpha_est(c1, t1, t2, s1, s2);
+        }
+    }
+}
+
+// Minimum / maximum over groups of 8 consecutive lanes (every lane gets it).
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <typename V>
+__device__ __forceinline__ V min8(V v)
+{
+    v = fmin(v, dpp_mov<0xB1>(v));   // lane ^ 1
+    v = fmin(v, dpp_mov<0x4E>(v));   // lane ^ 2
+    return fmin(v, dpp_mov<0x141>(v));  // the other half of the 8 lanes
+}
+template <typename V>
+__device__ __forceinline__ V max8(V v)
+{
+    v = fmax(v, dpp_mov<0xB1>(v));
+    v = fmax(v, dpp_mov<0x4E>(v));
+    return fmax(v, dpp_mov<0x141>(v));
+}
+
+// Range record of one block of 32 x 8 nodes (kRec values): the deflection
+// range over the block's nodes (min ax, max ax, min ay, max ay), over its first
+// row, over its first column, and the first node's deflection; nodes outside
+// the grid do not count.  A triangle tile's range is the union of its blocks',
+// the first columns of the blocks to their right, the first rows of the blocks
+// above and the first node of the block diagonally above (tile_range_rec).
+//
+// Writes the two records of a unit of 32 x 16 nodes held by one wave: lane l
+// holds row l % 16, columns 4 (l / 16) + r and 16 + 4 (l / 16) + r (v[r], v[4 + r]).
+// All 64 lanes call it.
+template <typename V>
+__device__ __forceinline__ void write_records(const V* sx, const V* sy, int i0, int j0, int nx, int ny, int nbx,
+                                              V* __restrict__ rec)
+{
+    const int lane = lane_id(), q = lane >> 4, row = lane & 15;
+    V a = V(INFINITY), b = V(-INFINITY), c = V(INFINITY), d = V(-INFINITY);
+    const bool rin = j0 + row < ny;
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        const int col = i0 + (k >> 2) * 16 + 4 * q + (k & 3);
+        if (rin && col < nx) {
+            a = fmin(a, sx[k]);
+            b = fmax(b, sx[k]);
+            c = fmin(c, sy[k]);
+            d = fmax(d, sy[k]);
+        }
+    }
+    // first column: lanes 0..15 hold it as v[0]; the others bring nothing
+    const bool fc = q == 0 && rin;
+    const V fx0 = min8(fc ? sx[0] : V(INFINITY)), fx1 = max8(fc ? sx[0] : V(-INFINITY));
+    const V fy0 = min8(fc ? sy[0] : V(INFINITY)), fy1 = max8(fc ? sy[0] : V(-INFINITY));
+#pragma unroll
+    for (int m = 16; m <= 32; m <<= 1) {
+        a = fmin(a, __shfl_xor(a, m, 64));
+        b = fmax(b, __shfl_xor(b, m, 64));
+        c = fmin(c, __shfl_xor(c, m, 64));
+        d = fmax(d, __shfl_xor(d, m, 64));
+    }
+    // a..d: the row's range, in every lane of the row
+    const V A = min8(a), B = max8(b), C = min8(c), D = max8(d);
+    if ((lane & 7) == 0 && q == 0 && rin && i0 < nx) {
+        V* o = rec + ((size_t)((j0 + row) >> 3) * nbx + (i0 >> 5)) * kRec;
+        o[0] = A;
+        o[1] = B;
+        o[2] = C;
+        o[3] = D;
+        o[4] = a;
+        o[5] = b;
+        o[6] = c;
+        o[7] = d;
+        o[8] = fx0;
+        o[9] = fx1;
+        o[10] = fy0;
+        o[11] = fy1;
+        o[12] = sx[0];
+        o[13] = sy[0];
+    }
+}
+
+// Stores a wave's unit (layout of write_records) to the field planes.
+template <typename V>
+__device__ __forceinline__ void store_unit(const V* s, V* __restrict__ out, int i0, int j0, int nx, int ny, bool vec)
+{
+    typedef V vec4 __attribute__((ext_vector_type(4)));
+    const int lane = lane_id(), j = j0 + (lane & 15);
+    if (j >= ny) return;
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+        const int i = i0 + 16 * b + 4 * (lane >> 4);
+        V* o = out + (size_t)j * nx + i;
+        if (vec && i + 3 < nx) {
+            *reinterpret_cast<vec4*>(o) = vec4{s[4 * b], s[4 * b + 1], s[4 * b + 2], s[4 * b + 3]};
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                if (i + r < nx) o[r] = s[4 * b + r];
+        }
+    }
+}
+
+// ---------------------------------------------------------------- FP32 tiles
+
+// One tile of T x T nodes per workgroup of 256 threads.
+template <int T>
+struct Tile32 {
+    static constexpr int NW = 4;  // waves
+    struct Lds {
+        TileLists lists;
+        double part[NW][2][64];
+        double coef[2][64];
+        float cheb[8][T];
+        float g[16][T];
+        float c00[2];
+    };
+};
+
+// The FP32 field of the tile at node (i0, j0) by a workgroup of 256 threads.
+//   1. lists (FP32 criterion, one potential per thread);
+//   2. far sum at the 8 x 8 Chebyshev points, lane = point, the waves sharing
+//      the far list, in FP64 with unrefined estimates (add_alpha_est);
+//   3. Chebyshev coefficients (two 8-point transforms per component, FP64),
+//      then per node row the 8 coefficients in x (FP64, stored as FP32); the
+//      constant term is kept apart, so that what is interpolated is the
+//      variation over the tile and its rounding is relative to that;
+//   4. per unit of 32 x 16 nodes: interpolation in x as a matrix product
+//      (v_mfma_f32_16x16x4f32, x nodes by rows, inner index the coefficient),
+//      near potentials per node, the constant term last.
+template <int T>
+__device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const double* __restrict__ tab64,
+                                            const float* __restrict__ tab32, int np, const GridDesc& g, int i0,
+                                            int j0, float* __restrict__ ax, float* __restrict__ ay,
+                                            bool bad, float* __restrict__ rec, int nbx)
+{
+    constexpr int NW = Tile32<T>::NW, NTH = 64 * NW;
+    const int tid = threadIdx.x;
+    constexpr float hw = 0.5f * (T - 1);
+    const int lane = lane_id(), wt = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float xc = (float)i0 + hw, yc = (float)j0 + hw;
+    tile_lists(L.lists, np, [&](int p) {
+        const float* c = tab32 + (size_t)p * T32_STRIDE;
+        return tab64[(size_t)p * T64_STRIDE + T64_S2] <= 1e300 &&  // a cut radius whose square overflows: FP32 form
+               tile_far((xc - c[T32_CXH]) - c[T32_CXL], (yc - c[T32_CYH]) - c[T32_CYL], c[T32_A], c[T32_B], c[T32_C],
+                        c[T32_A2], hw, kFarC32);
+    });
+    const int nn = __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
+    {
+        const double t1 = g.x0 + ((double)xc + kDct8.xi[lane & 7] * hw) * g.h;
+        const double t2 = g.y0 + ((double)yc + kDct8.xi[lane >> 3] * hw) * g.h;
+        double s1 = 0.0, s2 = 0.0;
+        far_sum(tab64, L.lists.list + nn, wt * nf / NW, (wt + 1) * nf / NW, t1, t2, s1, s2);
+        L.part[wt][0][lane] = s1;
+        L.part[wt][1][lane] = s2;
+    }
+    __syncthreads();
+    for (int c = wt; c < 2; c += NW) {  // component c: one wave each
+        double v = L.part[0][c][lane];
+        for (int w = 1; w < NW; w++) v += L.part[w][c][lane];
+        L.coef[c][lane] = v;
+        wave_lds_sync();
+        const int a = lane & 7, k = lane >> 3;
+        double u = 0.0;  // transform in x: point index lane & 7
+        for (int m = 0; m < 8; m++) u = fma(kDct8.d[8 * a + m], L.coef[c][8 * k + m], u);
+        wave_lds_sync();
+        L.coef[c][lane] = u;  // [k][a]
+        wave_lds_sync();
+        double w = 0.0;  // transform in y: coefficient b = k
+        for (int m = 0; m < 8; m++) w = fma(kDct8.d[8 * k + m], L.coef[c][8 * m + a], w);
+        wave_lds_sync();
+        if (lane == 0) {
+            L.c00[c] = (float)w;
+            w -= (double)(float)w;  // the constant's rounding stays in the interpolated part
+        }
+        L.coef[c][lane] = w;  // [b][a]
+    }
+    __syncthreads();
+    {
+        const int row = tid % T;
+        double tb[8];
+        const double y = ((double)row - hw) / (double)hw;
+        tb[0] = 1.0;
+        tb[1] = y;
+#pragma unroll
+        for (int b = 2; b < 8; b++) tb[b] = fma(2.0 * y, tb[b - 1], -tb[b - 2]);
+        if (tid < T)
+#pragma unroll
+            for (int b = 0; b < 8; b++) L.cheb[b][row] = (float)tb[b];
+        for (int q = tid / T; q < 16; q += NTH / T) {  // (component, a)
+            const double* co = L.coef[q >> 3] + (q & 7);
+            double v = 0.0;
+#pragma unroll
+            for (int b = 7; b >= 0; b--) v = fma(co[8 * b], tb[b], v);
+            L.g[q][row] = (float)v;
+        }
+    }
+    __syncthreads();
+    constexpr int UX = T / 32, UNITS = UX * (T / 16);
+    const int li = lane & 15, lk = lane >> 4;
+    const bool vec = (g.nx & 3) == 0 && (((size_t)ax | (size_t)ay) & 15) == 0;
+    for (int u = wt; u < UNITS; u += NW) {
+        const int cu = (u % UX) * 32, ru = (u / UX) * 16;
+        if (i0 + cu >= g.nx || j0 + ru >= g.ny) continue;
+        floatx4 acc[2][2];  // [component][column block]
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                acc[c][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int k = 1; k >= 0; k--)
+                    acc[c][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(L.cheb[4 * k + lk][cu + 16 * b + li],
+                                                                     L.g[8 * c + 4 * k + lk][ru + li], acc[c][b], 0,
+                                                                     0, 0);
+            }
+        float sx[8], sy[8], fi[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            sx[k] = acc[0][k >> 2][k & 3];
+            sy[k] = acc[1][k >> 2][k & 3];
+            fi[k] = (float)(i0 + cu + 16 * (k >> 2) + 4 * lk + (k & 3));
+        }
+        const float fj = (float)(j0 + ru + li);
+        for_list(L.lists.list, 0, nn, [&](int p) {
+            const float* c = tab32 + (size_t)p * T32_STRIDE;
+            const float nyv = (fj - c[T32_CYH]) - c[T32_CYL];
+            const float4 rc =
+                make_float4(c[T32_BP] * nyv, c[T32_CQ] * nyv, fmaf(c[T32_DQ] * nyv, nyv, c[T32_A2]), c[T32_RSK]);
+            field32_pot<8, 1>(c, &rc, fi, sx, sy);
+        });
+        const float cx = L.c00[0], cy = L.c00[1];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            sx[k] = bad ? __builtin_nanf("") : sx[k] + cx;
+            sy[k] = bad ? __builtin_nanf("") : sy[k] + cy;
+        }
+        if (rec) write_records(sx, sy, i0 + cu, j0 + ru, g.nx, g.ny, nbx, rec);
+        store_unit(sx, ax, i0 + cu, j0 + ru, g.nx, g.ny, vec);
+        store_unit(sy, ay, i0 + cu, j0 + ru, g.nx, g.ny, vec);
+    }
+}
+
+}  // namespace lens

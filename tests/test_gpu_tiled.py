@@ -1,0 +1,82 @@
+"""GPU parity of the tiled deflection field (near potentials per node, the far
+ones through one Chebyshev polynomial per tile) against the FP64 CPU oracle, at
+the edges of its tiles and of the rule that selects it: grids a node short of,
+on and past multiples of the tile sides, thin grids, few and many potentials,
+every profile kind, centres on nodes and outside the grid.
+
+Bar in FP32: the library's stated FP32 deflection bound (test_gpu_parity).  The
+oracle evaluates sampled rows: the first and last two, and the rows around
+every kind of tile boundary."""
+import numpy as np
+import pytest
+
+import oracle
+import synthlens as S
+from test_gpu_parity import fp32_alpha_bound
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lens():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    import paper_1902_03252_amd as lens
+    lens.context()
+    return lens
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda")
+
+
+def potentials(grid, p, seed):
+    """Galaxies of every profile kind over a field a little wider than the grid, one halo, one centre exactly on a
+    node, one 1e-9 nodes off a node, and one with a cut radius whose square overflows."""
+    g = np.random.default_rng(seed)
+    lx, ly = 0.5 * (grid.nx - 1) * grid.h, 0.5 * (grid.ny - 1) * grid.h
+    prm = S.draw_galaxies(g, p, 1.0)
+    prm[0] = grid.x0 + lx + 1.2 * lx * prm[0]
+    prm[1] = grid.y0 + ly + 1.2 * ly * prm[1]
+    kind = g.integers(0, 4, p)
+    prm[4, kind % 2 == 1] = 0.0
+    prm[5, kind // 2 == 1] = np.inf
+    prm[:, 0] = (grid.x0 + lx, grid.y0 + ly, 0.05, 0.3, 5.0, 1000.0, 1000.0)
+    prm[0, 1], prm[1, 1] = grid.x0 + (grid.nx // 3) * grid.h, grid.y0 + (grid.ny // 2) * grid.h
+    prm[0, 2], prm[1, 2] = prm[0, 1] + 1e-9 * grid.h, prm[1, 1] - grid.h
+    prm[5, 3] = 1e160
+    prm[2, p // 2] = 0.95
+    return prm
+
+
+def sampled_rows(ny, g):
+    rows = {0, 1, ny - 2, ny - 1} | {r + d for r in (32, 64, 128, 256) for d in (-1, 0, 1)}
+    rows |= set(int(v) for v in g.integers(0, ny, 4))
+    return sorted(r for r in rows if 0 <= r < ny - 1)
+
+
+def check_rows(ax, ay, prm, grid, tol, what):
+    worst = 0.0
+    for j in sampled_rows(grid.ny, np.random.default_rng(1)):
+        sub = S.Grid(grid.x0, grid.y0 + j * grid.h, grid.h, grid.nx, 2)
+        ox, oy = oracle.alpha_grid(prm, sub)
+        for got, want in ((ax, ox), (ay, oy)):
+            worst = max(worst, np.abs(got[j:j + 2].double().cpu().numpy() - want).max())
+    print(f"  {what}: max err {worst:.2e} (bar {tol:.2e})", flush=True)
+    assert worst <= tol
+
+
+# (nx, ny, P): the rule's sides 32, 64 and 128 and both of its limits in P
+SHAPES = [(512, 512, 64), (513, 511, 70), (545, 481, 80), (1025, 1023, 40), (2049, 1500, 120), (1999, 2113, 700),
+          (40007, 9, 60), (9, 40007, 60), (2300, 2300, 4), (2300, 2300, 3), (300, 280, 2048), (300, 280, 2049)]
+
+
+@pytest.mark.parametrize("nx,ny,p", SHAPES)
+def test_tiled_fp32_field(lens, nx, ny, p):
+    grid = S.Grid(-61.3, -47.9, 120.0 / max(nx, ny), nx, ny)
+    prm = potentials(grid, p, nx + p) if p > 3 else potentials(grid, 4, nx)[:, :p]
+    ax, ay = lens.lens_deflect(dev(prm), grid, "fp32")
+    prm = prm.copy()
+    prm[5, prm[5] > 1e100] = np.inf  # the oracle squares the cut radius
+    check_rows(ax, ay, prm, grid, fp32_alpha_bound(prm, grid), f"fp32 {nx}x{ny} P={p}")
