@@ -418,10 +418,14 @@ int lens_deflect(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* gri
     const KernelEvents* ev;
     if ((rc = timing_begin(ctx, &kev, &ev, &slot))) return rc;
     hipError_t e;
-    if (prec == LENS_FP64)
+    const int side = tiled_side(g, pot->n, prec != LENS_FP64);
+    if (prec == LENS_FP64 && side)
+        e = launch_tiled64(side, (const double*)ctx->buf[B_TAB64], (const float*)ctx->buf[B_TAB32], pot->n, g,
+                           (double*)ax, (double*)ay, st, nullptr, nullptr, ev, stream);
+    else if (prec == LENS_FP64)
         e = launch_field64((const double*)ctx->buf[B_TAB64], pot->n, g, (double*)ax, (double*)ay, st, nullptr, 5, 1,
                            ev, stream);
-    else if (const int side = tiled_side(g, pot->n))
+    else if (side)
         e = launch_tiled32(side, (const double*)ctx->buf[B_TAB64], (const float*)ctx->buf[B_TAB32], pot->n, g,
                            (float*)ax, (float*)ay, st, nullptr, nullptr, ev, stream);
     else
@@ -597,7 +601,7 @@ int chi2_plan(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* grid, 
     pl.vbytes = pl.mixed ? 4 : 8;
     pl.flag_cap = pl.mixed ? flag_cap : 0;
     // the head's source-plane part runs inside the field launch when the grid allows
-    pl.side = pl.mixed ? tiled_side(pl.g, pl.np) : 0;
+    pl.side = tiled_side(pl.g, pl.np, pl.mixed);
     pl.fused = pl.side || fused_head_fits(pl.g, pl.o, pl.npl, pl.mixed) != 0;
     size_t* b = pl.bytes;
     b[CB_STATE] = sizeof(EvalState);
@@ -671,6 +675,9 @@ int chi2_run(lens_ctx* ctx, const Chi2Plan& pl, const Chi2Bufs& b, const lens_po
     if (mixed && pl.side)
         e = launch_tiled32(pl.side, tab64, tab32, np, g, (float*)field, (float*)field + nn, nullptr, (float*)rr, &ha,
                            ev, stream);
+    else if (pl.side)
+        e = launch_tiled64(pl.side, tab64, tab32, np, g, (double*)field, (double*)field + nn, nullptr, (double*)rr,
+                           &ha, ev, stream);
     else if (mixed && pl.fused)
         e = launch_field32h(tab32, np, g, (float*)field, (float*)field + nn, pl.npl, (float*)rr, pl.tx_shift,
                             pl.tiles_x, ha, ev, stream);

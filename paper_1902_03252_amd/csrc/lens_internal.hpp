@@ -110,11 +110,15 @@ inline bool bfield_code_ok(int code)
 
 // Field by tiles of side x side nodes (lens_tiles.hpp); rec: 32 x 8 block
 // records or null; h: the head's arguments (fused head) or null.
-int tiled_side(const GridDesc& g, int np);  // 0: direct field
+int tiled_side(const GridDesc& g, int np, bool fp32);  // 0: direct field
+int tile_side_for(double nodes, double total, int np, bool fp32);
 inline int rec_nbx(const GridDesc& g) { return (g.nx + 31) / 32; }
 inline int rec_nby(const GridDesc& g) { return (g.ny + 7) / 8; }
 hipError_t launch_tiled32(int side, const double* tab64, const float* tab32, int np, const GridDesc& g, float* ax,
                           float* ay, const EvalState* st, float* rec, const HeadArgs* h, const KernelEvents* ev,
+                          hipStream_t s);
+hipError_t launch_tiled64(int side, const double* tab64, const float* tab32, int np, const GridDesc& g, double* ax,
+                          double* ay, const EvalState* st, double* rec, const HeadArgs* h, const KernelEvents* ev,
                           hipStream_t s);
 
 hipError_t launch_field32h(const float* tab32, int np, const GridDesc& g, float* ax, float* ay, int npl, float* rr,

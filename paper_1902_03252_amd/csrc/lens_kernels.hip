@@ -407,7 +407,26 @@ __global__ __launch_bounds__(256) void k_tiled32(const double* __restrict__ tab6
     }
     const int tile = blockIdx.x - head_blocks, tj = tile / ntx, ti = tile - tj * ntx;
     const bool bad = st != nullptr && st->status != kStatusOk;
-    tile32_body<T>(*reinterpret_cast<Lds*>(lds.raw), tab64, tab32, np, g, ti * T, tj * T, ax, ay, bad, rec, nbx);
+    tile32_body<T>(*reinterpret_cast<Lds*>(lds.raw), IsoProfile{tab64, tab32}, np, g, ti * T, tj * T, ax, ay, bad,
+                   rec, nbx);
+}
+
+template <int T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_tiled64(const double* __restrict__ tab64, const float* __restrict__ tab32,
+                                                 int np, GridDesc g, int ntx, double* __restrict__ ax,
+                                                 double* __restrict__ ay, const EvalState* __restrict__ st,
+                                                 double* __restrict__ rec, int nbx, HeadArgs h, int head_blocks)
+{
+    using Lds = typename Tile64<T>::Lds;
+    __shared__ FusedLds<fused_lds_bytes((int)sizeof(Lds))> lds;
+    if ((int)blockIdx.x < head_blocks) {
+        fused_head(*reinterpret_cast<HeadLds*>(lds.raw), h, blockIdx.x, head_blocks);
+        return;
+    }
+    const int tile = blockIdx.x - head_blocks, tj = tile / ntx, ti = tile - tj * ntx;
+    const bool bad = st != nullptr && st->status != kStatusOk;
+    tile64_body<T>(*reinterpret_cast<Lds*>(lds.raw), IsoProfile{tab64, tab32}, np, g, ti * T, tj * T, ax, ay, bad,
+                   rec, nbx);
 }
 
 // ============================================================== triangle stage
@@ -1129,26 +1148,41 @@ hipError_t launch_field64h(const double* tab64, int np, const GridDesc& g, doubl
 // Workgroups of the fused head in a tiled launch: one wave per observed image.
 static int head_blocks_for(const ObsPtrs& obs) { return obs.n_img > 0 ? (int)cdiv(obs.n_img, 4) : 1; }
 
-// Tile side of the tiled FP32 field, 0 for the direct field.  The tiled kernel
-// has about 10 us of its own chain (lists, Chebyshev points, transforms), so it
-// pays from about 2^24 node-potential terms on (512^2 x 50: 11.8 us against 11.7
-// direct; 1024^2 x 50: 13.5 against 31.1; 411 x 300 x 50: 14.1 against 10.2), and
-// with fewer than 4 potentials there is nothing to share.  The side trades far
-// work (P 64 / T^2 profile evaluations per node, at 116 cycles per 64) against
-// near work (potentials within 3.6 half widths, taken as uniform over the grid,
-// at 75 cycles) with the rest at 60, and must leave enough workgroups: the
-// longer of the chip's throughput and one workgroup's own chain counts.
-int tiled_side(const GridDesc& g, int np)
+// Tile side of a tiled field, 0 for the direct field.  The tiled kernels have a
+// chain of their own (lists, Chebyshev points, transforms: about 10 us in FP32,
+// 25 us in FP64), so they pay from about 2^24 node-potential terms on (tiled
+// against direct, FP32: 512^2 x 50 11.8 / 11.7 us, 1024^2 x 50 13.5 / 31.1, 411 x
+// 300 x 50 14.1 / 10.2; FP64: 512^2 x 50 27.6 / 29.9, 512^2 x 100 41 / 53,
+// 1024^2 x 50 38 / 82), and with fewer than 4 potentials there is nothing to share.
+// The side trades far work (P N^2 / T^2 profile evaluations per node) against
+// near work (potentials within about c + 1 half widths, taken as uniform over the
+// grid), and must leave enough workgroups: the longer of the chip's throughput
+// and one workgroup's own chain counts.  Cycles per 64 nodes and potential from
+// the instruction counts: FP32 116 far, 75 near, 60 for the rest; FP64 180, 200, 200.
+int tiled_side(const GridDesc& g, int np, bool fp32)
 {
     const double nodes = (double)g.nx * g.ny;
     if (np < 4 || np > kTileMaxP || nodes * np < (double)(1 << 24)) return 0;
+    return tile_side_for(nodes, nodes, np, fp32);
+}
+
+// The best side for a grid of `nodes` nodes in a launch of `total` nodes.
+int tile_side_for(double nodes, double total, int np, bool fp32)
+{
     int best = 0;
     double cost = 0.0;
     for (int t = 32; t <= 128; t *= 2) {
-        const double near = std::min((double)np, 1.0 + np * kPi * 3.24 * t * t / nodes);
-        const double units = std::max(1.0, t * t / 2048.0);  // units of 512 nodes per wave
-        const double all = nodes / 64.0 * (75.0 * near + 116.0 * 64.0 * np / ((double)t * t) + 60.0) / 1024.0;
-        const double chain = 6000.0 + 62.0 * np + units * (600.0 + 640.0 * near);
+        const double t2 = (double)t * t, units = std::max(1.0, t2 / 2048.0);  // units of 512 nodes per wave
+        double all, chain;
+        if (fp32) {
+            const double near = std::min((double)np, 1.0 + np * kPi * 3.24 * t2 / nodes);
+            all = total / 64.0 * (75.0 * near + 116.0 * 64.0 * np / t2 + 60.0) / 1024.0;
+            chain = 6000.0 + 62.0 * np + units * (600.0 + 640.0 * near);
+        } else {
+            const double near = std::min((double)np, 1.0 + np * kPi * 6.5 * t2 / nodes);
+            all = total / 64.0 * (200.0 * near + 180.0 * 256.0 * np / t2 + 200.0) / 1024.0;
+            chain = 8000.0 + 300.0 * np + units * (800.0 + 1600.0 * near);
+        }
         const double c = std::max(all, chain);
         if (!best || c < cost) {
             best = t;
@@ -1168,6 +1202,25 @@ hipError_t launch_tiled32(int side, const double* tab64, const float* tab32, int
     auto go = [&](auto t) {
         constexpr int T = decltype(t)::value;
         return launch_ev(ev, k_tiled32<T>, dim3(n_tiles + hb), dim3(256), s, tab64, tab32, np, g, ntx, ax, ay, st, rec, rec_nbx(g), ha, hb);
+    };
+    switch (side) {
+    case 32: return go(std::integral_constant<int, 32>());
+    case 64: return go(std::integral_constant<int, 64>());
+    default: return go(std::integral_constant<int, 128>());
+    }
+}
+
+hipError_t launch_tiled64(int side, const double* tab64, const float* tab32, int np, const GridDesc& g, double* ax,
+                          double* ay, const EvalState* st, double* rec, const HeadArgs* h, const KernelEvents* ev,
+                          hipStream_t s)
+{
+    const int ntx = (int)cdiv(g.nx, side), n_tiles = ntx * (int)cdiv(g.ny, side);
+    const int hb = h ? head_blocks_for(h->obs) : 0;
+    const HeadArgs ha = h ? *h : HeadArgs{};
+    auto go = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        return launch_ev(ev, k_tiled64<T>, dim3(n_tiles + hb), dim3(256), s, tab64, tab32, np, g, ntx, ax, ay, st,
+                         rec, rec_nbx(g), ha, hb);
     };
     switch (side) {
     case 32: return go(std::integral_constant<int, 32>());

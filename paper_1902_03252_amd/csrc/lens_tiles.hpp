@@ -143,14 +143,15 @@ __device__ __forceinline__ void tile_lists(TileLists& L, int np, F&& isfar)
     __syncthreads();
 }
 
-// Runs f(p) for the list entries [k0, k1) with a wave-uniform p; all 64 lanes
-// call it.  64 entries are loaded at a time, one per lane.
+// Runs f(p) for the list entries [0, n), or for p = 0 .. n - 1 without a list,
+// with a wave-uniform p; all 64 lanes call it.  64 entries are loaded at a
+// time, one per lane.
 template <class F>
-__device__ __forceinline__ void for_list(const unsigned short* list, int k0, int k1, F&& f)
+__device__ __forceinline__ void for_list(const unsigned short* list, bool has_list, int n, F&& f)
 {
-    for (int b = k0; b < k1; b += 64) {
-        const int cnt = min(64, k1 - b);
-        const int mine = lane_id() < cnt ? (int)list[b + lane_id()] : 0;
+    for (int b = 0; b < n; b += 64) {
+        const int cnt = min(64, n - b);
+        const int mine = has_list && lane_id() < cnt ? (int)list[b + lane_id()] : b + lane_id();
         for (int k = 0; k < cnt; k++) f(__builtin_amdgcn_readlane(mine, k));
     }
 }
@@ -168,23 +169,36 @@ __device__ __forceinline__ Far64 load_far(const double* __restrict__ t)
             t[T64_A2], t[T64_S2], t[T64_RA], t[T64_RS], t[T64_K]};
 }
 
-// FP64 deflection of a far potential with the hardware root and reciprocal
-// estimates unrefined (relative error 2^-24, the FP32 unit roundoff): the far
-// part of an FP32 field.  Three such factors and no other rounding above 2^-52
-// leave it within about 4 u w_p.
-__device__ __forceinline__ void add_alpha_est(const Far64& p, double t1, double t2, double& s1, double& s2)
+// FP64 deflection of a far potential at the point c + e (FULL: the arithmetic of
+// add_alpha64; c + e and not one coordinate, so that the offset from the
+// potential is rounded relative to itself) or at the point c (!FULL).  !FULL: the
+// hardware root and reciprocal estimates unrefined (relative error 2^-24, the FP32 unit roundoff),
+// for the far part of an FP32 field: three such factors and no other rounding
+// above 2^-52 leave it within about 4 u w_p.
+template <bool FULL, bool CUT>
+__device__ __forceinline__ void add_far(const Far64& p, double c1, double c2, double e1, double e2, double& s1,
+                                        double& s2)
 {
-    const double d1 = t1 - p.xc, d2 = t2 - p.yc;
+    double d1 = c1 - p.xc, d2 = c2 - p.yc;
+    if constexpr (FULL) {
+        d1 += e1;
+        d2 += e2;
+    }
     const double m1 = fma(p.A, d1, p.B * d2);
     const double m2 = fma(p.B, d1, p.C * d2);
     const double R2 = fma(d1, m1, d2 * m2);
-    const double a2 = p.a2 + R2;
-    const double qa = fma(a2, __builtin_amdgcn_rsq(a2), p.ra);
-    double f;
-    if (__double_as_longlong(p.rs) == 0) {  // uncut (a scalar test)
-        f = __builtin_amdgcn_rcp(qa);
+    const double a2 = p.a2 + R2, b2 = p.s2 + R2;
+    double qa, f;
+    if constexpr (FULL)
+        qa = sqrt_est64(a2) + p.ra;
+    else
+        qa = fma(a2, __builtin_amdgcn_rsq(a2), p.ra);
+    if constexpr (!CUT) {
+        f = FULL ? rcp_est64(qa) : __builtin_amdgcn_rcp(qa);
+    } else if constexpr (FULL) {
+        const double qs = sqrt_est64(b2) + p.rs;
+        f = (qs - qa) * rcp_est64(qa * qs);
     } else {
-        const double b2 = p.s2 + R2;
         const double qs = fma(b2, __builtin_amdgcn_rsq(b2), p.rs);
         f = (qs - qa) * __builtin_amdgcn_rcp(qa * qs);
     }
@@ -193,25 +207,44 @@ __device__ __forceinline__ void add_alpha_est(const Far64& p, double t1, double 
     s2 = fma(kf, m2, s2);
 }
 
-// Sum of the far potentials list[k0..k1) at (t1, t2), two at a time: the next
-// pair's constants (scalar loads, a few hundred cycles away) are requested
-// before the current pair is evaluated.
+// Sum of the far potentials list[k0..k1) at c + e, two at a time: their
+// constants' scalar loads are in flight together, their evaluations (one serial
+// chain each) interleave when both are of one kind, and they go to two partial
+// sums.
+template <bool FULL>
 __device__ __forceinline__ void far_sum(const double* __restrict__ tab64, const unsigned short* list, int k0, int k1,
-                                        double t1, double t2, double& s1, double& s2)
+                                        double c1, double c2, double e1, double e2, double& s1, double& s2)
 {
+    double r1 = 0.0, r2 = 0.0;
     for (int b = k0; b < k1; b += 64) {
-        const int cnt = min(64, k1 - b), last = cnt - 1;
+        const int cnt = min(64, k1 - b);
         const int mine = lane_id() < cnt ? (int)list[b + lane_id()] : 0;
-        auto row = [&](int k) { return tab64 + (size_t)__builtin_amdgcn_readlane(mine, min(k, last)) * T64_STRIDE; };
-        Far64 n0 = load_far(row(0)), n1 = load_far(row(1));
-        for (int k = 0; k < cnt; k += 2) {
-            const Far64 c0 = n0, c1 = n1;
-            n0 = load_far(row(k + 2));
-            n1 = load_far(row(k + 3));
-            add_alpha_est(c0, t1, t2, s1, s2);
-            if (k < last) add_alpha_est(c1, t1, t2, s1, s2);
+        auto row = [&](int k) { return load_far(tab64 + (size_t)__builtin_amdgcn_readlane(mine, k) * T64_STRIDE); };
+        auto cut = [](const Far64& p) { return __double_as_longlong(p.rs) != 0; };
+        auto one = [&](const Far64& p, double& x, double& y) {
+            if (cut(p))
+                add_far<FULL, true>(p, c1, c2, e1, e2, x, y);
+            else
+                add_far<FULL, false>(p, c1, c2, e1, e2, x, y);
+        };
+        int k = 0;
+        for (; k + 2 <= cnt; k += 2) {
+            const Far64 p = row(k), q = row(k + 1);
+            if (cut(p) && cut(q)) {
+                add_far<FULL, true>(p, c1, c2, e1, e2, s1, s2);
+                add_far<FULL, true>(q, c1, c2, e1, e2, r1, r2);
+            } else if (!cut(p) && !cut(q)) {
+                add_far<FULL, false>(p, c1, c2, e1, e2, s1, s2);
+                add_far<FULL, false>(q, c1, c2, e1, e2, r1, r2);
+            } else {
+                one(p, s1, s2);
+                one(q, r1, r2);
+            }
         }
+        if (k < cnt) one(row(k), s1, s2);
     }
+    s1 += r1;
+    s2 += r2;
 }
 
 // Minimum / maximum over groups of 8 consecutive lanes (every lane gets it).
@@ -306,15 +339,22 @@ __device__ __forceinline__ void write_records(const V* sx, const V* sy, int i0, 
 template <typename V>
 __device__ __forceinline__ void store_unit(const V* s, V* __restrict__ out, int i0, int j0, int nx, int ny, bool vec)
 {
-    typedef V vec4 __attribute__((ext_vector_type(4)));
     const int lane = lane_id(), j = j0 + (lane & 15);
     if (j >= ny) return;
 #pragma unroll
     for (int b = 0; b < 2; b++) {
         const int i = i0 + 16 * b + 4 * (lane >> 4);
         V* o = out + (size_t)j * nx + i;
-        if (vec && i + 3 < nx) {
-            *reinterpret_cast<vec4*>(o) = vec4{s[4 * b], s[4 * b + 1], s[4 * b + 2], s[4 * b + 3]};
+        if (vec && i + 3 < nx) {  // 16-byte stores: nx is a multiple of 16 / sizeof(V)
+            constexpr int W = 16 / (int)sizeof(V);
+            typedef V vecw __attribute__((ext_vector_type(W)));
+#pragma unroll
+            for (int r = 0; r < 4; r += W) {
+                vecw v;
+#pragma unroll
+                for (int q = 0; q < W; q++) v[q] = s[4 * b + r + q];
+                *reinterpret_cast<vecw*>(o + r) = v;
+            }
         } else {
 #pragma unroll
             for (int r = 0; r < 4; r++)
@@ -322,6 +362,78 @@ __device__ __forceinline__ void store_unit(const V* s, V* __restrict__ out, int 
         }
     }
 }
+
+// ---------------------------------------------------------------- profiles
+
+// The isothermal family of the tables (tab64, tab32) as a tile's summand.
+struct IsoProfile {
+    const double* tab64;
+    const float* tab32;
+
+    __device__ __forceinline__ bool far(int p, float xc, float yc, float hw, float c) const
+    {
+        const float* r = tab32 + (size_t)p * T32_STRIDE;
+        // (a cut radius whose square overflows keeps the FP32 table's form)
+        return tab64[(size_t)p * T64_STRIDE + T64_S2] <= 1e300 &&
+               tile_far((xc - r[T32_CXH]) - r[T32_CXL], (yc - r[T32_CYH]) - r[T32_CYL], r[T32_A], r[T32_B], r[T32_C],
+                        r[T32_A2], hw, c);
+    }
+
+    // Sum of list[k0..k1) at c + e: for an FP32 field, or in full FP64.
+    template <bool FULL>
+    __device__ __forceinline__ void far_at(const unsigned short* list, int k0, int k1, double c1, double c2, double e1,
+                                           double e2, double& s1, double& s2) const
+    {
+        far_sum<FULL>(tab64, list, k0, k1, c1, c2, e1, e2, s1, s2);
+    }
+
+    // Adds potential p at 8 nodes of one row (per lane): node-unit columns fi, row fj.
+    __device__ __forceinline__ void near32(int p, const float* fi, float fj, float* sx, float* sy) const
+    {
+        const float* c = tab32 + (size_t)p * T32_STRIDE;
+        const float nyv = (fj - c[T32_CYH]) - c[T32_CYL];
+        const float4 rc =
+            make_float4(c[T32_BP] * nyv, c[T32_CQ] * nyv, fmaf(c[T32_DQ] * nyv, nyv, c[T32_A2]), c[T32_RSK]);
+        field32_pot<8, 1>(c, &rc, fi, sx, sy);
+    }
+    __device__ __forceinline__ void near64(int p, const double* t1, double t2, double* sx, double* sy) const
+    {
+        const Far64 c = load_far(tab64 + (size_t)p * T64_STRIDE);
+        if (__double_as_longlong(c.rs) == 0)
+            near64_nodes<false>(c, t1, t2, sx, sy);
+        else
+            near64_nodes<true>(c, t1, t2, sx, sy);
+    }
+    // add_alpha64 at 8 nodes, the profile kind decided once, four nodes' chains
+    // interleaved at a time (all eight would cost the occupancy its registers).
+    template <bool CUT>
+    __device__ __forceinline__ static void near64_nodes(const Far64& c, const double* t1, double t2, double* sx,
+                                                        double* sy)
+    {
+        const double d2 = t2 - c.yc, bd2 = c.B * d2, cd2 = c.C * d2;
+#pragma unroll
+        for (int q = 0; q < 8; q += 4) {
+#pragma unroll
+            for (int k = q; k < q + 4; k++) {
+                const double d1 = t1[k] - c.xc;
+                const double m1 = fma(c.A, d1, bd2), m2 = fma(c.B, d1, cd2);
+                const double R2 = fma(d1, m1, d2 * m2);
+                const double qa = sqrt_est64(fmax(fabs(c.a2 + R2), 1e-300)) + c.ra;
+                double f;
+                if constexpr (CUT) {
+                    const double qs = sqrt_est64(c.s2 + R2) + c.rs;
+                    f = (qs - qa) * rcp_est64(qa * qs);
+                } else {
+                    f = rcp_est64(qa);
+                }
+                const double kf = c.K * f;
+                sx[k] = fma(kf, m1, sx[k]);
+                sy[k] = fma(kf, m2, sy[k]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+};
 
 // ---------------------------------------------------------------- FP32 tiles
 
@@ -350,10 +462,9 @@ struct Tile32 {
 //   4. per unit of 32 x 16 nodes: interpolation in x as a matrix product
 //      (v_mfma_f32_16x16x4f32, x nodes by rows, inner index the coefficient),
 //      near potentials per node, the constant term last.
-template <int T>
-__device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const double* __restrict__ tab64,
-                                            const float* __restrict__ tab32, int np, const GridDesc& g, int i0,
-                                            int j0, float* __restrict__ ax, float* __restrict__ ay,
+template <int T, class P>
+__device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const P& prof, int np, const GridDesc& g,
+                                            int i0, int j0, float* __restrict__ ax, float* __restrict__ ay,
                                             bool bad, float* __restrict__ rec, int nbx)
 {
     constexpr int NW = Tile32<T>::NW, NTH = 64 * NW;
@@ -361,18 +472,15 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const do
     constexpr float hw = 0.5f * (T - 1);
     const int lane = lane_id(), wt = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float xc = (float)i0 + hw, yc = (float)j0 + hw;
-    tile_lists(L.lists, np, [&](int p) {
-        const float* c = tab32 + (size_t)p * T32_STRIDE;
-        return tab64[(size_t)p * T64_STRIDE + T64_S2] <= 1e300 &&  // a cut radius whose square overflows: FP32 form
-               tile_far((xc - c[T32_CXH]) - c[T32_CXL], (yc - c[T32_CYH]) - c[T32_CYL], c[T32_A], c[T32_B], c[T32_C],
-                        c[T32_A2], hw, kFarC32);
-    });
-    const int nn = __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
+    // beyond the lists' capacity every potential counts as near, in order
+    const bool all = np > kTileMaxP;
+    if (!all) tile_lists(L.lists, np, [&](int p) { return prof.far(p, xc, yc, hw, kFarC32); });
+    const int nn = all ? np : __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
     {
-        const double t1 = g.x0 + ((double)xc + kDct8.xi[lane & 7] * hw) * g.h;
-        const double t2 = g.y0 + ((double)yc + kDct8.xi[lane >> 3] * hw) * g.h;
+        const double c1 = g.x0 + (double)xc * g.h, c2 = g.y0 + (double)yc * g.h, half = (double)hw * g.h;
         double s1 = 0.0, s2 = 0.0;
-        far_sum(tab64, L.lists.list + nn, wt * nf / NW, (wt + 1) * nf / NW, t1, t2, s1, s2);
+        prof.template far_at<false>(L.lists.list + nn, wt * nf / NW, (wt + 1) * nf / NW,
+                                    c1 + kDct8.xi[lane & 7] * half, c2 + kDct8.xi[lane >> 3] * half, 0.0, 0.0, s1, s2);
         L.part[wt][0][lane] = s1;
         L.part[wt][1][lane] = s2;
     }
@@ -444,13 +552,7 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const do
             fi[k] = (float)(i0 + cu + 16 * (k >> 2) + 4 * lk + (k & 3));
         }
         const float fj = (float)(j0 + ru + li);
-        for_list(L.lists.list, 0, nn, [&](int p) {
-            const float* c = tab32 + (size_t)p * T32_STRIDE;
-            const float nyv = (fj - c[T32_CYH]) - c[T32_CYL];
-            const float4 rc =
-                make_float4(c[T32_BP] * nyv, c[T32_CQ] * nyv, fmaf(c[T32_DQ] * nyv, nyv, c[T32_A2]), c[T32_RSK]);
-            field32_pot<8, 1>(c, &rc, fi, sx, sy);
-        });
+        for_list(L.lists.list, !all, nn, [&](int p) { prof.near32(p, fi, fj, sx, sy); });
         const float cx = L.c00[0], cy = L.c00[1];
 #pragma unroll
         for (int k = 0; k < 8; k++) {
@@ -460,6 +562,142 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const do
         if (rec) write_records(sx, sy, i0 + cu, j0 + ru, g.nx, g.ny, nbx, rec);
         store_unit(sx, ax, i0 + cu, j0 + ru, g.nx, g.ny, vec);
         store_unit(sy, ay, i0 + cu, j0 + ru, g.nx, g.ny, vec);
+    }
+}
+
+// ---------------------------------------------------------------- FP64 tiles
+
+// The same in FP64 with 16 x 16 Chebyshev points (one per thread of the
+// workgroup) and v_mfma_f64_16x16x4f64.  The row coefficients (16 per row and
+// component) are formed by the lanes that feed them to the matrix product, once
+// per group of 16 rows, so they need no LDS.
+template <int T>
+struct Tile64 {
+    struct Lds {
+        TileLists lists;
+        double f[2][256], u[2][256];
+        double cheb[16][T];
+    };
+};
+
+template <int T, class P>
+__device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P& prof, int np, const GridDesc& g,
+                                            int i0, int j0, double* __restrict__ ax, double* __restrict__ ay,
+                                            bool bad, double* __restrict__ rec, int nbx)
+{
+    constexpr float hw = 0.5f * (T - 1);
+    const int tid = threadIdx.x, lane = lane_id(), wt = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float xc = (float)i0 + hw, yc = (float)j0 + hw;
+    const bool all = np > kTileMaxP;
+    if (!all) tile_lists(L.lists, np, [&](int p) { return prof.far(p, xc, yc, hw, kFarC64); });
+    const int nn = all ? np : __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
+    const int lo = tid & 15, hi = tid >> 4;
+    // The polynomial is in (t - c)/half, t the nodes' rounded FP64 coordinates
+    // (node_coord) and c the tile centre's: nodes then keep their own position
+    // to a rounding relative to the tile, as theta - theta_c does in the direct sum.
+    const double c1 = g.x0 + (double)xc * g.h, c2 = g.y0 + (double)yc * g.h;
+    const double half = (double)hw * g.h, ihalf = 1.0 / half;
+    {
+        double s1 = 0.0, s2 = 0.0;
+        prof.template far_at<true>(L.lists.list + nn, 0, nf, c1, c2, kDct16.xi[lo] * half, kDct16.xi[hi] * half, s1, s2);
+        L.f[0][tid] = s1;
+        L.f[1][tid] = s2;
+    }
+    if (tid < T) {
+        const double x = (node_coord(g.x0, i0 + tid, g.h) - c1) * ihalf;
+        double a = 1.0, b = x;
+        for (int m = 0; m < 16; m++) {
+            L.cheb[m][tid] = a;
+            const double n = fma(2.0 * x, b, -a);
+            a = b;
+            b = n;
+        }
+    }
+    __syncthreads();
+    // the value at a middle point is taken off before the transforms and added
+    // last, at the nodes: the transforms' and the interpolation's rounding is then
+    // relative to the variation over the tile
+    const double r0 = L.f[0][16 * 8 + 8], r1 = L.f[1][16 * 8 + 8];
+    {
+        double u0 = 0.0, u1 = 0.0;  // transform in x: point row hi, coefficient lo
+#pragma unroll
+        for (int m = 0; m < 16; m++) {
+            const double d = kDct16.d[16 * lo + m];
+            u0 = fma(d, L.f[0][16 * hi + m] - r0, u0);
+            u1 = fma(d, L.f[1][16 * hi + m] - r1, u1);
+        }
+        L.u[0][tid] = u0;
+        L.u[1][tid] = u1;
+    }
+    __syncthreads();
+    {
+        double w0 = 0.0, w1 = 0.0;  // transform in y: coefficient hi in y, lo in x
+#pragma unroll
+        for (int m = 0; m < 16; m++) {
+            const double d = kDct16.d[16 * hi + m];
+            w0 = fma(d, L.u[0][16 * m + lo], w0);
+            w1 = fma(d, L.u[1][16 * m + lo], w1);
+        }
+        L.f[0][tid] = w0;
+        L.f[1][tid] = w1;
+    }
+    __syncthreads();
+    const int li = lane & 15, lk = lane >> 4;
+    // output value r of lane l of the matrix product is row l / 16 + 4 r: the x
+    // nodes are assigned so that a lane holds four consecutive ones
+    const int xi = 4 * (li & 3) + (li >> 2);
+    const bool vec = (g.nx & 1) == 0 && (((size_t)ax | (size_t)ay) & 15) == 0;
+    for (int ru = 16 * wt; ru < T; ru += 64) {
+        if (j0 + ru >= g.ny) break;
+        const double t2 = node_coord(g.y0, j0 + ru + li, g.h);
+        double B[2][4];  // coefficient 4 s + lk of row ru + li
+        {
+            const double y = (t2 - c2) * ihalf;
+            double tb[16];
+            tb[0] = 1.0;
+            tb[1] = y;
+#pragma unroll
+            for (int b = 2; b < 16; b++) tb[b] = fma(2.0 * y, tb[b - 1], -tb[b - 2]);
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+#pragma unroll
+                for (int s = 0; s < 4; s++) {
+                    double v = 0.0;
+#pragma unroll
+                    for (int b = 15; b >= 0; b--) v = fma(L.f[c][16 * b + 4 * s + lk], tb[b], v);
+                    B[c][s] = v;
+                }
+        }
+        for (int cu = 0; cu < T; cu += 32) {
+            if (i0 + cu >= g.nx) break;
+            doublex4 acc[2][2];
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                acc[0][b] = acc[1][b] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int s = 3; s >= 0; s--) {
+                    const double A = L.cheb[4 * s + lk][cu + 16 * b + xi];
+                    acc[0][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(A, B[0][s], acc[0][b], 0, 0, 0);
+                    acc[1][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(A, B[1][s], acc[1][b], 0, 0, 0);
+                }
+            }
+            double sx[8], sy[8], t1[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                sx[k] = acc[0][k >> 2][k & 3];
+                sy[k] = acc[1][k >> 2][k & 3];
+                t1[k] = node_coord(g.x0, i0 + cu + 16 * (k >> 2) + 4 * lk + (k & 3), g.h);
+            }
+            for_list(L.lists.list, !all, nn, [&](int p) { prof.near64(p, t1, t2, sx, sy); });
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                sx[k] = bad ? __builtin_nan("") : sx[k] + r0;
+                sy[k] = bad ? __builtin_nan("") : sy[k] + r1;
+            }
+            if (rec) write_records(sx, sy, i0 + cu, j0 + ru, g.nx, g.ny, nbx, rec);
+            store_unit(sx, ax, i0 + cu, j0 + ru, g.nx, g.ny, vec);
+            store_unit(sy, ay, i0 + cu, j0 + ru, g.nx, g.ny, vec);
+        }
     }
 }
 
