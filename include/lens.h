@@ -111,9 +111,10 @@ typedef struct {
                              to FP64 when min_k |c_k| < fb_tau * h^2                 */
     double fb_tau;        /* literal-mode factor (e.g. 1e-6); ignored in mode 0    */
     int32_t hit_capacity; /* rows of out->hits / out->img_xy, 1 .. 8192            */
-    int32_t field_npl;    /* grid nodes per thread of the FP32 field kernel: 1, 2, 4 or
-                             8 (batched: 1, 2, 4); 0 = the autotuned choice, else
-                             chosen from the grid size (batched: 2)               */
+    int32_t field_npl;    /* grid nodes per thread of the direct FP32 field kernel: 1,
+                             2, 4 or 8 (batched: 1, 2, 4); 0 = the autotuned choice,
+                             else chosen from the grid size.  No effect where the
+                             field is evaluated by tiles (large problems, batches)  */
     int32_t tile;         /* cells per triangle-stage tile: 1 = 32x8, 2 = 64x16,
                              3 = 64x8, 4 = 32x16; 0 = the autotuned choice, else
                              32x8                                                 */

@@ -35,7 +35,7 @@ struct PlanChunk {
 struct PlanEntry {
     std::vector<int32_t> pot_off;
     std::vector<double> grids;  // x0, y0, h, nx, ny per sample
-    int npl, shape, fp32;
+    int shape, fp32;
     std::vector<PlanChunk> chunks;
 };
 
@@ -834,11 +834,11 @@ long long batch_field_budget()
 // P * nx * ny, heaviest first, and the work items of the field (row segments)
 // and triangle (tile) stages are enumerated in that order.  New plans are
 // uploaded on `s` from pinned staging that stays alive with the plan.
-int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_grid* grids, int npl, int shape,
-               bool fp32, hipStream_t s, PlanEntry** out)
+int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_grid* grids, int shape, bool fp32,
+                hipStream_t s, PlanEntry** out)
 {
     for (PlanEntry* e : *c->plans) {
-        if (e->npl != npl || e->shape != shape || e->fp32 != (int)fp32 ||
+        if (e->shape != shape || e->fp32 != (int)fp32 ||
             (int)e->pot_off.size() != n_samples + 1)
             continue;
         if (memcmp(e->pot_off.data(), pot_off, sizeof(int32_t) * (n_samples + 1)) != 0) continue;
@@ -865,7 +865,6 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
     }
     PlanEntry* e = new (std::nothrow) PlanEntry();
     if (!e) return LENS_ERR_DEVICE;
-    e->npl = npl;
     e->shape = shape;
     e->fp32 = (int)fp32;
     e->pot_off.assign(pot_off, pot_off + n_samples + 1);
@@ -880,7 +879,6 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
     }
     int tx, ty;
     tile_dims(shape, tx, ty);
-    const int seg_nodes = 256 * (fp32 ? field_cols(npl) : 1), seg_rows = fp32 ? field_rows(npl) : 1;
     const long long elem = fp32 ? 8 : 16;  // two planes
     const long long budget = batch_field_budget();
     int s0 = 0;
@@ -908,7 +906,8 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
         };
         std::stable_sort(perm.begin(), perm.end(), [&](int x, int y) { return cost(x) > cost(y); });
         const size_t o_pot = 0, o_grid = align8(o_pot + 4 * (size_t)(n + 1)),
-                     o_perm = align8(o_grid + sizeof(GridDesc) * (size_t)n), o_fo = align8(o_perm + 4 * (size_t)n),
+                     o_perm = align8(o_grid + sizeof(GridDesc) * (size_t)n), o_side = align8(o_perm + 4 * (size_t)n),
+                     o_fo = align8(o_side + 4 * (size_t)n),
                      o_to = o_fo + 8 * (size_t)(n + 1), o_no = o_to + 8 * (size_t)(n + 1),
                      o_rr = o_no + 8 * (size_t)n, bytes = o_rr + 8 * (size_t)n;
         if (hipHostMalloc(&ch.host_stage, bytes, hipHostMallocDefault) != hipSuccess) {
@@ -919,6 +918,7 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
         int32_t* h_pot = (int32_t*)(hb + o_pot);
         GridDesc* h_grid = (GridDesc*)(hb + o_grid);
         int32_t* h_perm = (int32_t*)(hb + o_perm);
+        int32_t* h_side = (int32_t*)(hb + o_side);
         long long* h_fo = (long long*)(hb + o_fo);
         long long* h_to = (long long*)(hb + o_to);
         long long* h_no = (long long*)(hb + o_no);
@@ -931,7 +931,8 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
             h_no[k] = node;
             h_rr[k] = nrr;
             node += (long long)g.nx * g.ny;
-            nrr += (long long)g.ny * ((g.nx - 2) / tx + 2) * kRR;
+            h_side[k] = tile_side_for((double)g.nx * g.ny, (double)nodes, pot_off[s0 + k + 1] - pot_off[s0 + k], fp32);
+            nrr += (long long)rec_nbx(h_grid[k]) * rec_nby(h_grid[k]) * kRec;
             ch.n_tests += 2ll * (g.nx - 1) * (g.ny - 1);
         }
         ch.n_rr = nrr;
@@ -940,7 +941,8 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
         for (int k = 0; k < n; k++) {
             const lens_grid& g = grids[s0 + perm[k]];
             h_perm[k] = perm[k];
-            h_fo[k + 1] = h_fo[k] + (long long)((g.ny + seg_rows - 1) / seg_rows) * ((g.nx + seg_nodes - 1) / seg_nodes);
+            const int side = h_side[perm[k]];
+            h_fo[k + 1] = h_fo[k] + (long long)((g.ny + side - 1) / side) * ((g.nx + side - 1) / side);
             // triangle stage: one item per (tile row, block of 64 tile columns)
             h_to[k + 1] = h_to[k] + (long long)(((g.nx - 2) / tx + 1 + 63) / 64) * ((g.ny - 2) / ty + 1);
         }
@@ -963,11 +965,11 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
         ch.bp.pot_off = (const int*)(db + o_pot);
         ch.bp.grid = (const GridDesc*)(db + o_grid);
         ch.bp.perm = (const int*)(db + o_perm);
+        ch.bp.side = (const int*)(db + o_side);
         ch.bp.fitem_off = (const long long*)(db + o_fo);
         ch.bp.titem_off = (const long long*)(db + o_to);
         ch.bp.node_off = (const long long*)(db + o_no);
         ch.bp.rr_off = (const long long*)(db + o_rr);
-        ch.bp.tx_shift = tx == 64 ? 6 : 5;
         if (hipMemcpyAsync(ch.dev_plan, ch.host_stage, bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
             launch_bmap(ch.bp, ch.fmap, ch.tmap, s) != hipSuccess)
             rc = LENS_ERR_DEVICE;
@@ -1014,9 +1016,8 @@ extern "C" int lens_image_chi2_batched(lens_ctx* ctx, const lens_potentials* all
     for (int i = 0; i < n_samples; i++) side = std::max(side, std::max(grids[i].nx, grids[i].ny));
     resolve_tuned(ctx, opts->prec, 1, side, ((long long)all->n + n_samples - 1) / n_samples, shape, npl);
     if (!shape) shape = 1;
-    npl = mixed ? (npl ? npl : 0x41) : 1;  // FP32 field: 1 column x 4 rows per thread (measured fastest)
     PlanEntry* plan = nullptr;
-    int rc = batch_plan(ctx, n_samples, pot_off, grids, npl, shape, mixed, stream, &plan);
+    int rc = batch_plan(ctx, n_samples, pot_off, grids, shape, mixed, stream, &plan);
     if (rc) return rc;
 
     // scratch sized for the largest chunk
@@ -1074,12 +1075,9 @@ extern "C" int lens_image_chi2_batched(lens_ctx* ctx, const lens_potentials* all
         const KernelEvents* ev;
         if ((rc = timing_begin(ctx, &kev, &ev, &slot))) return rc;
         if (e == hipSuccess) {
-            if (mixed)
-                e = launch_bfield32(bp, ch.fmap, ch.n_fitems, (const float*)ctx->buf[B_TAB32], (float*)field,
-                                    (float*)field + ch.n_nodes, (float*)ctx->buf[B_RR], npl, ev, stream);
-            else
-                e = launch_bfield64(bp, ch.fmap, ch.n_fitems, (const double*)ctx->buf[B_TAB64], (double*)field,
-                                    (double*)field + ch.n_nodes, (double*)ctx->buf[B_RR], ev, stream);
+            const size_t plane = (size_t)ch.n_nodes * (mixed ? 4 : 8);
+            e = launch_bfield(mixed, bp, ch.fmap, ch.n_fitems, (const double*)ctx->buf[B_TAB64],
+                              (const float*)ctx->buf[B_TAB32], field, (char*)field + plane, ctx->buf[B_RR], ev, stream);
         }
         if (e != hipSuccess) return LENS_ERR_DEVICE;
         timing_end(ctx, slot);

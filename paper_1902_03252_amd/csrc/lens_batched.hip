@@ -6,8 +6,8 @@
 //   k_bsys    one wave per sample: error bound, barycentres, system rows,
 //             counters
 //   k_bmap    work-item -> sample maps of the field and triangle stages
-//   k_bfield  FP32 or FP64 deflection, one workgroup per (sample, row segment),
-//             heaviest samples first
+//   k_btiled  FP32 or FP64 deflection, one workgroup per (sample, tile), heaviest
+//             samples first
 //   k_btri    one workgroup per (sample, tile), heaviest samples first
 //   k_bfbpos  FP64 image positions of every hit (a workgroup per sample) and
 //             the FP64 re-test of every undecided FP32 test
@@ -15,6 +15,7 @@
 // The per-sample work follows exactly the single-evaluation path (same device
 // functions, Rexroth et al. 2019, Sec. 2.2.1-2.2.2 and Algorithm 1).
 #include "lens_path.hpp"
+#include "lens_tiles.hpp"
 
 namespace lens {
 
@@ -144,77 +145,64 @@ __global__ __launch_bounds__(256) void k_bmap(BatchPlan bp, int* __restrict__ fm
 
 // ============================================================== field
 
-// One workgroup per (sample, block of NR rows, row segment of 256*NPL nodes);
-// the map gives the sample (heaviest samples first).  Same inner loop as the
-// single-evaluation FP32 field (NPL nodes in each of NR rows per thread), and
-// the same tile range partials (per sample).
-template <int NPL, int NR>
-__global__ __launch_bounds__(256) void k_bfield32(BatchPlan bp, const int* __restrict__ fmap,
-                                                  const float* __restrict__ tab32, float* __restrict__ fx,
-                                                  float* __restrict__ fy, float* __restrict__ rr)
+// One workgroup per (sample, tile); the map gives the sample (heaviest samples
+// first).  The tiled field of the single evaluation (lens_tiles.hpp) with each
+// sample's own tile side, for every sample: a batch fills the chip whatever its
+// samples' sizes, and a sample too small to have far potentials costs what the
+// direct sum would.
+template <int T>
+__device__ __forceinline__ void btile(void* lds, const IsoProfile& prof, int np, const GridDesc& g, int tile, float* fx,
+                                      float* fy, float* rec)
 {
-    __shared__ float4 srow[NR * 256];
-    const long long item = blockIdx.x;
-    const int k = fmap[item];
+    const int ntx = (g.nx + T - 1) / T, tj = tile / ntx, ti = tile - tj * ntx;
+    tile32_body<T>(*reinterpret_cast<typename Tile32<T>::Lds*>(lds), prof, np, g, ti * T, tj * T, fx, fy, false, rec,
+                   (g.nx + 31) >> 5);
+}
+template <int T>
+__device__ __forceinline__ void btile(void* lds, const IsoProfile& prof, int np, const GridDesc& g, int tile, double* fx,
+                                      double* fy, double* rec)
+{
+    const int ntx = (g.nx + T - 1) / T, tj = tile / ntx, ti = tile - tj * ntx;
+    tile64_body<T>(*reinterpret_cast<typename Tile64<T>::Lds*>(lds), prof, np, g, ti * T, tj * T, fx, fy, false, rec,
+                   (g.nx + 31) >> 5);
+}
+
+template <typename V>
+__device__ __forceinline__ void bfield(void* lds, const BatchPlan& bp, const int* __restrict__ fmap,
+                                       const double* __restrict__ tab64, const float* __restrict__ tab32,
+                                       V* __restrict__ fx, V* __restrict__ fy, V* __restrict__ rec)
+{
+    const int k = fmap[blockIdx.x];
     const int s = bp.perm[k];
     const GridDesc g = bp.grid[s];
-    const int segs = (g.nx + 256 * NPL - 1) / (256 * NPL);
-    const long long local = item - bp.fitem_off[k];
-    const int j0 = (int)(local / segs) * NR, seg = (int)(local % segs);
-    const int i0 = (seg * 256 + threadIdx.x) * NPL;
-    const int p0 = bp.pot_off[0];
-    const float* tab = tab32 + (size_t)(bp.pot_off[s] - p0) * T32_STRIDE;
-    const int np = bp.pot_off[s + 1] - bp.pot_off[s];
-    float fi[NPL], sx[NR * NPL], sy[NR * NPL];
-#pragma unroll
-    for (int q = 0; q < NPL; q++) fi[q] = (float)(i0 + q);
-#pragma unroll
-    for (int q = 0; q < NR * NPL; q++) {
-        sx[q] = 0.0f;
-        sy[q] = 0.0f;
-    }
-    field32_all_wg<NPL, NR>(tab, np, (float)j0, fi, sx, sy, srow);
-    const int tiles_x = (g.nx - 2) / (1 << bp.tx_shift) + 1;
-#pragma unroll
-    for (int r = 0; r < NR; r++) {
-        const int j = j0 + r;
-        if (j >= g.ny) break;  // uniform over the workgroup
-        tile_partials<float, NPL>(sx + r * NPL, sy + r * NPL, i0, j, g.nx, bp.tx_shift, tiles_x, rr + bp.rr_off[s]);
-        const size_t row = (size_t)bp.node_off[s] + (size_t)j * g.nx;
-#pragma unroll
-        for (int q = 0; q < NPL; q++) {
-            if (i0 + q < g.nx) {
-                fx[row + i0 + q] = sx[r * NPL + q];
-                fy[row + i0 + q] = sy[r * NPL + q];
-            }
-        }
+    const int tile = (int)(blockIdx.x - bp.fitem_off[k]);
+    const int q0 = bp.pot_off[s] - bp.pot_off[0], np = bp.pot_off[s + 1] - bp.pot_off[s];
+    const IsoProfile prof{tab64 + (size_t)q0 * T64_STRIDE, tab32 + (size_t)q0 * T32_STRIDE};
+    V* ox = fx + bp.node_off[s];
+    V* oy = fy + bp.node_off[s];
+    V* r = rec + bp.rr_off[s];
+    switch (bp.side[s]) {  // uniform over the workgroup
+    case 32: btile<32>(lds, prof, np, g, tile, ox, oy, r); break;
+    case 64: btile<64>(lds, prof, np, g, tile, ox, oy, r); break;
+    default: btile<128>(lds, prof, np, g, tile, ox, oy, r); break;
     }
 }
 
-// FP64 field: one workgroup per (sample, row segment of 256 nodes).
-__global__ __launch_bounds__(256) void k_bfield64(BatchPlan bp, const int* __restrict__ fmap,
-                                                  const double* __restrict__ tab64, double* __restrict__ fx,
-                                                  double* __restrict__ fy, double* __restrict__ rr)
+__global__ __launch_bounds__(256) void k_btiled32(BatchPlan bp, const int* __restrict__ fmap,
+                                                  const double* __restrict__ tab64, const float* __restrict__ tab32,
+                                                  float* __restrict__ fx, float* __restrict__ fy,
+                                                  float* __restrict__ rec)
 {
-    const long long item = blockIdx.x;
-    const int k = fmap[item];
-    const int s = bp.perm[k];
-    const GridDesc g = bp.grid[s];
-    const int segs = (g.nx + 255) / 256;
-    const long long local = item - bp.fitem_off[k];
-    const int j = (int)(local / segs), i = (int)(local % segs) * 256 + threadIdx.x;
-    const int p0 = bp.pot_off[0];
-    const double* tab = tab64 + (size_t)(bp.pot_off[s] - p0) * T64_STRIDE;
-    const int np = bp.pot_off[s + 1] - bp.pot_off[s];
-    const double t1 = node_coord(g.x0, i, g.h), t2 = node_coord(g.y0, j, g.h);
-    double s1 = 0.0, s2 = 0.0;
-    alpha64_all_wg(tab, np, t1, t2, s1, s2);
-    const int tiles_x = (g.nx - 2) / (1 << bp.tx_shift) + 1;
-    tile_partials<double, 1>(&s1, &s2, i, j, g.nx, bp.tx_shift, tiles_x, rr + bp.rr_off[s]);
-    if (i >= g.nx) return;
-    const size_t n = (size_t)bp.node_off[s] + (size_t)j * g.nx + i;
-    fx[n] = s1;
-    fy[n] = s2;
+    __shared__ __align__(16) unsigned char lds[sizeof(Tile32<128>::Lds)];
+    bfield<float>(lds, bp, fmap, tab64, tab32, fx, fy, rec);
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_btiled64(
+    BatchPlan bp, const int* __restrict__ fmap, const double* __restrict__ tab64, const float* __restrict__ tab32,
+    double* __restrict__ fx, double* __restrict__ fy, double* __restrict__ rec)
+{
+    __shared__ __align__(16) unsigned char lds[sizeof(Tile64<128>::Lds)];
+    bfield<double>(lds, bp, fmap, tab64, tab32, fx, fy, rec);
 }
 
 // ============================================================== triangles
@@ -254,7 +242,7 @@ __global__ __launch_bounds__(256) void k_btri(BatchPlan bp, const int* __restric
         const bool act = col < tiles_x;
         const Tile T = tile_of<S>(g, tiles_x, band * tiles_x + (act ? col : 0));
         double rng[4] = {0.0, 0.0, 0.0, 0.0};
-        if (act) tile_range_lane<S, V>(rr + bp.rr_off[s], tiles_x, T, rng);
+        if (act) tile_range_rec<S, V>(rr + bp.rr_off[s], (g.nx + 31) >> 5, (g.ny + 7) >> 3, T, rng);
         const double* rows = sysrow + (size_t)s * nsys * SYS_STRIDE;
         const V* sfx = fx + bp.node_off[s];
         const V* sfy = fy + bp.node_off[s];
@@ -566,24 +554,12 @@ hipError_t launch_bmap(const BatchPlan& bp, int* fmap, int* tmap, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_bfield32(const BatchPlan& bp, const int* fmap, long long n_items, const float* tab32, float* fx,
-                           float* fy, float* rr, int npl, const KernelEvents* ev, hipStream_t s)
+hipError_t launch_bfield(bool fp32, const BatchPlan& bp, const int* fmap, long long n_items, const double* tab64,
+                         const float* tab32, void* fx, void* fy, void* rec, const KernelEvents* ev, hipStream_t s)
 {
     const dim3 grid((unsigned)n_items), block(256);
-    switch (npl) {
-    case 0x01: return launch_ev(ev, k_bfield32<1, 1>, grid, block, s, bp, fmap, tab32, fx, fy, rr);
-    case 0x04: return launch_ev(ev, k_bfield32<4, 1>, grid, block, s, bp, fmap, tab32, fx, fy, rr);
-    case 0x21: return launch_ev(ev, k_bfield32<1, 2>, grid, block, s, bp, fmap, tab32, fx, fy, rr);
-    case 0x22: return launch_ev(ev, k_bfield32<2, 2>, grid, block, s, bp, fmap, tab32, fx, fy, rr);
-    case 0x41: return launch_ev(ev, k_bfield32<1, 4>, grid, block, s, bp, fmap, tab32, fx, fy, rr);
-    default: return launch_ev(ev, k_bfield32<2, 1>, grid, block, s, bp, fmap, tab32, fx, fy, rr);
-    }
-}
-
-hipError_t launch_bfield64(const BatchPlan& bp, const int* fmap, long long n_items, const double* tab64, double* fx,
-                           double* fy, double* rr, const KernelEvents* ev, hipStream_t s)
-{
-    return launch_ev(ev, k_bfield64, dim3((unsigned)n_items), dim3(256), s, bp, fmap, tab64, fx, fy, rr);
+    if (fp32) return launch_ev(ev, k_btiled32, grid, block, s, bp, fmap, tab64, tab32, (float*)fx, (float*)fy, (float*)rec);
+    return launch_ev(ev, k_btiled64, grid, block, s, bp, fmap, tab64, tab32, (double*)fx, (double*)fy, (double*)rec);
 }
 
 template <class F>

@@ -55,11 +55,11 @@ struct BatchPlan {
     const int* pot_off;           // [n+1] parameter columns of each sample (absolute)
     const GridDesc* grid;         // [n]
     const int* perm;              // [n] plan position -> sample (heaviest first)
-    const long long* fitem_off;   // [n+1] field work items, in plan order
+    const int* side;              // [n] nodes per side of the sample's field tiles
+    const long long* fitem_off;   // [n+1] field work items (tiles), in plan order
     const long long* titem_off;   // [n+1] triangle-stage items (tile row x 64 tile columns), in plan order
     const long long* node_off;    // [n] offset of each sample's field (nodes)
-    const long long* rr_off;      // [n] offset of each sample's tile range partials (values)
-    int tx_shift;                 // log2 of the tile width in cells
+    const long long* rr_off;      // [n] offset of each sample's range records (values)
 };
 
 // Per-sample counters and status of a batch chunk (device arrays).
@@ -101,8 +101,7 @@ inline bool field_code_ok(int code)
     return code == 1 || code == 2 || code == 4 || code == 8 || code == 0x21 || code == 0x22 || code == 0x24 ||
            code == 0x41 || code == 0x42;
 }
-// Layouts of the batched FP32 field (one workgroup per (sample, block of rows,
-// row segment)).
+// Layout codes that a batched call accepts (its field is tiled: they have no effect).
 inline bool bfield_code_ok(int code)
 {
     return code == 1 || code == 2 || code == 4 || code == 0x21 || code == 0x22 || code == 0x41;
@@ -246,10 +245,8 @@ hipError_t launch_bhead(const BatchPlan& bp, const PotPtrs& pot, const ObsPtrs& 
 hipError_t launch_bsys(const BatchPlan& bp, const ObsPtrs& obs, const double* bterm, const double* bx,
                        const double* by, double* sysrow, const BatchState& bs, hipStream_t s);
 hipError_t launch_bmap(const BatchPlan& bp, int* fmap, int* tmap, hipStream_t s);
-hipError_t launch_bfield32(const BatchPlan& bp, const int* fmap, long long n_items, const float* tab32, float* fx,
-                           float* fy, float* rr, int npl, const KernelEvents* ev, hipStream_t s);
-hipError_t launch_bfield64(const BatchPlan& bp, const int* fmap, long long n_items, const double* tab64, double* fx,
-                           double* fy, double* rr, const KernelEvents* ev, hipStream_t s);
+hipError_t launch_bfield(bool fp32, const BatchPlan& bp, const int* fmap, long long n_items, const double* tab64,
+                         const float* tab32, void* fx, void* fy, void* rec, const KernelEvents* ev, hipStream_t s);
 hipError_t launch_btri(const BatchPlan& bp, const int* tmap, long long n_items, int nsys, const double* sysrow,
                        const void* fx, const void* fy, const void* rr, bool fp32, const BatchState& bs, int mode,
                        double tau, int hcap, unsigned long long* hits, unsigned long long* flags, long long flag_cap,
