@@ -931,7 +931,8 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
             h_no[k] = node;
             h_rr[k] = nrr;
             node += (long long)g.nx * g.ny;
-            h_side[k] = tile_side_for((double)g.nx * g.ny, (double)nodes, pot_off[s0 + k + 1] - pot_off[s0 + k], fp32);
+            h_side[k] = tile_side_for((double)g.nx * g.ny, (double)nodes, pot_off[s0 + k + 1] - pot_off[s0 + k],
+                                      fp32 ? kTileCost32 : kTileCost64);
             nrr += (long long)rec_nbx(h_grid[k]) * rec_nby(h_grid[k]) * kRec;
             ch.n_tests += 2ll * (g.nx - 1) * (g.ny - 1);
         }

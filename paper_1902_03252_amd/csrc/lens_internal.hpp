@@ -110,7 +110,15 @@ inline bool bfield_code_ok(int code)
 // Field by tiles of side x side nodes (lens_tiles.hpp); rec: 32 x 8 block
 // records or null; h: the head's arguments (fused head) or null.
 int tiled_side(const GridDesc& g, int np, bool fp32);  // 0: direct field
-int tile_side_for(double nodes, double total, int np, bool fp32);
+// Cost of a tiled field in cycles per 64 nodes and potential (near: per node; far:
+// per Chebyshev point, `points` of them; rest: per node whatever P), and the
+// near region's radius in half widths.
+struct TileCost {
+    double near, far, points, rest, reach;
+};
+constexpr TileCost kTileCost32 = {75.0, 116.0, 64.0, 60.0, 3.6};
+constexpr TileCost kTileCost64 = {200.0, 180.0, 256.0, 200.0, 5.1};
+int tile_side_for(double nodes, double total, int np, const TileCost& k);
 inline int rec_nbx(const GridDesc& g) { return (g.nx + 31) / 32; }
 inline int rec_nby(const GridDesc& g) { return (g.ny + 7) / 8; }
 hipError_t launch_tiled32(int side, const double* tab64, const float* tab32, int np, const GridDesc& g, float* ax,

@@ -1163,26 +1163,19 @@ int tiled_side(const GridDesc& g, int np, bool fp32)
 {
     const double nodes = (double)g.nx * g.ny;
     if (np < 4 || np > kTileMaxP || nodes * np < (double)(1 << 24)) return 0;
-    return tile_side_for(nodes, nodes, np, fp32);
+    return tile_side_for(nodes, nodes, np, fp32 ? kTileCost32 : kTileCost64);
 }
 
 // The best side for a grid of `nodes` nodes in a launch of `total` nodes.
-int tile_side_for(double nodes, double total, int np, bool fp32)
+int tile_side_for(double nodes, double total, int np, const TileCost& k)
 {
     int best = 0;
     double cost = 0.0;
     for (int t = 32; t <= 128; t *= 2) {
         const double t2 = (double)t * t, units = std::max(1.0, t2 / 2048.0);  // units of 512 nodes per wave
-        double all, chain;
-        if (fp32) {
-            const double near = std::min((double)np, 1.0 + np * kPi * 3.24 * t2 / nodes);
-            all = total / 64.0 * (75.0 * near + 116.0 * 64.0 * np / t2 + 60.0) / 1024.0;
-            chain = 6000.0 + 62.0 * np + units * (600.0 + 640.0 * near);
-        } else {
-            const double near = std::min((double)np, 1.0 + np * kPi * 6.5 * t2 / nodes);
-            all = total / 64.0 * (200.0 * near + 180.0 * 256.0 * np / t2 + 200.0) / 1024.0;
-            chain = 8000.0 + 300.0 * np + units * (800.0 + 1600.0 * near);
-        }
+        const double near = std::min((double)np, 1.0 + np * kPi * 0.25 * k.reach * k.reach * t2 / nodes);
+        const double all = total / 64.0 * (k.near * near + k.far * k.points * np / t2 + k.rest) / 1024.0;
+        const double chain = 7000.0 + k.far * k.points / 120.0 * np + units * (700.0 + 8.0 * k.near * near);
         const double c = std::max(all, chain);
         if (!best || c < cost) {
             best = t;

@@ -83,3 +83,30 @@ def test_tiled_field(lens, nx, ny, p, prec):
     prm[5, prm[5] > 1e100] = np.inf  # the oracle squares the cut radius
     tol = 1e-10 if prec == "fp64" else fp32_alpha_bound(prm, grid)
     check_rows(ax, ay, prm, grid, tol, f"{prec} {nx}x{ny} P={p}")
+
+
+# NFW halos: (nx, ny, P) around the tile sides and the rule's limits
+NFW_SHAPES = [(512, 500, 40), (545, 481, 80), (1025, 1023, 60), (2049, 1500, 302), (40007, 9, 60), (300, 280, 2048),
+              (300, 280, 2049), (2300, 2300, 3)]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,p", NFW_SHAPES)
+def test_tiled_nfw_field(lens, nx, ny, p, prec):
+    """FP64 within 1e-10 arcsec; FP32 within u (64 + P) sum_p w_p, w_p = 1.3 kappa_s r_s (1 + eps)/sqrt(1 - eps)
+    the largest deflection of a halo (4 g(x)/x is at most 1.3), 64 u w_p for one halo's evaluation (about 30
+    operations, five of them 1-2 ulp functions, doubled) and (P - 1) u sum w for the sum."""
+    grid = S.Grid(-31.3, -27.9, 60.0 / max(nx, ny), nx, ny)
+    h = S.nfw_cluster(grid, n_galaxies=p - 2, seed=p)
+    h[0, p - 1], h[1, p - 1] = grid.x0 + (nx // 3) * grid.h, grid.y0 + (ny // 2) * grid.h  # a centre on a node
+    w = (1.3 * h[5] * h[4] * (1 + h[2]) / np.sqrt(1 - h[2])).sum()
+    tol = 1e-10 if prec == "fp64" else 2.0 ** -24 * (64 + p) * w
+    ax, ay = lens.lens_deflect_nfw(dev(h), grid, prec)
+    worst = 0.0
+    for j in sampled_rows(ny, np.random.default_rng(1)):
+        sub = S.Grid(grid.x0, grid.y0 + j * grid.h, grid.h, nx, 2)
+        want = oracle.nfw_alpha_grid(h, sub)
+        for got, o in ((ax, want[0]), (ay, want[1])):
+            worst = max(worst, np.abs(got[j:j + 2].double().cpu().numpy() - o).max())
+    print(f"  nfw {prec} {nx}x{ny} P={p}: max err {worst:.2e} (bar {tol:.2e})", flush=True)
+    assert worst <= tol
