@@ -19,7 +19,7 @@ using namespace lens;
 namespace {
 
 enum Buf { B_TAB64, B_TAB32, B_BTERM, B_FIELD, B_BX, B_BY, B_SYS, B_STATE, B_HITS, B_FLAGS, B_POS, B_CONTRIB,
-           B_PART, B_BCOUNT, B_VJP, B_SRC, B_SRCST, B_RR, B_PAIRS, B_MIX, B_MLIST, B_MMASK, B_HMC, B_MHP, B_NFW, B_NBUF };
+           B_PART, B_BCOUNT, B_VJP, B_SRC, B_SRCST, B_RR, B_PAIRS, B_MIX, B_MCOUNT, B_MMASK, B_HMC, B_MHP, B_NFW, B_NBUF };
 
 // Device work plan of one chunk of a batch (see lens_image_chi2_batched).
 struct PlanChunk {
@@ -447,7 +447,7 @@ int lens_deflect_mixed(lens_ctx* ctx, const lens_potentials* pot, const lens_gri
         !is_fin(opts->t12) || !(opts->t34 >= 0.0) || !is_fin(opts->t34))
         return LENS_ERR_INVALID;
     const long long nn = (long long)grid->nx * grid->ny;
-    if (nn >= (1ll << 32)) return LENS_ERR_INVALID;  // DP list entries are 32-bit pixel indices
+    if (nn >= (1ll << 32)) return LENS_ERR_INVALID;  // 32-bit pixel counts
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return LENS_ERR_DEVICE;
     const GridDesc g = grid_desc(grid);
@@ -455,7 +455,8 @@ int lens_deflect_mixed(lens_ctx* ctx, const lens_potentials* pot, const lens_gri
     int rc;
     if ((rc = ensure(ctx, B_TAB64, np * T64_STRIDE * 8)) || (rc = ensure(ctx, B_TAB32, np * T32_STRIDE * 4)) ||
         (rc = ensure(ctx, B_BTERM, np * 3 * 8)) || (rc = ensure(ctx, B_MIX, sizeof(MixState))) ||
-        (rc = ensure(ctx, B_MLIST, (size_t)nn * 4)) || (!mask && (rc = ensure(ctx, B_MMASK, (size_t)nn))))
+        (rc = ensure(ctx, B_MCOUNT, mixed_counts(g) * sizeof(uint2))) ||
+        (!mask && (rc = ensure(ctx, B_MMASK, (size_t)nn))))
         return rc;
     MixedLaunch ml;
     ml.tab64 = (double*)ctx->buf[B_TAB64];
@@ -465,12 +466,11 @@ int lens_deflect_mixed(lens_ctx* ctx, const lens_potentials* pot, const lens_gri
     ml.ax = ax;
     ml.ay = ay;
     ml.mask = mask ? mask : (unsigned char*)ctx->buf[B_MMASK];
-    ml.list = (unsigned*)ctx->buf[B_MLIST];
+    ml.counts = (uint2*)ctx->buf[B_MCOUNT];
     ml.stats = (long long*)stats;
     ml.n_cluster = opts->n_cluster;
     ml.pc = opts->patch_cluster;
     ml.pg = opts->patch_galaxy;
-    ml.npl = std::min(field_cols(field_npl(g)) * field_rows(field_npl(g)), 4);
     ml.t12 = opts->t12;
     ml.t34 = opts->t34;
     int slot;

@@ -163,8 +163,8 @@ __device__ __forceinline__ void btile(void* lds, const IsoProfile& prof, int np,
                                       double* fy, double* rec)
 {
     const int ntx = (g.nx + T - 1) / T, tj = tile / ntx, ti = tile - tj * ntx;
-    tile64_body<T>(*reinterpret_cast<typename Tile64<T>::Lds*>(lds), prof, np, g, ti * T, tj * T, fx, fy, false, rec,
-                   (g.nx + 31) >> 5);
+    tile64_body<T>(*reinterpret_cast<typename Tile64<T>::Lds*>(lds), prof, np, g, ti * T, tj * T,
+                   FieldSink64{fx, fy, rec, g.nx, g.ny, false});
 }
 
 template <typename V>

@@ -209,12 +209,10 @@ hipError_t launch_src(const PotPtrs& pot, const ObsPtrs& obs, double* beta, doub
                       SrcState* st, double* chi2, int* status, const double* g_chi2, double* grad,
                       const HmcUpdate* upd, hipStream_t s);
 
-// Device state of the mixed-precision SIE gradient (reset by its first kernel).
+// Device state of the mixed-precision SIE gradient (set by its first kernel).
 struct MixState {
-    unsigned n_list;   // DP list length
-    unsigned n_patch;  // list entries that are block pixels
     int status;
-    int pad;
+    int pad[3];
 };
 
 // Arguments of the mixed-precision SIE gradient.
@@ -225,13 +223,14 @@ struct MixedLaunch {
     MixState* st;
     double *ax, *ay;       // [ny*nx] output
     unsigned char* mask;   // [ny*nx] 0 FP32, 1 DP block, 2 DP by the criteria
-    unsigned* list;        // [ny*nx] DP pixel list
+    uint2* counts;         // [mixed_counts] block and criteria pixels per scan workgroup
     long long* stats;      // [4] block pixels, criteria pixels, DP pixels, status
-    int n_cluster, pc, pg, npl;
+    int n_cluster, pc, pg;
     double t12, t34;
     const KernelEvents* ev;  // times the FP32 field kernel when not null
 };
 
+size_t mixed_counts(const GridDesc& g);
 hipError_t launch_mixed(const PotPtrs& pot, const GridDesc& g, const MixedLaunch& ml, hipStream_t s);
 
 size_t nfw_scratch(int np);  // bytes of device scratch of launch_nfw

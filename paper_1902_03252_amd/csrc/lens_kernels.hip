@@ -415,7 +415,7 @@ template <int T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_tiled64(const double* __restrict__ tab64, const float* __restrict__ tab32,
                                                  int np, GridDesc g, int ntx, double* __restrict__ ax,
                                                  double* __restrict__ ay, const EvalState* __restrict__ st,
-                                                 double* __restrict__ rec, int nbx, HeadArgs h, int head_blocks)
+                                                 double* __restrict__ rec, HeadArgs h, int head_blocks)
 {
     using Lds = typename Tile64<T>::Lds;
     __shared__ FusedLds<fused_lds_bytes((int)sizeof(Lds))> lds;
@@ -425,8 +425,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     }
     const int tile = blockIdx.x - head_blocks, tj = tile / ntx, ti = tile - tj * ntx;
     const bool bad = st != nullptr && st->status != kStatusOk;
-    tile64_body<T>(*reinterpret_cast<Lds*>(lds.raw), IsoProfile{tab64, tab32}, np, g, ti * T, tj * T, ax, ay, bad,
-                   rec, nbx);
+    tile64_body<T>(*reinterpret_cast<Lds*>(lds.raw), IsoProfile{tab64, tab32}, np, g, ti * T, tj * T,
+                   FieldSink64{ax, ay, rec, g.nx, g.ny, bad});
 }
 
 // ============================================================== triangle stage
@@ -1213,7 +1213,7 @@ hipError_t launch_tiled64(int side, const double* tab64, const float* tab32, int
     auto go = [&](auto t) {
         constexpr int T = decltype(t)::value;
         return launch_ev(ev, k_tiled64<T>, dim3(n_tiles + hb), dim3(256), s, tab64, tab32, np, g, ntx, ax, ay, st,
-                         rec, rec_nbx(g), ha, hb);
+                         rec, ha, hb);
     };
     switch (side) {
     case 32: return go(std::integral_constant<int, 32>());

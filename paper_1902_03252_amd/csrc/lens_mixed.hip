@@ -11,13 +11,20 @@
 //   k_mix_field32  FP32 field at every node (SIE form alpha = K m / R with
 //                  R = sqrt(d . M d): one reciprocal square root per
 //                  potential), written as double; mask cleared
-//   k_mix_patches  one workgroup per halo marks its block in the mask
-//   k_mix_scan<0>  appends the block pixels to the DP list
-//   k_mix_dp       FP64 gradient of the listed pixels
-//   k_mix_scan<1>  criteria on the field so far; appends flagged pixels
-//   k_mix_dp       FP64 gradient of those pixels
+//   k_mix_blocks   FP64 gradient of the cluster-scale halos' blocks, then of the
+//                  others' (two launches), marked 1
+//   k_mix_scan     criteria on the field so far, pixels marked 2; counts
+//   k_mix_dp       FP64 gradient of the pixels marked 2, by tiles
 //   k_mix_stats    counts and status to the caller's stats
+// The FP32 field decides which pixels the criteria take, so it is summed over
+// the potentials at every pixel; the FP64 gradient of the criteria pixels (a
+// fifth of the benchmark image) goes through the tiled field: 0.4 ms against 4.2
+// for the sum over 702 halos at each of 8.8 M pixels.
 #include "lens_path.hpp"
+#include "lens_tiles.hpp"
+
+#include <algorithm>
+#include <type_traits>
 
 namespace lens {
 
@@ -28,11 +35,7 @@ __global__ __launch_bounds__(256) void k_mix_prep(PotPtrs pot, GridDesc g, doubl
                                                   MixState* __restrict__ st)
 {
     __shared__ int s_bad;
-    if (threadIdx.x == 0) {
-        s_bad = 0;
-        st->n_list = 0;
-        st->n_patch = 0;
-    }
+    if (threadIdx.x == 0) s_bad = 0;
     __syncthreads();
     bool bad = false;
     for (int p = threadIdx.x; p < pot.n; p += 256) {
@@ -48,158 +51,133 @@ __global__ __launch_bounds__(256) void k_mix_prep(PotPtrs pot, GridDesc g, doubl
 
 // ---------------------------------------------------------------- FP32 field
 
-// FP32 SIE contribution of table row c for NPL nodes of a row: node-unit
-// offsets from the exact centre split (as in the general FP32 field), m = M d,
-// R^2 = d . m clamped below at 1e-30 (the centre, where m = 0, contributes 0),
-// alpha += (K/h) m / R.
-template <int NPL>
-__device__ __forceinline__ void sie32_pot(const float* __restrict__ c, float4 rc, const float* fi, float* sx,
+// Reciprocal root (the hardware instruction, 1 ulp) issued at raised wave
+// priority.  On gfx950 two waves of a SIMD issue a simple FP32 operation each in
+// the same four cycles, but a transcendental takes the SIMD alone for eight;
+// spread through the waves' streams they leave the simple operations unpaired
+// (probe at 8 waves per SIMD, this loop's mix: 4.19 cycles per instruction).  A
+// wave that reaches one goes first, the others' simple operations then pair up:
+// 3.19 cycles.  The closing s_setprio is also the wait state between a
+// transcendental and the first use of its result.  With few waves per SIMD there
+// is nothing to pair and the fixed order costs latency (300 x 211 x 30: 12 us
+// against 9), so the single-node layout uses the plain instruction.
+__device__ __forceinline__ float rsq_pri(float x)
+{
+    float r;
+    asm("s_setprio 3\n\tv_rsq_f32 %0, %1\n\ts_setprio 0" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// FP32 SIE contribution of table row c for NPL columns in each of NR rows (sx,
+// sy: [NR][NPL]): node-unit offsets from the exact centre split (as in the
+// general FP32 field), m = M d, R^2 = d . m clamped below at 1e-30 (the centre,
+// where m = 0, contributes 0), alpha += (K/h) m / R.  Without CLAMP the caller
+// knows that R^2 stays above 1e-30 (the result is then the same bit for bit).
+template <int NPL, int NR, bool CLAMP>
+__device__ __forceinline__ void sie32_pot(const float* __restrict__ c, const float4* rc, const float* fi, float* sx,
                                           float* sy)
 {
     const float cxh = c[T32_CXH], cxl = c[T32_CXL];
     const float A = c[T32_A], B = c[T32_B], K = c[T32_K];
-    const float nyv = rc.x, bny = rc.y, cny = rc.z;  // the row part (pots_wg)
 #pragma unroll
     for (int k = 0; k < NPL; k++) {
         const float nxv = (fi[k] - cxh) - cxl;
-        const float m1 = fmaf(A, nxv, bny);
-        const float m2 = fmaf(B, nxv, cny);
-        const float R2 = fmaxf(fmaf(nxv, m1, nyv * m2), 1e-30f);
-        const float kr = K * __builtin_amdgcn_rsqf(R2);
-        sx[k] = fmaf(kr, m1, sx[k]);
-        sy[k] = fmaf(kr, m2, sy[k]);
+#pragma unroll
+        for (int r = 0; r < NR; r++) {
+            const float m1 = fmaf(A, nxv, rc[r].y);
+            const float m2 = fmaf(B, nxv, rc[r].z);
+            float R2 = fmaf(nxv, m1, rc[r].x * m2);
+            if constexpr (CLAMP) R2 = fmaxf(R2, 1e-30f);
+            const float kr = K * (NPL * NR > 1 ? rsq_pri(R2) : __builtin_amdgcn_rsqf(R2));
+            sx[r * NPL + k] = fmaf(kr, m1, sx[r * NPL + k]);
+            sy[r * NPL + k] = fmaf(kr, m2, sy[r * NPL + k]);
+        }
     }
 }
 
-// Workgroup = 256 * NPL consecutive nodes of row blockIdx.y; each thread NPL
-// consecutive nodes.  Writes the FP32 field as double and clears the mask.
-template <int NPL>
-__global__ __launch_bounds__(256) void k_mix_field32(const float* __restrict__ tab32, int np, int nx,
+// Workgroup = 256 * NPL columns of NR consecutive rows; each thread NPL
+// consecutive columns of every row, so the column offset is formed once for the
+// NR rows.  The row parts (n_y, B n_y, C n_y) of up to 256 potentials at a time
+// are formed by one thread each, in LDS, with a bit per potential that needs the
+// clamp: its centre within a node of the block, or M so flat that R^2 is not
+// safely above 1e-30 half a node away (a potential stored with M = 0 among
+// them).  Bound by vector issue: 7 simple operations, 2 / NR for the column
+// offset and the reciprocal root per pixel and potential.  Writes the FP32 field
+// as double and clears the mask.
+template <int NPL, int NR>
+__global__ __launch_bounds__(256) void k_mix_field32(const float* __restrict__ tab32, int np, int nx, int ny,
                                                      double* __restrict__ ax, double* __restrict__ ay,
                                                      unsigned char* __restrict__ mask,
                                                      const MixState* __restrict__ st)
 {
-    const int j = blockIdx.y;
-    const int i0 = (blockIdx.x * 256 + threadIdx.x) * NPL;
-    if ((int)(blockIdx.x * 256 * NPL) >= nx) return;
-    const float fj = (float)j;
-    float fi[NPL], sx[NPL], sy[NPL];
+    __shared__ float4 srow[NR * 256];
+    __shared__ unsigned long long sclamp[4];
+    const int j0 = blockIdx.y * NR;
+    const int ib = blockIdx.x * 256 * NPL, i0 = ib + threadIdx.x * NPL;
+    float fi[NPL], sx[NR * NPL], sy[NR * NPL];
 #pragma unroll
-    for (int k = 0; k < NPL; k++) {
-        fi[k] = (float)(i0 + k);
-        sx[k] = 0.0f;
-        sy[k] = 0.0f;
-    }
+    for (int k = 0; k < NPL; k++) fi[k] = (float)(i0 + k);
+#pragma unroll
+    for (int q = 0; q < NR * NPL; q++) sx[q] = sy[q] = 0.0f;
     const bool bad = st->status != kStatusOk;
-    if (!bad)  // uniform over the launch
-        pots_wg<T32_STRIDE, T32_CYH, T32_CYL, T32_B, T32_C>(
-            tab32, np, fj, [&](const float* c, float4 rc) { sie32_pot<NPL>(c, rc, fi, sx, sy); });
-    const size_t row = (size_t)j * nx;
+    for (int p0 = 0; p0 < np && !bad; p0 += 256) {  // uniform over the launch
+        const int pc = min(256, np - p0);
+        if (p0 > 0) __syncthreads();  // the previous chunk has been read
+        bool clamp = false;
+        if ((int)threadIdx.x < pc) {
+            const float* c = tab32 + (size_t)(p0 + threadIdx.x) * T32_STRIDE;
+            const float A = c[T32_A], B = c[T32_B], C = c[T32_C];
 #pragma unroll
-    for (int k = 0; k < NPL; k++) {
-        if (i0 + k < nx) {
-            ax[row + i0 + k] = bad ? __builtin_nan("") : (double)sx[k];
-            ay[row + i0 + k] = bad ? __builtin_nan("") : (double)sy[k];
-            mask[row + i0 + k] = 0;
+            for (int r = 0; r < NR; r++) {
+                const float nyv = ((float)(j0 + r) - c[T32_CYH]) - c[T32_CYL];
+                srow[r * 256 + threadIdx.x] = make_float4(nyv, B * nyv, C * nyv, 0.0f);
+            }
+            const float cx = c[T32_CXH], cy = c[T32_CYH], det = A * C - B * B, tr = A + C;
+            const bool inside = cx >= (float)(ib - 2) && cx <= (float)(ib + 256 * NPL + 1) && cy >= (float)(j0 - 2) &&
+                                cy <= (float)(j0 + NR + 1);
+            // smallest eigenvalue of M h^2 >= det / tr; R^2 >= that / 4 outside
+            clamp = inside || !(det > 1e-4f * tr * tr) || !(det > 1e-27f * tr);
+        }
+        const unsigned long long b = __ballot(clamp);
+        if (lane_id() == 0) sclamp[threadIdx.x >> 6] = b;
+        __syncthreads();
+        for (int w = 0; w * 64 < pc; w++) {
+            const unsigned long long lw = sclamp[w];
+            const unsigned long long cl =
+                ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(lw >> 32)) << 32) |
+                (unsigned)__builtin_amdgcn_readfirstlane((int)lw);
+            const int n = min(64, pc - 64 * w);
+            auto add = [&](int q, auto clamped) {
+                const int p = 64 * w + q;
+                float4 rc[NR];
+#pragma unroll
+                for (int r = 0; r < NR; r++) rc[r] = srow[r * 256 + p];
+                sie32_pot<NPL, NR, decltype(clamped)::value>(tab32 + (size_t)(p0 + p) * T32_STRIDE, rc, fi, sx, sy);
+            };
+            for (int q = 0; q < n; q++) {  // a run without the clamp, then one with it
+                const unsigned long long rest = cl >> q;
+                const int stop = rest ? min(n, q + __builtin_ctzll(rest)) : n;
+                for (; q < stop; q++) add(q, std::false_type());
+                if (q < n) add(q, std::true_type());
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+        if (j0 + r >= ny) break;
+        const size_t row = (size_t)(j0 + r) * nx;
+#pragma unroll
+        for (int k = 0; k < NPL; k++) {
+            if (i0 + k < nx) {
+                ax[row + i0 + k] = bad ? __builtin_nan("") : (double)sx[r * NPL + k];
+                ay[row + i0 + k] = bad ? __builtin_nan("") : (double)sy[r * NPL + k];
+                mask[row + i0 + k] = 0;
+            }
         }
     }
 }
 
 // ---------------------------------------------------------------- DP blocks and criteria
-
-// Workgroup p marks the block of halo p: p x p pixels (pc for the first
-// n_cluster halos, pg for the others) spanning node indices [k - size/2,
-// k - size/2 + size) on each axis, k = (x_c - x0)/h rounded half away from
-// zero, clipped to the grid.
-__global__ __launch_bounds__(256) void k_mix_patches(PotPtrs pot, GridDesc g, int n_cluster, int pc, int pg,
-                                                     unsigned char* __restrict__ mask,
-                                                     const MixState* __restrict__ st)
-{
-    if (st->status != kStatusOk) return;
-    const int p = blockIdx.x;
-    const long long size = p < n_cluster ? pc : pg;
-    const long long ki = llround((pot.x[p] - g.x0) / g.h), kj = llround((pot.y[p] - g.y0) / g.h);
-    long long i0 = ki - size / 2, i1 = ki - size / 2 + size, j0 = kj - size / 2, j1 = kj - size / 2 + size;
-    i0 = i0 < 0 ? 0 : i0;
-    j0 = j0 < 0 ? 0 : j0;
-    i1 = i1 > g.nx ? g.nx : i1;
-    j1 = j1 > g.ny ? g.ny : j1;
-    if (i0 >= i1 || j0 >= j1) return;
-    const long long w = i1 - i0, n = w * (j1 - j0);
-    for (long long q = threadIdx.x; q < n; q += 256) {
-        const long long j = j0 + q / w, i = i0 + q % w;
-        mask[j * g.nx + i] = 1;
-    }
-}
-
-constexpr int kScanPer = 16;               // pixels per thread of the scan
-constexpr int kScanChunk = 256 * kScanPer;  // pixels per workgroup
-
-// Appends the pixels of chunk blockIdx.x (4096 consecutive pixels) that need
-// double precision to list[]: MODE 0, the block pixels (mask 1); MODE 1, the
-// pixels outside the blocks where the criteria of Sec. 3.3 hold on the field
-// so far (marked 2):
-//     d1 = ax(i,j) - ax(i-1,j), d2 = ay(i,j) - ay(i,j-1),
-//     d3 = ax(i,j) - ax(i,j-1), d4 = ay(i,j) - ay(i-1,j),
-//     |dx - d1| < t12, |dx - d2| < t12, |d3| > t34 or |d4| > t34,
-// a difference whose neighbour is outside the image not being evaluated.  The
-// workgroup compacts its pixels through a prefix sum in LDS: one list-counter
-// atomic per chunk.
-template <int MODE>
-__global__ __launch_bounds__(256) void k_mix_scan(const double* __restrict__ ax, const double* __restrict__ ay,
-                                                  int nx, long long n_nodes, double dx, double t12, double t34,
-                                                  unsigned char* __restrict__ mask, unsigned* __restrict__ list,
-                                                  MixState* __restrict__ st)
-{
-    __shared__ unsigned s_wave[4];
-    __shared__ unsigned s_base;
-    if (st->status != kStatusOk) return;
-    const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
-    const long long c0 = (long long)blockIdx.x * kScanChunk;
-    unsigned bits = 0, cnt = 0;
-#pragma unroll 4
-    for (int k = 0; k < kScanPer; k++) {
-        const long long n = c0 + k * 256 + t;
-        if (n >= n_nodes) break;
-        bool need = false;
-        const unsigned char m = mask[n];
-        if (MODE == 0) {
-            need = m == 1;
-        } else if (m == 0) {
-            const long long j = n / nx, i = n - j * nx;
-            const double x = ax[n], y = ay[n];
-            if (i > 0) {
-                const double d1 = x - ax[n - 1], d4 = y - ay[n - 1];
-                need = fabs(dx - d1) < t12 || fabs(d4) > t34;
-            }
-            if (j > 0) {
-                const double d2 = y - ay[n - nx], d3 = x - ax[n - nx];
-                need = need || fabs(dx - d2) < t12 || fabs(d3) > t34;
-            }
-            if (need) mask[n] = 2;
-        }
-        bits |= (need ? 1u : 0u) << k;
-        cnt += need ? 1u : 0u;
-    }
-    // exclusive prefix of the per-thread counts over the workgroup
-    unsigned inc = cnt;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned v = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += v;
-    }
-    if (lane == 63) s_wave[wave] = inc;
-    __syncthreads();
-    if (t == 0) {
-        const unsigned total = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
-        s_base = total ? atomicAdd(&st->n_list, total) : 0u;
-    }
-    __syncthreads();
-    unsigned pos = s_base + inc - cnt;
-    for (int w = 0; w < wave; w++) pos += s_wave[w];
-    for (int k = 0; k < kScanPer; k++)
-        if (bits & (1u << k)) list[pos++] = (unsigned)(c0 + k * 256 + t);
-}
 
 // 1/sqrt(x) in FP64 for a positive normal x: the hardware estimate (relative
 // error below 2^-24 on gfx950, measured) refined by one Newton-Raphson step
@@ -224,47 +202,185 @@ __device__ __forceinline__ void sie64_add(const double* __restrict__ t, double t
     s2 = fma(kr, m2, s2);
 }
 
-// FP64 gradient of list entries [lo, hi), lo = the block count (MODE 1) or 0
-// (MODE 0), hi = the list length.
-template <int MODE>
-__global__ __launch_bounds__(256) void k_mix_dp(const double* __restrict__ tab64, int np, GridDesc g,
-                                                const unsigned* __restrict__ list, double* __restrict__ ax,
-                                                double* __restrict__ ay, MixState* __restrict__ st)
+// The FP64 blocks of halos [p0, p0 + gridDim.x): `size` x `size` pixels spanning
+// node indices [k - size/2, k - size/2 + size) on each axis, k = (x_c - x0)/h
+// rounded half away from zero, clipped to the grid.  The workgroups of column
+// blockIdx.x mark halo blockIdx.x's pixels in the mask and write their FP64
+// gradient, 256 pixels at a time (a pixel of two blocks is written twice with
+// the same value).
+__global__ __launch_bounds__(256) void k_mix_blocks(PotPtrs pot, GridDesc g, int p0, int size_,
+                                                    const double* __restrict__ tab64, double* __restrict__ ax,
+                                                    double* __restrict__ ay, unsigned char* __restrict__ mask,
+                                                    const MixState* __restrict__ st)
 {
     if (st->status != kStatusOk) return;
-    const unsigned hi = st->n_list;
-    const unsigned lo = MODE == 0 ? 0u : st->n_patch;
-    for (unsigned e = lo + blockIdx.x * 256 + threadIdx.x; e < hi; e += gridDim.x * 256) {
-        const unsigned n = list[e];
-        const int j = (int)(n / (unsigned)g.nx), i = (int)(n - (unsigned)j * (unsigned)g.nx);
+    const int p = p0 + blockIdx.x;
+    const long long size = size_;
+    const long long ki = llround((pot.x[p] - g.x0) / g.h), kj = llround((pot.y[p] - g.y0) / g.h);
+    long long i0 = ki - size / 2, i1 = ki - size / 2 + size, j0 = kj - size / 2, j1 = kj - size / 2 + size;
+    i0 = i0 < 0 ? 0 : i0;
+    j0 = j0 < 0 ? 0 : j0;
+    i1 = i1 > g.nx ? g.nx : i1;
+    j1 = j1 > g.ny ? g.ny : j1;
+    if (i0 >= i1 || j0 >= j1) return;
+    const unsigned w = (unsigned)(i1 - i0), n = w * (unsigned)(j1 - j0);
+    for (unsigned q = blockIdx.y * 256 + threadIdx.x; q < n; q += gridDim.y * 256) {
+        const int j = (int)(j0 + q / w), i = (int)(i0 + q % w);
         const double t1 = node_coord(g.x0, i, g.h), t2 = node_coord(g.y0, j, g.h);
         double s1 = 0.0, s2 = 0.0;
 #pragma unroll 4
-        for (int p = 0; p < np; p++) sie64_add(tab64 + (size_t)p * T64_STRIDE, t1, t2, s1, s2);
-        ax[n] = s1;
-        ay[n] = s2;
+        for (int m = 0; m < pot.n; m++) sie64_add(tab64 + (size_t)m * T64_STRIDE, t1, t2, s1, s2);
+        const size_t o = (size_t)j * g.nx + i;
+        ax[o] = s1;
+        ay[o] = s2;
+        mask[o] = 1;
     }
 }
 
-// The block count is the list length after k_mix_scan<0> (read before the
-// criteria scan appends).
-__global__ void k_mix_mark(MixState* __restrict__ st)
+// Criteria of Sec. 3.3 on the field so far, one workgroup per 256 columns of
+// kScanRows rows, thread = column, the previous row's values kept in registers
+// and the left neighbour taken from the lane beside it (every value read once,
+// plus a row above the block and a column beside each wave):
+//     d1 = ax(i,j) - ax(i-1,j), d2 = ay(i,j) - ay(i,j-1),
+//     d3 = ax(i,j) - ax(i,j-1), d4 = ay(i,j) - ay(i-1,j),
+//     |dx - d1| < t12, |dx - d2| < t12, |d3| > t34 or |d4| > t34,
+// a difference whose neighbour is outside the image not being evaluated.
+// Pixels outside the blocks where one holds are marked 2.  counts[workgroup]
+// receives its block pixels and its criteria pixels (no atomics: thousands of
+// workgroups on one counter would queue for it).
+constexpr int kScanRows = 16;
+__global__ __launch_bounds__(256) void k_mix_scan(const double* __restrict__ ax, const double* __restrict__ ay,
+                                                  GridDesc g, double t12, double t34, unsigned char* __restrict__ mask,
+                                                  uint2* __restrict__ counts, const MixState* __restrict__ st)
 {
-    if (threadIdx.x == 0) st->n_patch = st->n_list;
+    __shared__ unsigned s_cnt[4][2];
+    unsigned nb = 0, nc = 0;
+    if (st->status == kStatusOk) {  // uniform over the launch
+        const int i = blockIdx.x * 256 + threadIdx.x, j0 = blockIdx.y * kScanRows;
+        const int ic = min(i, g.nx - 1), il = max(ic - 1, 0);
+        const bool in = i < g.nx, edge = lane_id() == 0;
+        double px = 0.0, py = 0.0;
+        if (j0 > 0) {
+            px = ax[(size_t)(j0 - 1) * g.nx + ic];
+            py = ay[(size_t)(j0 - 1) * g.nx + ic];
+        }
+        const int j1 = min(j0 + kScanRows, g.ny);
+        for (int j = j0; j < j1; j++) {
+            const size_t row = (size_t)j * g.nx;
+            const double x = ax[row + ic], y = ay[row + ic];
+            const unsigned char m = mask[row + ic];
+            double lx = __shfl_up(x, 1, 64), ly = __shfl_up(y, 1, 64);
+            if (edge) {
+                lx = ax[row + il];
+                ly = ay[row + il];
+            }
+            bool need = false;
+            if (i > 0) need = fabs(g.h - (x - lx)) < t12 || fabs(y - ly) > t34;
+            if (j > 0) need = need || fabs(g.h - (y - py)) < t12 || fabs(x - px) > t34;
+            need = need && in && m == 0;
+            if (need) mask[row + ic] = 2;
+            nc += need ? 1u : 0u;
+            nb += in && m == 1 ? 1u : 0u;
+            px = x;
+            py = y;
+        }
+    }
+    for (int k = 32; k >= 1; k >>= 1) {
+        nb += __shfl_xor(nb, k, 64);
+        nc += __shfl_xor(nc, k, 64);
+    }
+    if (lane_id() == 0) {
+        s_cnt[threadIdx.x >> 6][0] = nb;
+        s_cnt[threadIdx.x >> 6][1] = nc;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        counts[blockIdx.y * gridDim.x + blockIdx.x] =
+            make_uint2(s_cnt[0][0] + s_cnt[1][0] + s_cnt[2][0] + s_cnt[3][0],
+                       s_cnt[0][1] + s_cnt[1][1] + s_cnt[2][1] + s_cnt[3][1]);
 }
 
-__global__ void k_mix_stats(const MixState* __restrict__ st, long long* __restrict__ stats)
+// Units of a tile that hold criteria pixels, those pixels stored.
+struct CriteriaSink {
+    double *ax, *ay;
+    const unsigned char* mask;
+    int nx, ny;
+
+    __device__ __forceinline__ bool wants(int i0, int j0) const
+    {
+        const int lane = lane_id(), j = j0 + (lane & 15), i = i0 + 8 * (lane >> 4);
+        bool any = false;
+        if (j < ny)
+            for (int k = 0; k < 8; k++) any = any || (i + k < nx && mask[(size_t)j * nx + i + k] == 2);
+        return __ballot(any) != 0;
+    }
+    __device__ __forceinline__ void put(const double* sx, const double* sy, int i0, int j0) const
+    {
+        const int lane = lane_id(), j = j0 + (lane & 15);
+        if (j >= ny) return;
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int i = i0 + 16 * (k >> 2) + 4 * (lane >> 4) + (k & 3);
+            const size_t o = (size_t)j * nx + i;
+            if (i < nx && mask[o] == 2) {
+                ax[o] = sx[k];
+                ay[o] = sy[k];
+            }
+        }
+    }
+};
+
+// FP64 gradient of the criteria pixels: the tiled FP64 field (lens_tiles.hpp) on
+// the tiles that hold any.
+template <int T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_mix_dp(
+    const double* __restrict__ tab64, const float* __restrict__ tab32, int np, GridDesc g, int ntx,
+    const unsigned char* __restrict__ mask, double* __restrict__ ax, double* __restrict__ ay,
+    const MixState* __restrict__ st)
 {
+    __shared__ typename Tile64<T>::Lds lds;
+    if (st->status != kStatusOk) return;
+    const int tj = blockIdx.x / ntx, ti = blockIdx.x - tj * ntx;
+    const int i = ti * T + (int)(threadIdx.x % T);
+    bool any = false;
+    for (int j = tj * T + (int)(threadIdx.x / T); j < min(g.ny, tj * T + T); j += 256 / T)
+        any = any || (i < g.nx && mask[(size_t)j * g.nx + i] == 2);
+    if (!__syncthreads_or(any)) return;
+    tile64_body<T>(lds, IsoProfile{tab64, tab32}, np, g, ti * T, tj * T, CriteriaSink{ax, ay, mask, g.nx, g.ny});
+}
+
+// Totals and status.
+__global__ __launch_bounds__(1024) void k_mix_stats(const MixState* __restrict__ st, const uint2* __restrict__ counts,
+                                                    int n, long long* __restrict__ stats)
+{
+    __shared__ unsigned long long s_n[2];
+    if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+    __syncthreads();
+    unsigned long long nb = 0, nc = 0;
+    for (int k = threadIdx.x; k < n; k += 1024) {
+        nb += counts[k].x;
+        nc += counts[k].y;
+    }
+    if (nb) atomicAdd(&s_n[0], nb);
+    if (nc) atomicAdd(&s_n[1], nc);
+    __syncthreads();
     if (threadIdx.x == 0) {
         const bool ok = st->status == kStatusOk;
-        stats[0] = ok ? (long long)st->n_patch : 0;
-        stats[1] = ok ? (long long)(st->n_list - st->n_patch) : 0;
-        stats[2] = ok ? (long long)st->n_list : 0;
+        stats[0] = ok ? (long long)s_n[0] : 0;
+        stats[1] = ok ? (long long)s_n[1] : 0;
+        stats[2] = ok ? (long long)(s_n[0] + s_n[1]) : 0;
         stats[3] = st->status;
     }
 }
 
 // ---------------------------------------------------------------- launcher
+
+static dim3 scan_grid(const GridDesc& g)
+{
+    return dim3((unsigned)((g.nx + 255) / 256), (unsigned)((g.ny + kScanRows - 1) / kScanRows));
+}
+
+size_t mixed_counts(const GridDesc& g) { return (size_t)scan_grid(g).x * scan_grid(g).y; }
 
 hipError_t launch_mixed(const PotPtrs& pot, const GridDesc& g, const MixedLaunch& ml, hipStream_t s)
 {
@@ -272,35 +388,45 @@ hipError_t launch_mixed(const PotPtrs& pot, const GridDesc& g, const MixedLaunch
     k_mix_prep<<<1, 256, 0, s>>>(pot, g, ml.tab64, ml.tab32, ml.bterm, ml.st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int npl = ml.npl;
-    const dim3 fgrid((unsigned)((g.nx + 256 * npl - 1) / (256 * npl)), (unsigned)g.ny);
-    switch (npl) {
-    case 1: e = launch_ev(ml.ev, k_mix_field32<1>, fgrid, dim3(256), s, (const float*)ml.tab32, pot.n, g.nx, ml.ax,
-                      ml.ay, ml.mask, (const MixState*)ml.st); break;
-    case 2: e = launch_ev(ml.ev, k_mix_field32<2>, fgrid, dim3(256), s, (const float*)ml.tab32, pot.n, g.nx, ml.ax,
-                      ml.ay, ml.mask, (const MixState*)ml.st); break;
-    default: e = launch_ev(ml.ev, k_mix_field32<4>, fgrid, dim3(256), s, (const float*)ml.tab32, pot.n, g.nx, ml.ax,
-                       ml.ay, ml.mask, (const MixState*)ml.st); break;
-    }
+    // FP32 field layout: two columns of four rows per thread once there are
+    // workgroups enough (6730^2 x 702: 5.93 ms against 6.97 for 1 x 4, 6.35 for 2 x 2,
+    // 6.07 for 4 x 4, and 8.12 for the former 4 x 1 with the clamp everywhere), one
+    // column below (1200 x 900 x 200: 76 us against 86), single nodes for small images.
+    auto field = [&](auto kern, int c, int r) {
+        return launch_ev(ml.ev, kern, dim3((unsigned)((g.nx + 256 * c - 1) / (256 * c)), (unsigned)((g.ny + r - 1) / r)),
+                         dim3(256), s, (const float*)ml.tab32, pot.n, g.nx, g.ny, ml.ax, ml.ay, ml.mask,
+                         (const MixState*)ml.st);
+    };
+    e = n_nodes >= (4ll << 20)   ? field(k_mix_field32<2, 4>, 2, 4)
+        : n_nodes >= (1ll << 18) ? field(k_mix_field32<1, 4>, 1, 4)
+                                 : field(k_mix_field32<1, 1>, 1, 1);
+    if (e != hipSuccess) return e;
+    // blocks: 256 pixels per workgroup, a few workgroups per CU in all at least
+    auto blocks = [&](int p0, int n, int size) {
+        if (n <= 0 || size <= 0) return hipSuccess;
+        const long long px = (long long)std::min(size, g.nx) * std::min(size, g.ny);
+        const unsigned ny = (unsigned)std::min(std::max(1ll, 16384ll / n), (px + 255) / 256);
+        k_mix_blocks<<<dim3((unsigned)n, ny), 256, 0, s>>>(pot, g, p0, size, ml.tab64, ml.ax, ml.ay, ml.mask, ml.st);
+        return hipGetLastError();
+    };
+    if ((e = blocks(0, ml.n_cluster, ml.pc)) != hipSuccess) return e;
+    if ((e = blocks(ml.n_cluster, pot.n - ml.n_cluster, ml.pg)) != hipSuccess) return e;
+    const dim3 sg = scan_grid(g);
+    k_mix_scan<<<sg, 256, 0, s>>>(ml.ax, ml.ay, g, ml.t12, ml.t34, ml.mask, ml.counts, ml.st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (pot.n > 0) {
-        k_mix_patches<<<(unsigned)pot.n, 256, 0, s>>>(pot, g, ml.n_cluster, ml.pc, ml.pg, ml.mask, ml.st);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    const long long sb = (n_nodes + kScanChunk - 1) / kScanChunk;
-    const unsigned scan_blocks = (unsigned)(sb < 1 ? 1 : sb);
-    k_mix_scan<0><<<scan_blocks, 256, 0, s>>>(ml.ax, ml.ay, g.nx, n_nodes, g.h, ml.t12, ml.t34, ml.mask, ml.list,
-                                              ml.st);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_mix_mark<<<1, 64, 0, s>>>(ml.st);
-    k_mix_dp<0><<<2048, 256, 0, s>>>(ml.tab64, pot.n, g, ml.list, ml.ax, ml.ay, ml.st);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_mix_scan<1><<<scan_blocks, 256, 0, s>>>(ml.ax, ml.ay, g.nx, n_nodes, g.h, ml.t12, ml.t34, ml.mask, ml.list,
-                                              ml.st);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_mix_dp<1><<<2048, 256, 0, s>>>(ml.tab64, pot.n, g, ml.list, ml.ax, ml.ay, ml.st);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_mix_stats<<<1, 64, 0, s>>>(ml.st, ml.stats);
+    const int side = tile_side_for((double)n_nodes, (double)n_nodes, pot.n, kTileCost64);
+    auto dp = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        const int ntx = (g.nx + T - 1) / T;
+        k_mix_dp<T><<<(unsigned)(ntx * ((g.ny + T - 1) / T)), 256, 0, s>>>(ml.tab64, ml.tab32, pot.n, g, ntx, ml.mask,
+                                                                          ml.ax, ml.ay, ml.st);
+        return hipGetLastError();
+    };
+    e = side == 32   ? dp(std::integral_constant<int, 32>())
+        : side == 64 ? dp(std::integral_constant<int, 64>())
+                     : dp(std::integral_constant<int, 128>());
+    if (e != hipSuccess) return e;
+    k_mix_stats<<<1, 1024, 0, s>>>(ml.st, ml.counts, (int)mixed_counts(g), ml.stats);
     return hipGetLastError();
 }
 

@@ -309,7 +309,8 @@ __global__ __launch_bounds__(256) void k_nfw_tiled64(const double* __restrict__ 
 {
     __shared__ typename Tile64<T>::Lds lds;
     const int tj = blockIdx.x / ntx, ti = blockIdx.x - tj * ntx;
-    tile64_body<T>(lds, NfwProfile{t64, t32}, np, g, ti * T, tj * T, ax, ay, *st != kStatusOk, (double*)nullptr, 0);
+    tile64_body<T>(lds, NfwProfile{t64, t32}, np, g, ti * T, tj * T,
+                   FieldSink64{ax, ay, nullptr, g.nx, g.ny, *st != kStatusOk});
 }
 
 // ---------------------------------------------------------------- launcher

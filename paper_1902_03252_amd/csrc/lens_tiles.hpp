@@ -580,10 +580,29 @@ struct Tile64 {
     };
 };
 
-template <int T, class P>
+// Where a tile's units of 32 x 16 nodes go: to the field planes, with the range
+// records where asked for.
+struct FieldSink64 {
+    double *ax, *ay, *rec;
+    int nx, ny;
+    bool bad;  // the whole field is NaN
+
+    __device__ __forceinline__ bool wants(int, int) const { return true; }  // wave-uniform
+    __device__ __forceinline__ void put(double* sx, double* sy, int i0, int j0) const
+    {
+        if (bad)
+#pragma unroll
+            for (int k = 0; k < 8; k++) sx[k] = sy[k] = __builtin_nan("");
+        if (rec) write_records(sx, sy, i0, j0, nx, ny, (nx + 31) >> 5, rec);
+        const bool vec = (nx & 1) == 0 && (((size_t)ax | (size_t)ay) & 15) == 0;
+        store_unit(sx, ax, i0, j0, nx, ny, vec);
+        store_unit(sy, ay, i0, j0, nx, ny, vec);
+    }
+};
+
+template <int T, class P, class Sink>
 __device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P& prof, int np, const GridDesc& g,
-                                            int i0, int j0, double* __restrict__ ax, double* __restrict__ ay,
-                                            bool bad, double* __restrict__ rec, int nbx)
+                                            int i0, int j0, const Sink& sink)
 {
     constexpr float hw = 0.5f * (T - 1);
     const int tid = threadIdx.x, lane = lane_id(), wt = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -646,7 +665,6 @@ __device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P&
     // output value r of lane l of the matrix product is row l / 16 + 4 r: the x
     // nodes are assigned so that a lane holds four consecutive ones
     const int xi = 4 * (li & 3) + (li >> 2);
-    const bool vec = (g.nx & 1) == 0 && (((size_t)ax | (size_t)ay) & 15) == 0;
     for (int ru = 16 * wt; ru < T; ru += 64) {
         if (j0 + ru >= g.ny) break;
         const double t2 = node_coord(g.y0, j0 + ru + li, g.h);
@@ -670,6 +688,7 @@ __device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P&
         }
         for (int cu = 0; cu < T; cu += 32) {
             if (i0 + cu >= g.nx) break;
+            if (!sink.wants(i0 + cu, j0 + ru)) continue;
             doublex4 acc[2][2];
 #pragma unroll
             for (int b = 0; b < 2; b++) {
@@ -691,12 +710,10 @@ __device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P&
             for_list(L.lists.list, !all, nn, [&](int p) { prof.near64(p, t1, t2, sx, sy); });
 #pragma unroll
             for (int k = 0; k < 8; k++) {
-                sx[k] = bad ? __builtin_nan("") : sx[k] + r0;
-                sy[k] = bad ? __builtin_nan("") : sy[k] + r1;
+                sx[k] += r0;
+                sy[k] += r1;
             }
-            if (rec) write_records(sx, sy, i0 + cu, j0 + ru, g.nx, g.ny, nbx, rec);
-            store_unit(sx, ax, i0 + cu, j0 + ru, g.nx, g.ny, vec);
-            store_unit(sy, ay, i0 + cu, j0 + ru, g.nx, g.ny, vec);
+            sink.put(sx, sy, i0 + cu, j0 + ru);
         }
     }
 }
