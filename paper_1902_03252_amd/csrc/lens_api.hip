@@ -1189,6 +1189,11 @@ extern "C" int lens_hmc_step(lens_ctx* ctx, double* state, int32_t n, const lens
         return LENS_ERR_INVALID;
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return LENS_ERR_DEVICE;
+    if (hmc_small_fits(n, obs_ptrs(obs)))
+        return launch_hmc_small(state, n, obs_ptrs(obs), step, n_leapfrog, momentum, u, chi2, accepted, stream) ==
+                       hipSuccess
+                   ? LENS_OK
+                   : LENS_ERR_DEVICE;
     const int n7 = 7 * n;
     int rc;
     if ((rc = ensure(ctx, B_HMC, (size_t)3 * n7 * 8 + 64))) return rc;

@@ -36,6 +36,8 @@
 // so the kernels accumulate the node sums and apply the constants once.
 #include "lens_path.hpp"
 
+#include <type_traits>
+
 namespace lens {
 
 // Derivative constants of one potential, arcsec units.
@@ -51,7 +53,8 @@ __device__ __forceinline__ void dconst(const PotPtrs& pot, int p, double* d)
     const double eps = pot.eps[p], phi = pot.phi[p], a = pot.r_core[p], s = pot.r_cut[p];
     const double sig = pot.sigma_v[p];
     const bool sinf = isinf(s);
-    const double c2 = cos(2.0 * phi), s2 = sin(2.0 * phi);
+    double s2, c2;
+    sincos(2.0 * phi, &s2, &c2);
     d[D_XC] = row[T64_XC];
     d[D_YC] = row[T64_YC];
     d[D_A] = row[T64_A];
@@ -514,6 +517,294 @@ __global__ __launch_bounds__(256) void k_src_bwd(PotPtrs pot, ObsPtrs obs, const
         upd.p[k7] -= upd.kick * upd.step[k7] * (0.5 * gv);
         if (upd.drift) upd.q[k7] += upd.step[k7] * upd.p[k7];
     }
+}
+
+// ============================================================== HMC step in one workgroup
+
+// A whole Hamiltonian step of a small model (lens_hmc_step): one workgroup of
+// 1024 threads keeps the trajectory, the constants and the images in LDS, so
+// that a leapfrog step is four barriers instead of two launches with their
+// tickets and global round trips (50 potentials, 60 images, 10 leapfrogs: 180 ->
+// 84 us).  The same formulas as k_src_fwd and k_src_bwd, 16 lanes per image (the
+// potentials over the lanes) and 16 lanes per potential (the images over the
+// lanes).  Bound by FP64 issue on one compute unit: of 7.5 us per gradient, 3.6 are
+// the gradient sums, 2.5 the deflections, 1.3 the constants' trigonometry and
+// divisions (four waves share them), hence the limit on n_img * n.
+constexpr int kHmcRow = 13;  // table row stride in LDS (values 0 .. T64_SINF; odd: 16 lanes read 16 rows)
+struct HmcLds {
+    double *d, *t, *q, *p, *st, *x, *y, *is2, *bx, *by, *cx, *cy, *dls, *csys;
+    int *off, *sys;
+};
+__host__ __device__ inline size_t hmc_lds(int n, int n_img, int n_sys, char* base, HmcLds* L)
+{
+    size_t o = 0;
+    auto take = [&](size_t count) {
+        double* r = reinterpret_cast<double*>(base + o);
+        o += 8 * count;
+        return r;
+    };
+    HmcLds l;
+    l.d = take((size_t)n * D_STRIDE);
+    l.t = take((size_t)n * kHmcRow);
+    l.q = take((size_t)7 * n);
+    l.p = take((size_t)7 * n);
+    l.st = take((size_t)7 * n);
+    l.x = take(n_img);
+    l.y = take(n_img);
+    l.is2 = take(n_img);
+    l.bx = take(n_img);
+    l.by = take(n_img);
+    l.cx = take(n_img);
+    l.cy = take(n_img);
+    l.dls = take(n_sys);
+    l.csys = take(n_sys);
+    l.off = reinterpret_cast<int*>(take((n_sys + 2) / 2));
+    l.sys = reinterpret_cast<int*>(take((n_img + 1) / 2));
+    if (L) *L = l;
+    return o;
+}
+
+// Part `role` (0..3) of the derivative constants and the table row of potential
+// p from the parameters in LDS (the same expressions as dconst and row64), so
+// that four waves share the chain of trigonometry and divisions.
+__device__ __forceinline__ bool hmc_consts(const PotPtrs& pot, int p, int role, double* d, double* r)
+{
+    const double eps = pot.eps[p], a = pot.r_core[p], s = pot.r_cut[p];
+    const bool sinf = isinf(s);
+    if (role == 0) {
+        double sn, c;
+        sincos(pot.phi[p], &sn, &c);
+        const double a1 = 1.0 - eps, a2 = 1.0 + eps;
+        r[T64_A] = d[D_A] = a1 * c * c + a2 * sn * sn;
+        r[T64_B] = d[D_B] = -2.0 * eps * c * sn;
+        r[T64_C] = d[D_C] = a1 * sn * sn + a2 * c * c;
+        return true;
+    }
+    if (role == 1) {
+        double s2, c2;
+        sincos(2.0 * pot.phi[p], &s2, &c2);
+        d[D_AE] = -c2;
+        d[D_BE] = -s2;
+        d[D_AP] = 2.0 * eps * s2;
+        d[D_BP] = -2.0 * eps * c2;
+        return true;
+    }
+    const double sig = pot.sigma_v[p], ratio = sig / kCkms;
+    const double b0 = 4.0 * kPi * ratio * ratio * kArcsecPerRad;
+    const double K = sinf ? b0 : b0 * s / (s - a);
+    if (role == 2) {
+        r[T64_K] = d[D_K] = K;
+        d[D_KA] = sinf ? 0.0 : K / (s - a);
+        d[D_KS] = sinf ? 0.0 : -K * a / (s * (s - a));
+        return true;
+    }
+    const double k1 = 8.0 * kPi * sig / (kCkms * kCkms) * kArcsecPerRad;
+    d[D_KSIG] = sinf ? k1 : k1 * s / (s - a);
+    r[T64_XC] = d[D_XC] = pot.x[p];
+    r[T64_YC] = d[D_YC] = pot.y[p];
+    r[T64_A2] = d[D_A2] = a * a;
+    r[T64_S2] = d[D_S2] = sinf ? 0.0 : s * s;
+    r[T64_RA] = d[D_RA] = a;
+    r[T64_RS] = d[D_RS] = sinf ? 0.0 : s;
+    r[T64_SINF] = d[D_SINF] = sinf ? 1.0 : 0.0;
+    d[D_S2A2] = sinf ? 0.0 : (s - a) * (s + a);
+    d[D_SMA] = sinf ? 0.0 : s - a;
+    return isfinite(pot.x[p]) && isfinite(pot.y[p]) && isfinite(eps) && isfinite(pot.phi[p]) && isfinite(a) &&
+           isfinite(sig) && eps >= 0.0 && eps < 1.0 && a >= 0.0 && sig >= 0.0 && s > a;
+}
+
+__global__ __launch_bounds__(1024) void k_hmc_small(double* __restrict__ state, int n, ObsPtrs obs,
+                                                    const double* __restrict__ step, int n_leapfrog,
+                                                    const double* __restrict__ momentum, const double* __restrict__ u,
+                                                    double* __restrict__ chi2, int* __restrict__ accepted)
+{
+    extern __shared__ __align__(16) char lds[];
+    __shared__ double s_chi[2], s_kin[2][16];
+    __shared__ int s_ok, s_obs_ok, s_acc;
+    const int t = threadIdx.x, lane = lane_id(), n7 = 7 * n, ni = obs.n_img, ns = obs.n_sys;
+    HmcLds L;
+    hmc_lds(n, ni, ns, lds, &L);
+    for (int k = t; k < n7; k += 1024) {
+        L.q[k] = state[k];
+        L.st[k] = step[k];
+        L.p[k] = step[k] != 0.0 ? momentum[k] : 0.0;
+    }
+    for (int k = t; k <= ns; k += 1024) L.off[k] = obs.sys_off[k];
+    for (int k = t; k < ns; k += 1024) L.dls[k] = obs.dls[k];
+    for (int k = t; k < ni; k += 1024) {
+        const double sg = obs.sigma[k];
+        L.x[k] = obs.x[k];
+        L.y[k] = obs.y[k];
+        L.is2[k] = sg > 0.0 && isfinite(sg) ? 1.0 / (sg * sg) : __builtin_nan("");
+    }
+    if (t == 0) s_obs_ok = 1;
+    __syncthreads();
+    for (int k = t; k < ni; k += 1024) L.sys[k] = system_of(L.off, ns, k);
+    for (int i = t; i < ns; i += 1024) {
+        const int j0 = L.off[i], j1 = L.off[i + 1];
+        bool ok = j0 <= j1 && j0 >= 0 && j1 <= ni && isfinite(L.dls[i]) && L.dls[i] >= 0.0;
+        for (int j = j0; ok && j < j1; j++) ok = isfinite(L.is2[j]);
+        if (!ok) s_obs_ok = 0;
+    }
+    if (t == 0 && (L.off[0] != 0 || L.off[ns] != ni)) s_obs_ok = 0;
+    PotPtrs pot;
+    pot.n = n;
+    pot.x = L.q;
+    pot.y = L.q + n;
+    pot.eps = L.q + 2 * n;
+    pot.phi = L.q + 3 * n;
+    pot.r_core = L.q + 4 * n;
+    pot.r_cut = L.q + 5 * n;
+    pot.sigma_v = L.q + 6 * n;
+    int ok0 = 0, ok1 = 0;
+    for (int l = 0; l <= n_leapfrog; l++) {
+        __syncthreads();
+        if (t == 0) s_ok = s_obs_ok;
+        __syncthreads();
+        // constants; after the first gradient only what a step can have moved
+        for (int p = t & 255; p < n; p += 256) {
+            const int role = t >> 8;
+            const bool moved = l == 0 || (role < 2 ? L.st[2 * n + p] != 0.0 || L.st[3 * n + p] != 0.0 : true);
+            if (moved && !hmc_consts(pot, p, role, L.d + p * D_STRIDE, L.t + p * kHmcRow)) s_ok = 0;
+        }
+        __syncthreads();
+        for (int j0 = 0; j0 < ni; j0 += 64) {  // source positions, 16 lanes per image
+            const int j = j0 + (t >> 4);
+            double s1 = 0.0, s2 = 0.0;
+            if (j < ni)
+                for (int p = t & 15; p < n; p += 16) add_alpha64(L.t + p * kHmcRow, L.x[j], L.y[j], s1, s2);
+            s1 = sum16(s1);
+            s2 = sum16(s2);
+            if (j < ni && (t & 15) == 0) {
+                const double r = L.dls[L.sys[j]];
+                L.bx[j] = src_map(L.x[j], r, s1);
+                L.by[j] = src_map(L.y[j], r, s2);
+            }
+        }
+        __syncthreads();
+        const bool ok = s_ok != 0;
+        // cotangents, one thread per image (each sums its own system's images), and
+        // the systems' chi^2 at the trajectory's ends
+        const bool ends = l == 0 || l == n_leapfrog;
+        for (int e = t; ok && e < ni + (ends ? ns : 0); e += 1024) {
+            const bool img = e < ni;
+            const int i = img ? L.sys[e] : e - ni;
+            const int j0 = L.off[i], j1 = L.off[i + 1], m = j1 - j0;
+            double bx = 0.0, by = 0.0, c = 0.0, wx = 0.0, wy = 0.0;
+            for (int j = j0; j < j1; j++) {
+                bx += L.bx[j];
+                by += L.by[j];
+            }
+            if (m > 0) {
+                bx /= m;
+                by /= m;
+            }
+            for (int j = j0; j < j1; j++) {
+                const double dx = L.bx[j] - bx, dy = L.by[j] - by, w = L.is2[j];
+                c += (dx * dx + dy * dy) * w;
+                wx += dx * w;
+                wy += dy * w;
+            }
+            if (img) {
+                const double r = L.dls[i], w = L.is2[e];
+                L.cx[e] = -r * (2.0 * (L.bx[e] - bx) * w - 2.0 * wx / m);
+                L.cy[e] = -r * (2.0 * (L.by[e] - by) * w - 2.0 * wy / m);
+            } else {
+                L.csys[i] = c;
+            }
+        }
+        __syncthreads();
+        if (l == 0) ok0 = ok;
+        ok1 = ok;
+        if (ends && t < 64) {
+            double v = 0.0;
+            for (int i = t; ok && i < ns; i += 64) v += L.csys[i];
+            v = wave_sum(v);
+            if (t == 0) s_chi[l == 0 ? 0 : 1] = ok ? v : __builtin_nan("");
+        }
+        // gradient of potential p by 16 lanes, then the kick (half at both ends) and the drift
+        const double kick = ends ? 0.5 : 1.0;
+        for (int p0 = 0; p0 < n; p0 += 64) {
+            const int p = p0 + (t >> 4);
+            double acc[7] = {0, 0, 0, 0, 0, 0, 0};
+            const double* d = L.d + (p < n ? p : 0) * D_STRIDE;
+            if (ok && p < n) {
+                const DConst<double> k = load_dconst<double>(d);
+                auto run = [&](auto cut, auto sing) {
+                    for (int j = t & 15; j < ni; j += 16)
+                        vjp_sums<double, decltype(cut)::value, decltype(sing)::value>(
+                            k, L.x[j] - d[D_XC], L.y[j] - d[D_YC], L.cx[j], L.cy[j], acc);
+                };
+                using B0 = std::false_type;
+                using B1 = std::true_type;
+                if (k.sinf)
+                    k.a == 0.0 ? run(B0(), B1()) : run(B0(), B0());
+                else
+                    k.a == 0.0 ? run(B1(), B1()) : run(B1(), B0());
+            }
+#pragma unroll
+            for (int c = 0; c < 7; c++) acc[c] = sum16(acc[c]);
+            const int c = t & 15;
+            if (p < n && c < 7) {
+                const int k7 = c * n + p;
+                const double st = L.st[k7];
+                const double gv = ok ? vjp_combine(d, acc, c) : __builtin_nan("");
+                if (st != 0.0) {
+                    const double pn = L.p[k7] - kick * st * (0.5 * gv);
+                    L.p[k7] = pn;
+                    if (l < n_leapfrog) L.q[k7] += st * pn;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // H = chi^2 / 2 + |p|^2 / 2 at both ends, fixed-order sums
+    double k0 = 0.0, k1 = 0.0;
+    for (int k = t; k < n7; k += 1024) {
+        if (L.st[k] == 0.0) continue;
+        k0 += momentum[k] * momentum[k];
+        k1 += L.p[k] * L.p[k];
+    }
+    k0 = wave_sum(k0);
+    k1 = wave_sum(k1);
+    if (lane == 0) {
+        s_kin[0][t >> 6] = k0;
+        s_kin[1][t >> 6] = k1;
+    }
+    __syncthreads();
+    if (t == 0) {
+        double a = 0.0, b = 0.0;
+        for (int w = 0; w < 16; w++) {
+            a += s_kin[0][w];
+            b += s_kin[1][w];
+        }
+        const double c0 = s_chi[0], c1 = s_chi[1];
+        const double h0 = 0.5 * c0 + 0.5 * a, h1 = 0.5 * c1 + 0.5 * b;
+        const bool acc = ok0 && ok1 && isfinite(c1) && isfinite(h1) && log(u[0]) < h0 - h1;
+        s_acc = acc;
+        *chi2 = acc ? c1 : c0;
+        *accepted = acc ? 1 : 0;
+    }
+    __syncthreads();
+    if (s_acc)
+        for (int k = t; k < n7; k += 1024) state[k] = L.q[k];
+}
+
+// Whether k_hmc_small takes a model: its LDS fits 64 KB and its work is small
+// enough for one compute unit (about 2.2 us + 2.1 us per 1024 image-potential
+// terms a gradient, against 17 us for the two launches of the general path).
+bool hmc_small_fits(int n, const ObsPtrs& obs)
+{
+    return obs.n_img > 0 && (long long)n * obs.n_img <= 6144 && obs.n_sys <= 4096 &&
+           hmc_lds(n, obs.n_img, obs.n_sys, nullptr, nullptr) <= 64000;
+}
+
+hipError_t launch_hmc_small(double* state, int n, const ObsPtrs& obs, const double* step, int n_leapfrog,
+                            const double* momentum, const double* u, double* chi2, int* accepted, hipStream_t s)
+{
+    k_hmc_small<<<1, 1024, hmc_lds(n, obs.n_img, obs.n_sys, nullptr, nullptr), s>>>(state, n, obs, step, n_leapfrog,
+                                                                                  momentum, u, chi2, accepted);
+    return hipGetLastError();
 }
 
 __global__ void k_status(int* status, int v)

@@ -118,6 +118,29 @@ __device__ __forceinline__ double src_map(double t, double r, double a)
     return t - r * a;
 }
 
+// Value of another lane of the same row of 16 (DPP control CTRL): no LDS trip.
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// Sum over each row of 16 consecutive lanes (every lane gets it; fixed order).
+__device__ __forceinline__ double sum16(double v)
+{
+    v += dpp_mov<0xB1>(v);    // lane ^ 1
+    v += dpp_mov<0x4E>(v);    // lane ^ 2
+    v += dpp_mov<0x141>(v);   // the other quad of the 8 lanes
+    return v + dpp_mov<0x140>(v);  // the other 8 lanes
+}
+
 // ---------------------------------------------------------------- FP64 deflection
 
 // FP64 square root and reciprocal of positive normal arguments from the

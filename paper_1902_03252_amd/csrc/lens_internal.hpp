@@ -209,6 +209,10 @@ hipError_t launch_src(const PotPtrs& pot, const ObsPtrs& obs, double* beta, doub
                       SrcState* st, double* chi2, int* status, const double* g_chi2, double* grad,
                       const HmcUpdate* upd, hipStream_t s);
 
+bool hmc_small_fits(int n, const ObsPtrs& obs);
+hipError_t launch_hmc_small(double* state, int n, const ObsPtrs& obs, const double* step, int n_leapfrog,
+                            const double* momentum, const double* u, double* chi2, int* accepted, hipStream_t s);
+
 // Device state of the mixed-precision SIE gradient (set by its first kernel).
 struct MixState {
     int status;
