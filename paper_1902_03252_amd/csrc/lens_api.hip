@@ -944,8 +944,8 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
             h_perm[k] = perm[k];
             const int side = h_side[perm[k]];
             h_fo[k + 1] = h_fo[k] + (long long)((g.ny + side - 1) / side) * ((g.nx + side - 1) / side);
-            // triangle stage: one item per (tile row, block of 64 tile columns)
-            h_to[k + 1] = h_to[k] + (long long)(((g.nx - 2) / tx + 1 + 63) / 64) * ((g.ny - 2) / ty + 1);
+            // triangle stage: one item per (tile row, kTriTiles tile columns)
+            h_to[k + 1] = h_to[k] + (long long)(((g.nx - 2) / tx + kTriTiles) / kTriTiles) * ((g.ny - 2) / ty + 1);
         }
         ch.n_nodes = node;
         ch.n_fitems = h_fo[n];
@@ -1043,7 +1043,7 @@ extern "C" int lens_image_chi2_batched(lens_ctx* ctx, const lens_potentials* all
         (rc = ensure(ctx, B_SYS, (size_t)max_n * obs->n_sys * SYS_STRIDE * 8)) ||
         (rc = ensure(ctx, B_HITS, per_sample_hits * 2 * 8)) ||
         (rc = ensure(ctx, B_FLAGS, (size_t)(mixed ? kFlagScratch : 1) * 8)) ||
-        (rc = ensure(ctx, B_POS, per_sample_hits * 4 * 8)) || (rc = ensure(ctx, B_PART, (size_t)(max_tiles / 4 + 1) * 2 * 4)) ||
+        (rc = ensure(ctx, B_POS, per_sample_hits * 4 * 8)) || (rc = ensure(ctx, B_PART, (size_t)max_tiles * 2 * 4)) ||
         (rc = ensure(ctx, B_RR, (size_t)max_rr * (mixed ? 4 : 8))) ||
         (rc = ensure(ctx, B_BCOUNT, (size_t)max_n * 20 + 8 * 16)))
         return rc;
@@ -1092,7 +1092,7 @@ extern "C" int lens_image_chi2_batched(lens_ctx* ctx, const lens_potentials* all
         if (e == hipSuccess)
             e = launch_btail(bp, o, bs, hcap, flag_cap, hits, fb, pos, fb_pos, out->chi2 + ch.s0,
                              out->chi2_sys + (size_t)ch.s0 * o.n_sys, out->n_pred + (size_t)ch.s0 * o.n_sys,
-                             out->status + ch.s0, agg, part, (ch.n_tiles + 3) / 4,
+                             out->status + ch.s0, agg, part, ch.n_tiles,
                              want_hits ? out->n_hits + ch.s0 : nullptr,
                              want_hits ? out->hits + (size_t)ch.s0 * 2 * hcap : nullptr,
                              want_hits ? out->img_xy + (size_t)ch.s0 * 2 * hcap : nullptr, stream);

@@ -8,7 +8,7 @@
 //   k_bmap    work-item -> sample maps of the field and triangle stages
 //   k_btiled  FP32 or FP64 deflection, one workgroup per (sample, tile), heaviest
 //             samples first
-//   k_btri    one workgroup per (sample, tile), heaviest samples first
+//   k_btri    one workgroup per (sample, 32 tiles of a row), heaviest samples first
 //   k_bfbpos  FP64 image positions of every hit (a workgroup per sample) and
 //             the FP64 re-test of every undecided FP32 test
 //   k_btail   one workgroup per sample: sort, matching, chi^2
@@ -207,108 +207,190 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 
 // ============================================================== triangles
 
-// One wave per (sample, tile row, block of 64 tile columns) work item,
-// heaviest samples first; lane = tile column.  Each lane bounds its own
-// tile's source-plane vertices from the range partials (loads of consecutive
-// tiles are consecutive) and tests every system's barycentre against that
-// box (system rows are wave-uniform), keeping a mask of the passing systems.
-// The wave then stages each tile with a passing system in its own LDS tile
-// (lane order) and tests its cells for those systems, all lanes over the
-// cells.  Hits go to the sample's own list (system << 32 | triangle id),
-// undecided tests to the batch list (sample << 44 | system << 31 | triangle
-// id).
+__device__ __forceinline__ float lane_val(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_val(double v, int l) { return bcast(v, l); }
+
+// A system's cut of cells by their boxes: cell (i, j) of the grid with
+// deflections in [lo, hi] holds the barycentre in neither triangle if
+//   fma(-r, hi_x, i h) > above[0]  or  fma(-r, lo_x, (i + 1) h) < below[0],
+// or the same in y.  The bounds hold the barycentre's offset from the grid's first
+// node, E_B, and room for this form's own rounding: 16 u (u = 2^-24 or 2^-53) of
+// the grid's and the barycentre's extent, where it is at most 6 u of them, and for
+// the deflection's part 4 E_B (E_B holds 2 u r W, the part is below 3 u r W); FP64:
+// 1e-9, as for the tiles.  A negative r is not cut.
+template <typename V>
+struct CellCut {
+    V r, above[2], below[2];
+};
+template <typename V>
+__device__ __forceinline__ CellCut<V> cell_cut(const GridDesc& g, const SysVals& y)
+{
+    CellCut<V> c;
+    V o[2], w[2];
+    if constexpr (sizeof(V) == 4) {
+        const float h = (float)g.h;
+        c.r = y.r32;
+        o[0] = (-y.bxh - y.bxl) * h;
+        o[1] = (-y.byh - y.byl) * h;
+        w[0] = 5.0f * y.e + 1e-6f * (fabsf(o[0]) + (float)g.nx * h);
+        w[1] = 5.0f * y.e + 1e-6f * (fabsf(o[1]) + (float)g.ny * h);
+    } else {
+        c.r = y.r;
+        o[0] = g.x0 - y.bx;
+        o[1] = g.y0 - y.by;
+        w[0] = w[1] = 1e-9;
+    }
+#pragma unroll
+    for (int d = 0; d < 2; d++) {
+        c.above[d] = c.r < V(0) ? V(INFINITY) : w[d] - o[d];
+        c.below[d] = c.r < V(0) ? V(-INFINITY) : -w[d] - o[d];
+    }
+    return c;
+}
+
+// One workgroup per (sample, tile row, kTriTiles consecutive tile columns) work
+// item, heaviest samples first.  Culling: lane l bounds tile l % 32's source-plane
+// vertices from the range records and tests two systems' barycentres per ballot
+// against that box, the waves taking turns in a chunk of 64 systems; LDS holds one
+// word per system, bit t = tile t passes.  Each tile with a passing system is then
+// cut into strips of 64 cells, one per lane, the strips dealt to the four waves
+// and the next strip's nodes loaded meanwhile.  A cell is first tested by the box
+// of its deflections alone (CellCut: 4 FMAs and 4 compares per system); the few
+// near cells load their nodes again and take the triangle tests.
+// Bound by latency and instruction issue together (54 % of the cycles issue a
+// vector instruction, 60 % of the waves' time is spent waiting, for records and
+// fields that the field stage left in HBM), hence four waves to a tile, no LDS
+// tile, and few registers (6 waves per SIMD).  32 x 8 tiles, one wave per (row, 64
+// columns) with the tiles in LDS before: 96 samples 334 -> 192 us, 256 chains of
+// 512^2 668 -> 210 us.  Items of 8 and 16 tiles took 297 and 226 us (222, 207),
+// of 64 191 us (247): workgroups without a passing tile against balance.
+// Hits go to the sample's own list (system << 32 | triangle id), undecided tests
+// to the batch list (sample << 44 | system << 31 | triangle id).
+static_assert(kTriTiles == 32, "two systems of 32 tiles per ballot, one word per system");
 template <class S, typename V>
-__global__ __launch_bounds__(256) void k_btri(BatchPlan bp, const int* __restrict__ tmap, long long n_items,
-                                              int nsys, const double* __restrict__ sysrow, const V* __restrict__ fx,
+__global__ __launch_bounds__(256) void k_btri(BatchPlan bp, const int* __restrict__ tmap, int nsys,
+                                              const double* __restrict__ sysrow, const V* __restrict__ fx,
                                               const V* __restrict__ fy, const V* __restrict__ rr, BatchState bs,
                                               int mode, double tau, int hcap, unsigned long long* __restrict__ hits,
                                               unsigned long long* __restrict__ flags, long long flag_cap,
                                               unsigned* __restrict__ part)
 {
-    __shared__ V sx[4][S::TNY][S::TNX], sy[4][S::TNY][S::TNX];
+    constexpr int RW = 64 / S::TX;               // cell rows of a strip
+    constexpr int NS = S::TX * S::TY / 256;      // strips per wave and tile
+    constexpr int SB = 64 / kTriTiles;           // systems per ballot
+    __shared__ unsigned long long spass[kTriTiles], sany[4];
     __shared__ unsigned sp[4][2];
-    const int wave = threadIdx.x >> 6, lane = lane_id();
-    const long long item = (long long)blockIdx.x * 4 + wave;
-    unsigned npair = 0, nbbox = 0;  // per lane: passing (tile, system) pairs of its tile; bbox passes
-    if (item < n_items) {
-        const int k = tmap[item];
-        const int s = bp.perm[k];
-        const GridDesc g = bp.grid[s];
-        const int tiles_x = (g.nx - 2) / S::TX + 1;
-        const int blocks_x = (tiles_x + 63) / 64;
-        const int local = (int)(item - bp.titem_off[k]);
-        const int band = local / blocks_x, cb = local - band * blocks_x;
-        const int col = cb * 64 + lane;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = lane_id();
+    unsigned npair = 0, nbbox = 0;  // passing (tile, system) pairs (wave-uniform); bbox passes per lane
+    const int k = tmap[blockIdx.x];
+    const int s = bp.perm[k];
+    const GridDesc g = bp.grid[s];
+    const int tiles_x = (g.nx - 2) / S::TX + 1;
+    const int blocks_x = (tiles_x + kTriTiles - 1) / kTriTiles;
+    const int local = (int)(blockIdx.x - bp.titem_off[k]);
+    const int band = local / blocks_x, c0 = (local - band * blocks_x) * kTriTiles;
+    const double* rows = sysrow + (size_t)s * nsys * SYS_STRIDE;
+    const V* sfx = fx + bp.node_off[s];
+    const V* sfy = fy + bp.node_off[s];
+    const float tau32 = (float)(tau * g.h * g.h);
+    const int cj0 = band * S::TY, ncy = min(S::TY, g.ny - 1 - cj0);  // of every tile of the row
+    // the lane's cell of the wave's strip n of tile t
+    auto cell = [&](int t, int n, int& gi, int& gj) -> bool {
+        const int ci0 = (c0 + t) * S::TX, li = lane % S::TX, lj = RW * (wave + 4 * n) + lane / S::TX;
+        const bool in = lj < ncy && ci0 + li < g.nx - 1;
+        gi = in ? ci0 + li : ci0;
+        gj = in ? cj0 + lj : cj0;
+        return in;
+    };
+    const V h = (V)g.h;
+    for (int sb = 0; sb < nsys; sb += 64) {
+        if (sb) __syncthreads();  // spass is read
+        CellCut<V> cut;
+        {
+            const int sys = min(sb + lane, nsys - 1);
+            cut = cell_cut<V>(g, sys_vals<V>(rows + (size_t)sys * SYS_STRIDE));
+        }
+        // the range and box values are needed here only: an opaque lane keeps the
+        // compiler from holding them in registers over the strips below
+        int cl = lane;
+        asm volatile("" : "+v"(cl));
+        const int col = c0 + (cl & (kTriTiles - 1));
         const bool act = col < tiles_x;
         const Tile T = tile_of<S>(g, tiles_x, band * tiles_x + (act ? col : 0));
         double rng[4] = {0.0, 0.0, 0.0, 0.0};
         if (act) tile_range_rec<S, V>(rr + bp.rr_off[s], (g.nx + 31) >> 5, (g.ny + 7) >> 3, T, rng);
-        const double* rows = sysrow + (size_t)s * nsys * SYS_STRIDE;
-        const V* sfx = fx + bp.node_off[s];
-        const V* sfy = fy + bp.node_off[s];
-        for (int sb = 0; sb < nsys; sb += 64) {
-            const int ns = min(64, nsys - sb);
-            // the chunk's system rows in one round of loads (lane = system), then broadcast
-            double lr = 0.0, leb = 0.0, lbx = 0.0, lby = 0.0;
-            if (lane < ns) {
-                const double* row = rows + (size_t)(sb + lane) * SYS_STRIDE;
-                lr = row[SYS_R];
-                leb = sizeof(V) == 4 ? row[SYS_EB] : 1e-9;
-                lbx = row[SYS_BX];
-                lby = row[SYS_BY];
+        unsigned long long any = 0;
+        for (int c = wave; c < kTriTiles && sb + c * SB < nsys; c += 4) {
+            const int sys = sb + c * SB + cl / kTriTiles;
+            bool in = false;
+            if (act && sys < nsys) {
+                const double* row = rows + (size_t)sys * SYS_STRIDE;
+                in = tile_box_contains(g, T, rng, row[SYS_R], sizeof(V) == 4 ? row[SYS_EB] : 1e-9, row[SYS_BX],
+                                       row[SYS_BY]);
             }
-            unsigned long long mask = 0;
-            for (int c = 0; c < ns; c++) {
-                if (act && tile_box_contains(g, T, rng, bcast(lr, c), bcast(leb, c), bcast(lbx, c), bcast(lby, c)))
-                    mask |= 1ull << c;
-            }
-            npair += (unsigned)__popcll(mask);
-            unsigned long long tiles = __ballot(mask != 0);
-            // the passing tiles in lane order; for tiles of up to 40 bytes of
-            // nodes per lane the next tile's nodes are loaded into registers
-            // while the current one is tested
-            constexpr bool kPre = TileRegs<S, V>::K * (int)sizeof(V) <= 40;
-            int l = tiles ? __ffsll((long long)tiles) - 1 : 0;
-            TileRegs<S, V> nxt;
-            if (kPre && tiles)
-                fetch_tile_regs<S, V>(sfx, sfy, g, tile_of<S>(g, tiles_x, band * tiles_x + cb * 64 + l), nxt);
-            while (tiles) {
+            const unsigned long long m = __ballot(in);
+            npair += (unsigned)__popcll(m);
+            any |= m;
+            if (lane == 0) spass[c] = m;
+        }
+        if (lane == 0) sany[wave] = any;
+        __syncthreads();
+        const unsigned long long all = sany[0] | sany[1] | sany[2] | sany[3];
+        // tiles that a system passes
+        unsigned tiles = (unsigned)__builtin_amdgcn_readfirstlane((int)(all | (all >> 32)));
+        if (tiles == 0) continue;
+        // bit t: tile t passes system sb + lane
+        const unsigned mine = sb + lane < nsys ? ((const unsigned*)spass)[lane] : 0;
+        int t = __ffs((int)tiles) - 1, n = 0, gi, gj;
+        bool in = cell(t, n, gi, gj);
+        V a[8];
+        load_cell(sfx, sfy, g, gi, gj, a);
+        while (tiles) {
+            const int tc = t, ci = gi, cj = gj;
+            const bool cin = in;
+            const V lx = fmin(fmin(a[0], a[1]), fmin(a[2], a[3])), hx = fmax(fmax(a[0], a[1]), fmax(a[2], a[3]));
+            const V ly = fmin(fmin(a[4], a[5]), fmin(a[6], a[7])), hy = fmax(fmax(a[4], a[5]), fmax(a[6], a[7]));
+            if (++n == NS) {
+                n = 0;
                 tiles &= tiles - 1;
-                unsigned long long m = __shfl(mask, l, 64);
-                const Tile Tl = tile_of<S>(g, tiles_x, band * tiles_x + cb * 64 + l);
-                if constexpr (kPre) {
-                    store_tile_regs<S, V>(nxt, Tl, sx[wave], sy[wave]);
-                    if (tiles) {
-                        l = __ffsll((long long)tiles) - 1;
-                        fetch_tile_regs<S, V>(sfx, sfy, g, tile_of<S>(g, tiles_x, band * tiles_x + cb * 64 + l), nxt);
-                    }
-                } else {
-                    stage_tile_wave<S, V>(sfx, sfy, g, Tl, sx[wave], sy[wave]);
-                    if (tiles) l = __ffsll((long long)tiles) - 1;
-                }
-                while (m) {
-                    const int c = __ffsll((long long)m) - 1;
-                    m &= m - 1;
-                    const unsigned sys = (unsigned)(sb + c);
-                    const double* row = rows + (size_t)sys * SYS_STRIDE;  // wave-uniform
-                    if constexpr (sizeof(V) == 4) {
-                        const float fr[6] = {(float)row[SYS_R],   (float)row[SYS_EB],  (float)row[SYS_BXH],
-                                             (float)row[SYS_BXL], (float)row[SYS_BYH], (float)row[SYS_BYL]};
-                        tri32_system<S, 64>(g, Tl, sx[wave], sy[wave], fr, ((unsigned long long)sys << 32),
-                                            ((unsigned long long)s << 44) | ((unsigned long long)sys << 31), mode,
-                                            (float)(tau * g.h * g.h), &bs.n_hits[s], hits + (size_t)s * hcap, hcap,
-                                            bs.n_flags, flags, flag_cap, nbbox, lane);
-                    } else {
-                        tri64_system<S, 64>(g, Tl, sx[wave], sy[wave], row[SYS_R], row[SYS_BX], row[SYS_BY],
-                                            ((unsigned long long)sys << 32), &bs.n_hits[s], hits + (size_t)s * hcap,
-                                            hcap, nbbox, lane);
-                    }
-                }
+                t = tiles ? __ffs((int)tiles) - 1 : t;
+            }
+            if (tiles) {
+                in = cell(t, n, gi, gj);
+                load_cell(sfx, sfy, g, gi, gj, a);
+            }
+            if (__ballot(cin) == 0) continue;  // outside the grid
+            const V x0 = (V)ci * h, x1 = (V)(ci + 1) * h, y0 = (V)cj * h, y1 = (V)(cj + 1) * h;
+            unsigned long long m = __ballot(((mine >> tc) & 1) != 0);
+            while (m) {
+                const int l = __ffsll((long long)m) - 1;
+                m &= m - 1;
+                const V r = lane_val(cut.r, l);
+                const bool near = cin && !(fma(-r, hx, x0) > lane_val(cut.above[0], l)) &&
+                                  !(fma(-r, lx, x1) < lane_val(cut.below[0], l)) &&
+                                  !(fma(-r, hy, y0) > lane_val(cut.above[1], l)) &&
+                                  !(fma(-r, ly, y1) < lane_val(cut.below[1], l));
+                if (__ballot(near) == 0) continue;
+                // few cells come here: their nodes (in the caches) and the system's row again
+                // rather than in registers all along
+                V av[8];
+                load_cell(sfx, sfy, g, ci, cj, av);
+                const SysVals y = sys_vals<V>(rows + (size_t)(sb + l) * SYS_STRIDE);
+                const unsigned bits = near ? test_cell(g, ci, cj, av, y, mode, tau32, nbbox) : 0u;
+                if (__ballot(bits != 0) == 0) continue;  // the common case: no hit, nothing undecided
+                const unsigned long long sys = (unsigned)(sb + l);
+                const unsigned tid0 = (unsigned)(2 * (cj * (g.nx - 1) + ci));
+                const unsigned long long hb = sys << 32, fb = ((unsigned long long)s << 44) | (sys << 31);
+                wave_append((bits & 3u) == kHit, hb | tid0, &bs.n_hits[s], hits + (size_t)s * hcap, hcap);
+                wave_append((bits >> 2) == kHit, hb | (tid0 + 1), &bs.n_hits[s], hits + (size_t)s * hcap, hcap);
+                wave_append((bits & 3u) == kFlag, fb | tid0, bs.n_flags, flags, flag_cap);
+                wave_append((bits >> 2) == kFlag, fb | (tid0 + 1), bs.n_flags, flags, flag_cap);
             }
         }
     }
-    // the pairs as a wave-uniform count, as write_part_sum takes them
-    for (int m = 32; m >= 1; m >>= 1) npair += __shfl_xor(npair, m, 64);
     write_part_sum(part, blockIdx.x, npair, nbbox, sp);
 }
 
@@ -578,14 +660,14 @@ hipError_t launch_btri(const BatchPlan& bp, const int* tmap, long long n_items, 
                        double tau, int hcap, unsigned long long* hits, unsigned long long* flags, long long flag_cap,
                        unsigned* part, int shape, hipStream_t s)
 {
-    const unsigned nb = (unsigned)((n_items + 3) / 4);
+    const unsigned nb = (unsigned)n_items;
     return with_bshape(shape, [&](auto sh) {
         using S = decltype(sh);
         if (fp32)
-            k_btri<S, float><<<nb, 256, 0, s>>>(bp, tmap, n_items, nsys, sysrow, (const float*)fx, (const float*)fy,
+            k_btri<S, float><<<nb, 256, 0, s>>>(bp, tmap, nsys, sysrow, (const float*)fx, (const float*)fy,
                                                 (const float*)rr, bs, mode, tau, hcap, hits, flags, flag_cap, part);
         else
-            k_btri<S, double><<<nb, 256, 0, s>>>(bp, tmap, n_items, nsys, sysrow, (const double*)fx,
+            k_btri<S, double><<<nb, 256, 0, s>>>(bp, tmap, nsys, sysrow, (const double*)fx,
                                                  (const double*)fy, (const double*)rr, bs, mode, tau, hcap, hits,
                                                  flags, flag_cap, part);
         return hipGetLastError();

@@ -57,7 +57,7 @@ struct BatchPlan {
     const int* perm;              // [n] plan position -> sample (heaviest first)
     const int* side;              // [n] nodes per side of the sample's field tiles
     const long long* fitem_off;   // [n+1] field work items (tiles), in plan order
-    const long long* titem_off;   // [n+1] triangle-stage items (tile row x 64 tile columns), in plan order
+    const long long* titem_off;   // [n+1] triangle-stage items (tile row x kTriTiles columns), in plan order
     const long long* node_off;    // [n] offset of each sample's field (nodes)
     const long long* rr_off;      // [n] offset of each sample's range records (values)
 };
@@ -73,6 +73,7 @@ struct BatchState {
 constexpr long long kHitScratch = 8192;   // largest hit list sorted in LDS (2^13)
 constexpr long long kFlagScratch = 1 << 20;
 constexpr int kMaxSystems = 1 << 19;      // systems fit the packed sort key
+constexpr int kTriTiles = 32;  // tile columns per work item of the batched triangle stage
 constexpr int kBatchMax = 1024;           // batch: per-sample hit capacity, images and systems
 
 // Arguments of the head's source-plane part when it runs inside a field launch.

@@ -496,10 +496,9 @@ __global__ __launch_bounds__(256) void k_cull(const V* __restrict__ rr, GridDesc
 
 // Containment of one (tile, system) pair by one wave: the tile's cells are
 // strided over the lanes, up to four cells per lane per step, with every vertex
-// load of a step issued before any decision.  Mixed path: FP32 vertex offsets
-// and the certified sign test; FP64 path: exact containment on the FP64
-// field's vertices.  Certain hits and undecided tests are appended (system <<
-// 32 | triangle id) with one atomic per wave.  All 64 lanes call it together.
+// load of a step issued before any decision (test_cell).  Certain hits and
+// undecided tests are appended (system << 32 | triangle id) with one atomic per
+// wave.  All 64 lanes call it together.
 template <class S, typename V>
 __device__ __forceinline__ void pair_test(const V* __restrict__ ax, const V* __restrict__ ay, const GridDesc& g,
                                           const Tile& T, int sys, const double* __restrict__ sysrow,
@@ -512,72 +511,21 @@ __device__ __forceinline__ void pair_test(const V* __restrict__ ax, const V* __r
     constexpr int QB = Q < 4 ? Q : 4;      // cells per lane per step
     const int lane = lane_id();
     // the system's row, read once per pair (sys is wave-uniform: scalar loads)
-    const double* row = sysrow + (size_t)sys * SYS_STRIDE;
-    const double rr64 = row[SYS_R], rbx = row[SYS_BX], rby = row[SYS_BY];
-    const float r32 = (float)rr64, e32 = (float)row[SYS_EB];
-    const float bxh = (float)row[SYS_BXH], bxl = (float)row[SYS_BXL];
-    const float byh = (float)row[SYS_BYH], byl = (float)row[SYS_BYL];
+    const SysVals y = sys_vals<V>(sysrow + (size_t)sys * SYS_STRIDE);
     for (int q0 = 0; q0 < Q; q0 += QB) {
         V va[QB][8];
 #pragma unroll
         for (int b = 0; b < QB; b++) {
             const int c = lane + 64 * (q0 + b), li = c % S::TX, lj = c / S::TX;
             const bool valid = li < T.ncx && lj < T.ncy;
-            const size_t n00 = valid ? (size_t)(T.cj0 + lj) * g.nx + (T.ci0 + li) : 0;
-            const size_t n01 = n00 + g.nx;
-            va[b][0] = ax[n00];
-            va[b][1] = ax[n00 + 1];
-            va[b][2] = ax[n01];
-            va[b][3] = ax[n01 + 1];
-            va[b][4] = ay[n00];
-            va[b][5] = ay[n00 + 1];
-            va[b][6] = ay[n01];
-            va[b][7] = ay[n01 + 1];
+            load_cell(ax, ay, g, valid ? T.ci0 + li : 0, valid ? T.cj0 + lj : 0, va[b]);
         }
         unsigned bits = 0;  // 4 bits per cell: result of triangle 0, then triangle 1
 #pragma unroll
         for (int b = 0; b < QB; b++) {
             const int c = lane + 64 * (q0 + b), li = c % S::TX, lj = c / S::TX;
-            if (!(li < T.ncx && lj < T.ncy)) continue;
-            const int gi = T.ci0 + li, gj = T.cj0 + lj;
-            int res0 = kMiss, res1 = kMiss;
-            if constexpr (sizeof(V) == 4) {
-                const float r = r32, E = e32;
-                const float h32 = (float)g.h;
-                const float ex0 = (((float)gi - bxh) - bxl) * h32;
-                const float ex1 = (((float)(gi + 1) - bxh) - bxl) * h32;
-                const float ey0 = (((float)gj - byh) - byl) * h32;
-                const float ey1 = (((float)(gj + 1) - byh) - byl) * h32;
-                const float d00x = fmaf(-r, va[b][0], ex0), d00y = fmaf(-r, va[b][4], ey0);
-                const float d10x = fmaf(-r, va[b][1], ex1), d10y = fmaf(-r, va[b][5], ey0);
-                const float d01x = fmaf(-r, va[b][2], ex0), d01y = fmaf(-r, va[b][6], ey1);
-                const float d11x = fmaf(-r, va[b][3], ex1), d11y = fmaf(-r, va[b][7], ey1);
-                const float tx[3] = {d00x, d10x, d01x}, ty[3] = {d00y, d10y, d01y};
-                const float ux[3] = {d11x, d01x, d10x}, uy[3] = {d11y, d01y, d10y};
-                res0 = decide32(tx, ty, E, mode, tau, nbbox);
-                res1 = decide32(ux, uy, E, mode, tau, nbbox);
-            } else {
-                const double r = rr64, bx = rbx, by = rby;
-                const double t0x = node_coord(g.x0, gi, g.h), t1x = node_coord(g.x0, gi + 1, g.h);
-                const double t0y = node_coord(g.y0, gj, g.h), t1y = node_coord(g.y0, gj + 1, g.h);
-                const double b00x = src_map(t0x, r, va[b][0]), b00y = src_map(t0y, r, va[b][4]);
-                const double b10x = src_map(t1x, r, va[b][1]), b10y = src_map(t0y, r, va[b][5]);
-                const double b01x = src_map(t0x, r, va[b][2]), b01y = src_map(t1y, r, va[b][6]);
-                const double b11x = src_map(t1x, r, va[b][3]), b11y = src_map(t1y, r, va[b][7]);
-                const double vx0[3] = {b00x, b10x, b01x}, vy0[3] = {b00y, b10y, b01y};
-                const double vx1[3] = {b11x, b01x, b10x}, vy1[3] = {b11y, b01y, b10y};
-                if (!(bx < fmin(vx0[0], fmin(vx0[1], vx0[2])) || bx > fmax(vx0[0], fmax(vx0[1], vx0[2])) ||
-                      by < fmin(vy0[0], fmin(vy0[1], vy0[2])) || by > fmax(vy0[0], fmax(vy0[1], vy0[2])))) {
-                    nbbox++;
-                    res0 = contains_exact(vx0, vy0, bx, by) ? kHit : kMiss;
-                }
-                if (!(bx < fmin(vx1[0], fmin(vx1[1], vx1[2])) || bx > fmax(vx1[0], fmax(vx1[1], vx1[2])) ||
-                      by < fmin(vy1[0], fmin(vy1[1], vy1[2])) || by > fmax(vy1[0], fmax(vy1[1], vy1[2])))) {
-                    nbbox++;
-                    res1 = contains_exact(vx1, vy1, bx, by) ? kHit : kMiss;
-                }
-            }
-            bits |= (unsigned)(res0 | (res1 << 2)) << (4 * b);
+            if (li < T.ncx && lj < T.ncy)
+                bits |= test_cell(g, T.ci0 + li, T.cj0 + lj, va[b], y, mode, tau, nbbox) << (4 * b);
         }
         if (__ballot(bits != 0) == 0) continue;  // the common case: no hit, nothing undecided
         const unsigned long long base = (unsigned long long)(unsigned)sys << 32;

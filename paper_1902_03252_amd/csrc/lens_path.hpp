@@ -367,9 +367,11 @@ __device__ __forceinline__ void wave_append(bool pred, unsigned long long key, u
     if (m == 0) return;
     const int leader = __ffsll((long long)m) - 1;
     const int cnt = __popcll(m);
-    long long base = 0;
-    if (lane_id() == leader) base = (long long)atomicAdd(counter, (unsigned long long)cnt);
-    base = __shfl(base, leader, 64);
+    unsigned long long b = 0;
+    if (lane_id() == leader) b = atomicAdd(counter, (unsigned long long)cnt);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, leader);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), leader);
+    const long long base = (long long)(((unsigned long long)hi << 32) | lo);
     const int off = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
     if (pred && base + off < cap) list[base + off] = key;
 }
@@ -434,11 +436,10 @@ __device__ __forceinline__ int decide32(const float* dx, const float* dy, float 
 
 // ---------------------------------------------------------------- tiles
 
-// A tile of TX x TY cells with its one-node halo of (TX+1) x (TY+1) nodes.
+// A tile of TX x TY cells.
 template <int TX_, int TY_>
 struct TileShape {
     static constexpr int TX = TX_, TY = TY_;
-    static constexpr int TNX = TX + 1, TNY = TY + 1;
     static_assert(TX * TY % 256 == 0, "a tile is a whole number of cells per wave step");
 };
 
@@ -540,87 +541,22 @@ __device__ __forceinline__ void tile_range_rec(const V* __restrict__ rec, int nb
         for (int u = 0; u <= BX; u++) {
             const bool in = bx + u < nbx && by + v < nby;
             const bool right = u == BX, above = v == BY;
-            const V* q = rec + ((size_t)(in ? by + v : by) * nbx + (in ? bx + u : bx)) * kRec;
-            // own blocks: values 0..3; above: 4..7; right: 8..11; diagonal: the node (12, 13)
+            // own blocks: values 0..3; above: 4..7; right: 8..11; diagonal: the node (12, 13);
+            // one aligned load each (records are kRec values, the buffer is 256-byte aligned)
             const int o = !in ? 0 : right ? (above ? 12 : 8) : above ? 4 : 0;
             const bool node = right && above && in;
-            const V a0 = q[o], a1 = q[o + (node ? 0 : 1)], a2 = q[o + (node ? 1 : 2)], a3 = q[o + (node ? 1 : 3)];
-            mnx = fmin(mnx, a0);
-            mxx = fmax(mxx, a1);
-            mny = fmin(mny, a2);
-            mxy = fmax(mxy, a3);
+            typedef V V4 __attribute__((ext_vector_type(4)));
+            const V4 q = *(const V4*)(rec + ((size_t)(in ? by + v : by) * nbx + (in ? bx + u : bx)) * kRec + o);
+            mnx = fmin(mnx, q.x);
+            mxx = fmax(mxx, node ? q.x : q.y);
+            mny = fmin(mny, node ? q.y : q.z);
+            mxy = fmax(mxy, node ? q.y : q.w);
         }
     }
     rng[0] = mnx;
     rng[1] = mxx;
     rng[2] = mny;
     rng[3] = mxy;
-}
-
-// Loads tile T's nodes (with the halo) into a wave-private LDS tile.
-template <class S, typename V>
-__device__ __forceinline__ void stage_tile_wave(const V* __restrict__ ax, const V* __restrict__ ay, const GridDesc& g,
-                                                const Tile& T, V (*sx)[S::TNX], V (*sy)[S::TNX])
-{
-    const int lane = lane_id();
-    constexpr int N = S::TNX * S::TNY;
-#pragma unroll
-    for (int k = 0; k < (N + 63) / 64; k++) {
-        const int q = lane + 64 * k;
-        const int li = q % S::TNX, lj = q / S::TNX;
-        if (q < N && li <= T.ncx && lj <= T.ncy) {
-            const size_t n = (size_t)(T.cj0 + lj) * g.nx + (T.ci0 + li);
-            sx[lj][li] = ax[n];
-            sy[lj][li] = ay[n];
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// A tile's nodes (with the halo) held in registers, lane-strided as
-// stage_tile_wave places them: fetched while the wave still works on the
-// previous tile, then written to the wave's LDS tile.
-template <class S, typename V>
-struct TileRegs {
-    static constexpr int N = S::TNX * S::TNY, K = (N + 63) / 64;
-    V x[K], y[K];
-};
-
-template <class S, typename V>
-__device__ __forceinline__ void fetch_tile_regs(const V* __restrict__ ax, const V* __restrict__ ay,
-                                                const GridDesc& g, const Tile& T, TileRegs<S, V>& t)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int k = 0; k < TileRegs<S, V>::K; k++) {
-        const int q = lane + 64 * k;
-        const int li = q % S::TNX, lj = q / S::TNX;
-        const bool in = q < TileRegs<S, V>::N && li <= T.ncx && lj <= T.ncy;
-        const size_t n = in ? (size_t)(T.cj0 + lj) * g.nx + (T.ci0 + li) : 0;
-        t.x[k] = ax[n];
-        t.y[k] = ay[n];
-    }
-}
-
-template <class S, typename V>
-__device__ __forceinline__ void store_tile_regs(const TileRegs<S, V>& t, const Tile& T, V (*sx)[S::TNX],
-                                                V (*sy)[S::TNX])
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int k = 0; k < TileRegs<S, V>::K; k++) {
-        const int q = lane + 64 * k;
-        const int li = q % S::TNX, lj = q / S::TNX;
-        if (q < TileRegs<S, V>::N && li <= T.ncx && lj <= T.ncy) {
-            sx[lj][li] = t.x[k];
-            sy[lj][li] = t.y[k];
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Sums a wave-uniform count a and a per-lane count b over the workgroup and
@@ -657,113 +593,102 @@ __device__ __forceinline__ bool tile_box_contains(const GridDesc& g, const Tile&
            by <= ty1 - r * rng[2] + eb;
 }
 
-// All triangles of a staged FP32 tile against one system (mixed path): the
-// certified FP32 decision for each, hits and undecided tests appended with
-// one atomic per wave.  fr = {r, E_B, bx_hi, bx_lo, by_hi, by_lo} as float;
-// an appended key is (hit_base | triangle id) or (flag_base | triangle id).
-// NT threads share the tile, a multiple of its width, so a thread keeps its
-// column in every pass; the passes' results are kept as bits and the appends
-// run only when some thread of the wave has a hit or an undecided test.
-template <class S, int NT = 256>
-__device__ __forceinline__ void tri32_system(const GridDesc& g, const Tile& T, const float (*sx)[S::TNX],
-                                             const float (*sy)[S::TNX], const float* fr,
-                                             unsigned long long hit_base, unsigned long long flag_base, int mode,
-                                             float tau, unsigned long long* hit_counter,
-                                             unsigned long long* hit_keys, long long hit_cap,
-                                             unsigned long long* flag_counter, unsigned long long* flag_keys,
-                                             long long flag_cap, unsigned& nbbox, int tix = threadIdx.x)
+// A system's values as the containment tests read them.
+struct SysVals {
+    double r, bx, by;             // FP64 path
+    float r32, e, bxh, bxl, byh, byl;  // mixed path: FP32 bound, split barycentre in node units
+};
+
+template <typename V>
+__device__ __forceinline__ SysVals sys_vals(const double* __restrict__ row)
 {
-    constexpr int IT = S::TX * S::TY / NT;  // cells per thread
-    static_assert(NT % S::TX == 0 && IT * 4 <= 64, "column per thread; 4 result bits per cell");
-    const float r = fr[0], E = fr[1], bxh = fr[2], bxl = fr[3], byh = fr[4], byl = fr[5];
-    const float h32 = (float)g.h;
-    const int li = tix % S::TX, lj0 = tix / S::TX;
-    const int gi = T.ci0 + li;
-    // offsets theta - barycentre in node units (exact hi part), then arcsec
-    const float ex0 = (((float)gi - bxh) - bxl) * h32;
-    const float ex1 = (((float)(gi + 1) - bxh) - bxl) * h32;
-    unsigned long long bits = 0;
-#pragma unroll 1
-    for (int it = 0; it < IT; it++) {
-        const int lj = lj0 + (NT / S::TX) * it;
-        const int gj = T.cj0 + lj;
-        const float ey0 = (((float)gj - byh) - byl) * h32;
-        const float ey1 = (((float)(gj + 1) - byh) - byl) * h32;
-        const float d00x = fmaf(-r, sx[lj][li], ex0), d00y = fmaf(-r, sy[lj][li], ey0);
-        const float d10x = fmaf(-r, sx[lj][li + 1], ex1), d10y = fmaf(-r, sy[lj][li + 1], ey0);
-        const float d01x = fmaf(-r, sx[lj + 1][li], ex0), d01y = fmaf(-r, sy[lj + 1][li], ey1);
-        const float d11x = fmaf(-r, sx[lj + 1][li + 1], ex1), d11y = fmaf(-r, sy[lj + 1][li + 1], ey1);
-        if (li < T.ncx && lj < T.ncy) {
-            const float tx[3] = {d00x, d10x, d01x}, ty[3] = {d00y, d10y, d01y};
-            const float ux[3] = {d11x, d01x, d10x}, uy[3] = {d11y, d01y, d10y};
-            const int res0 = decide32(tx, ty, E, mode, tau, nbbox);
-            const int res1 = decide32(ux, uy, E, mode, tau, nbbox);
-            bits |= (unsigned long long)(res0 | (res1 << 2)) << (4 * it);
-        }
+    SysVals v = {};
+    if constexpr (sizeof(V) == 4) {
+        v.r32 = (float)row[SYS_R];
+        v.e = (float)row[SYS_EB];
+        v.bxh = (float)row[SYS_BXH];
+        v.bxl = (float)row[SYS_BXL];
+        v.byh = (float)row[SYS_BYH];
+        v.byl = (float)row[SYS_BYL];
+    } else {
+        v.r = row[SYS_R];
+        v.bx = row[SYS_BX];
+        v.by = row[SYS_BY];
     }
-    if (__ballot(bits != 0) == 0) return;  // the common case: no hit, nothing undecided
-#pragma unroll 1
-    for (int it = 0; it < IT; it++) {
-        const unsigned rb = (unsigned)(bits >> (4 * it)) & 15u;
-        const int gj = T.cj0 + lj0 + (NT / S::TX) * it;
-        const unsigned tid0 = (unsigned)(2 * (gj * (g.nx - 1) + gi));
-        wave_append((rb & 3u) == kHit, hit_base | tid0, hit_counter, hit_keys, hit_cap);
-        wave_append((rb >> 2) == kHit, hit_base | (tid0 + 1), hit_counter, hit_keys, hit_cap);
-        wave_append((rb & 3u) == kFlag, flag_base | tid0, flag_counter, flag_keys, flag_cap);
-        wave_append((rb >> 2) == kFlag, flag_base | (tid0 + 1), flag_counter, flag_keys, flag_cap);
-    }
+    return v;
 }
 
-// All triangles of a staged FP64 tile against one system (FP64 path): exact
-// bounding box, then exact orientation signs; hits kept as bits and appended
-// only when some thread of the wave has one (as tri32_system).
-template <class S, int NT = 256>
-__device__ __forceinline__ void tri64_system(const GridDesc& g, const Tile& T, const double (*sx)[S::TNX],
-                                             const double (*sy)[S::TNX], double r, double bx, double by,
-                                             unsigned long long hit_base, unsigned long long* hit_counter,
-                                             unsigned long long* hit_keys, long long hit_cap, unsigned& nbbox,
-                                             int tix = threadIdx.x)
+// Both triangles of cell (gi, gj) against one system; a = alpha_x then alpha_y
+// at nodes 00, 10, 01, 11.  Mixed path: FP32 vertex offsets and the certified
+// sign test; FP64 path: exact containment on the FP64 field's vertices.  Returns
+// triangle 0's result in bits 0-1 and triangle 1's in bits 2-3.
+__device__ __forceinline__ unsigned test_cell(const GridDesc& g, int gi, int gj, const float* a, const SysVals& y,
+                                              int mode, float tau, unsigned& nbbox)
 {
-    constexpr int IT = S::TX * S::TY / NT;
-    static_assert(NT % S::TX == 0 && IT * 2 <= 64, "column per thread; 2 result bits per cell");
-    const int li = tix % S::TX, lj0 = tix / S::TX;
-    const int gi = T.ci0 + li;
+    // offsets theta - barycentre in node units (exact hi part), then arcsec
+    const float h32 = (float)g.h;
+    const float ex0 = (((float)gi - y.bxh) - y.bxl) * h32;
+    const float ex1 = (((float)(gi + 1) - y.bxh) - y.bxl) * h32;
+    const float ey0 = (((float)gj - y.byh) - y.byl) * h32;
+    const float ey1 = (((float)(gj + 1) - y.byh) - y.byl) * h32;
+    const float r = y.r32;
+    const float d00x = fmaf(-r, a[0], ex0), d00y = fmaf(-r, a[4], ey0);
+    const float d10x = fmaf(-r, a[1], ex1), d10y = fmaf(-r, a[5], ey0);
+    const float d01x = fmaf(-r, a[2], ex0), d01y = fmaf(-r, a[6], ey1);
+    const float d11x = fmaf(-r, a[3], ex1), d11y = fmaf(-r, a[7], ey1);
+    // most cells' boxes exclude the barycentre, and with them both triangles'
+    // (decide32 then returns a miss and counts nothing; mode 1 tests unwidened)
+    const float e = mode == 1 ? 0.0f : y.e;
+    const float xl = fminf(fminf(d00x, d10x), fminf(d01x, d11x)), xh = fmaxf(fmaxf(d00x, d10x), fmaxf(d01x, d11x));
+    const float yl = fminf(fminf(d00y, d10y), fminf(d01y, d11y)), yh = fmaxf(fmaxf(d00y, d10y), fmaxf(d01y, d11y));
+    if (xl > e || xh < -e || yl > e || yh < -e) return 0;
+    const float tx[3] = {d00x, d10x, d01x}, ty[3] = {d00y, d10y, d01y};
+    const float ux[3] = {d11x, d01x, d10x}, uy[3] = {d11y, d01y, d10y};
+    const int r0 = decide32(tx, ty, y.e, mode, tau, nbbox);
+    const int r1 = decide32(ux, uy, y.e, mode, tau, nbbox);
+    return (unsigned)(r0 | (r1 << 2));
+}
+
+__device__ __forceinline__ unsigned test_cell(const GridDesc& g, int gi, int gj, const double* a, const SysVals& y,
+                                              int, float, unsigned& nbbox)
+{
+    const double r = y.r, bx = y.bx, by = y.by;
     const double t0x = node_coord(g.x0, gi, g.h), t1x = node_coord(g.x0, gi + 1, g.h);
-    unsigned long long bits = 0;
-#pragma unroll 1
-    for (int it = 0; it < IT; it++) {
-        const int lj = lj0 + (NT / S::TX) * it;
-        const int gj = T.cj0 + lj;
-        if (li < T.ncx && lj < T.ncy) {
-            const double t0y = node_coord(g.y0, gj, g.h), t1y = node_coord(g.y0, gj + 1, g.h);
-            const double b00x = src_map(t0x, r, sx[lj][li]), b00y = src_map(t0y, r, sy[lj][li]);
-            const double b10x = src_map(t1x, r, sx[lj][li + 1]), b10y = src_map(t0y, r, sy[lj][li + 1]);
-            const double b01x = src_map(t0x, r, sx[lj + 1][li]), b01y = src_map(t1y, r, sy[lj + 1][li]);
-            const double b11x = src_map(t1x, r, sx[lj + 1][li + 1]), b11y = src_map(t1y, r, sy[lj + 1][li + 1]);
-            const double vx0[3] = {b00x, b10x, b01x}, vy0[3] = {b00y, b10y, b01y};
-            const double vx1[3] = {b11x, b01x, b10x}, vy1[3] = {b11y, b01y, b10y};
-            const double lo0 = fmin(vx0[0], fmin(vx0[1], vx0[2])), hi0 = fmax(vx0[0], fmax(vx0[1], vx0[2]));
-            const double lo1 = fmin(vy0[0], fmin(vy0[1], vy0[2])), hi1 = fmax(vy0[0], fmax(vy0[1], vy0[2]));
-            if (!(bx < lo0 || bx > hi0 || by < lo1 || by > hi1)) {
-                nbbox++;
-                if (contains_exact(vx0, vy0, bx, by)) bits |= 1ull << (2 * it);
-            }
-            const double lo2 = fmin(vx1[0], fmin(vx1[1], vx1[2])), hi2 = fmax(vx1[0], fmax(vx1[1], vx1[2]));
-            const double lo3 = fmin(vy1[0], fmin(vy1[1], vy1[2])), hi3 = fmax(vy1[0], fmax(vy1[1], vy1[2]));
-            if (!(bx < lo2 || bx > hi2 || by < lo3 || by > hi3)) {
-                nbbox++;
-                if (contains_exact(vx1, vy1, bx, by)) bits |= 2ull << (2 * it);
-            }
-        }
+    const double t0y = node_coord(g.y0, gj, g.h), t1y = node_coord(g.y0, gj + 1, g.h);
+    const double b00x = src_map(t0x, r, a[0]), b00y = src_map(t0y, r, a[4]);
+    const double b10x = src_map(t1x, r, a[1]), b10y = src_map(t0y, r, a[5]);
+    const double b01x = src_map(t0x, r, a[2]), b01y = src_map(t1y, r, a[6]);
+    const double b11x = src_map(t1x, r, a[3]), b11y = src_map(t1y, r, a[7]);
+    const double vx0[3] = {b00x, b10x, b01x}, vy0[3] = {b00y, b10y, b01y};
+    const double vx1[3] = {b11x, b01x, b10x}, vy1[3] = {b11y, b01y, b10y};
+    unsigned res = 0;
+    if (!(bx < fmin(vx0[0], fmin(vx0[1], vx0[2])) || bx > fmax(vx0[0], fmax(vx0[1], vx0[2])) ||
+          by < fmin(vy0[0], fmin(vy0[1], vy0[2])) || by > fmax(vy0[0], fmax(vy0[1], vy0[2])))) {
+        nbbox++;
+        if (contains_exact(vx0, vy0, bx, by)) res |= kHit;
     }
-    if (__ballot(bits != 0) == 0) return;
-#pragma unroll 1
-    for (int it = 0; it < IT; it++) {
-        const int gj = T.cj0 + lj0 + (NT / S::TX) * it;
-        const unsigned tid0 = (unsigned)(2 * (gj * (g.nx - 1) + gi));
-        wave_append(((bits >> (2 * it)) & 1ull) != 0, hit_base | tid0, hit_counter, hit_keys, hit_cap);
-        wave_append(((bits >> (2 * it)) & 2ull) != 0, hit_base | (tid0 + 1), hit_counter, hit_keys, hit_cap);
+    if (!(bx < fmin(vx1[0], fmin(vx1[1], vx1[2])) || bx > fmax(vx1[0], fmax(vx1[1], vx1[2])) ||
+          by < fmin(vy1[0], fmin(vy1[1], vy1[2])) || by > fmax(vy1[0], fmax(vy1[1], vy1[2])))) {
+        nbbox++;
+        if (contains_exact(vx1, vy1, bx, by)) res |= kHit << 2;
     }
+    return res;
+}
+
+// alpha at the four nodes of cell (gi, gj), as test_cell takes it.
+template <typename V>
+__device__ __forceinline__ void load_cell(const V* __restrict__ ax, const V* __restrict__ ay, const GridDesc& g,
+                                          int gi, int gj, V* a)
+{
+    const size_t n0 = (size_t)gj * g.nx + gi, n1 = n0 + g.nx;
+    a[0] = ax[n0];
+    a[1] = ax[n0 + 1];
+    a[2] = ax[n1];
+    a[3] = ax[n1 + 1];
+    a[4] = ay[n0];
+    a[5] = ay[n0 + 1];
+    a[6] = ay[n1];
+    a[7] = ay[n1 + 1];
 }
 
 // ---------------------------------------------------------------- FP64 vertices and positions
