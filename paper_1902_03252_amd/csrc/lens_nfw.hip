@@ -252,22 +252,23 @@ struct NfwProfile {
         s2 += r2;
     }
 
+    template <int NK>
     __device__ __forceinline__ void near32(int p, const float* fi, float fj, float* sx, float* sy) const
     {
         const float* c = t32 + (size_t)p * N32_STRIDE;
         const float A = c[N32_A], B = c[N32_B], irs2 = c[N32_IRS2], K = c[N32_K];
         const float nyv = (fj - c[N32_CYH]) - c[N32_CYL], bny = B * nyv, cny = c[N32_C] * nyv;
 #pragma unroll 1
-        for (int k = 0; k < 8; k += 4) {
+        for (int k = 0; k < NK; k += 4) {
 #pragma unroll
             for (int q = 0; q < 4; q++) {
-                const float nxv = ((k ? fi[4 + q] : fi[q]) - c[N32_CXH]) - c[N32_CXL];
+                const float nxv = ((k ? fi[NK - 4 + q] : fi[q]) - c[N32_CXH]) - c[N32_CXL];
                 const float m1 = fmaf(A, nxv, bny), m2 = fmaf(B, nxv, cny);
                 const float R2 = fmaf(nxv, m1, nyv * m2);
                 const float kg = R2 > 0.0f ? K * nfw_gx2(R2 * irs2) : 0.0f;
                 if (k) {
-                    sx[4 + q] = fmaf(kg, m1, sx[4 + q]);
-                    sy[4 + q] = fmaf(kg, m2, sy[4 + q]);
+                    sx[NK - 4 + q] = fmaf(kg, m1, sx[NK - 4 + q]);
+                    sy[NK - 4 + q] = fmaf(kg, m2, sy[NK - 4 + q]);
                 } else {
                     sx[q] = fmaf(kg, m1, sx[q]);
                     sy[q] = fmaf(kg, m2, sy[q]);

@@ -247,7 +247,7 @@ __device__ __forceinline__ void far_sum(const double* __restrict__ tab64, const 
     s2 += r2;
 }
 
-// Minimum / maximum over groups of 8 consecutive lanes (every lane gets it).
+// Minimum over groups of 8 consecutive lanes (every lane gets it).
 template <typename V>
 __device__ __forceinline__ V min8(V v)
 {
@@ -255,12 +255,53 @@ __device__ __forceinline__ V min8(V v)
     v = fmin(v, dpp_mov<0x4E>(v));   // lane ^ 2
     return fmin(v, dpp_mov<0x141>(v));  // the other half of the 8 lanes
 }
-template <typename V>
-__device__ __forceinline__ V max8(V v)
+
+// Exchanges x's odd rows of N lanes (N = 16, 32) with y's even ones.
+template <int N>
+__device__ __forceinline__ void row_swap(unsigned& x, unsigned& y)
 {
-    v = fmax(v, dpp_mov<0xB1>(v));
-    v = fmax(v, dpp_mov<0x4E>(v));
-    return fmax(v, dpp_mov<0x141>(v));
+    if constexpr (N == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    }
+}
+template <int N>
+__device__ __forceinline__ void row_swap(float& x, float& y)
+{
+    unsigned a = __float_as_uint(x), b = __float_as_uint(y);
+    row_swap<N>(a, b);
+    x = __uint_as_float(a);
+    y = __uint_as_float(b);
+}
+template <int N>
+__device__ __forceinline__ void row_swap(double& x, double& y)
+{
+    unsigned a = (unsigned)__double2loint(x), b = (unsigned)__double2loint(y);
+    unsigned c = (unsigned)__double2hiint(x), d = (unsigned)__double2hiint(y);
+    row_swap<N>(a, b);
+    row_swap<N>(c, d);
+    x = __hiloint2double((int)c, (int)a);
+    y = __hiloint2double((int)d, (int)b);
+}
+
+// A unit: the 32 x 2 NK nodes that a wave holds, NK = 8 or 4 per lane.  Lane l holds
+// row l % 16 (l % 8 for NK = 4) and value k column
+//   NK = 8: 16 (k / 4) + 4 (l / 16) + k % 4,   NK = 4: 16 (l / 8 % 2) + 4 (l / 16) + k.
+template <int NK>
+__device__ __forceinline__ int unit_row()
+{
+    return lane_id() & (2 * NK - 1);
+}
+template <int NK>
+__device__ __forceinline__ int unit_col(int k)
+{
+    const int lane = lane_id(), b = NK == 8 ? k >> 2 : (lane >> 3) & 1;
+    return 16 * b + 4 * (lane >> 4) + (k & 3);
 }
 
 // Range record of one block of 32 x 8 nodes (kRec values): the deflection
@@ -270,67 +311,86 @@ __device__ __forceinline__ V max8(V v)
 // the first columns of the blocks to their right, the first rows of the blocks
 // above and the first node of the block diagonally above (tile_range_rec).
 //
-// Writes the two records of a unit of 32 x 16 nodes held by one wave: lane l
-// holds row l % 16, columns 4 (l / 16) + r and 16 + 4 (l / 16) + r (v[r], v[4 + r]).
-// All 64 lanes call it.
-template <typename V>
+// Writes the records of a unit (two for NK = 8, one for NK = 4).  The maxima are
+// kept as minima of the negatives, and the four of a lane end in the four 16-lane
+// groups of one register (two row exchanges), so one butterfly serves all: group q
+// of 16 lanes holds min ax, min ay, -max ax, -max ay for q = 0 .. 3.  All 64 lanes
+// call it.
+template <int NK, typename V>
 __device__ __forceinline__ void write_records(const V* sx, const V* sy, int i0, int j0, int nx, int ny, int nbx,
                                               V* __restrict__ rec)
 {
-    const int lane = lane_id(), q = lane >> 4, row = lane & 15;
-    V a = V(INFINITY), b = V(-INFINITY), c = V(INFINITY), d = V(-INFINITY);
+    const int lane = lane_id(), q = lane >> 4, row = unit_row<NK>();
+    const V inf = V(INFINITY);
+    V a = inf, b = inf, c = inf, d = inf;
     const bool rin = j0 + row < ny;
+    if (i0 + 32 <= nx && j0 + 2 * NK <= ny) {  // the usual case: no node outside
+        a = sx[0];
+        b = sx[0];
+        c = sy[0];
+        d = sy[0];
 #pragma unroll
-    for (int k = 0; k < 8; k++) {
-        const int col = i0 + (k >> 2) * 16 + 4 * q + (k & 3);
-        if (rin && col < nx) {
+        for (int k = 1; k < NK; k++) {
             a = fmin(a, sx[k]);
             b = fmax(b, sx[k]);
             c = fmin(c, sy[k]);
             d = fmax(d, sy[k]);
         }
-    }
-    // first column: lanes 0..15 hold it as v[0]; the others bring nothing
-    const bool fc = q == 0 && rin;
-    const V fx0 = min8(fc ? sx[0] : V(INFINITY)), fx1 = max8(fc ? sx[0] : V(-INFINITY));
-    const V fy0 = min8(fc ? sy[0] : V(INFINITY)), fy1 = max8(fc ? sy[0] : V(-INFINITY));
+        b = -b;
+        d = -d;
+    } else {
 #pragma unroll
-    for (int m = 16; m <= 32; m <<= 1) {
-        a = fmin(a, __shfl_xor(a, m, 64));
-        b = fmax(b, __shfl_xor(b, m, 64));
-        c = fmin(c, __shfl_xor(c, m, 64));
-        d = fmax(d, __shfl_xor(d, m, 64));
+        for (int k = 0; k < NK; k++)
+            if (rin && i0 + unit_col<NK>(k) < nx) {
+                a = fmin(a, sx[k]);
+                b = fmin(b, -sx[k]);
+                c = fmin(c, sy[k]);
+                d = fmin(d, -sy[k]);
+            }
     }
-    // a..d: the row's range, in every lane of the row
-    const V A = min8(a), B = max8(b), C = min8(c), D = max8(d);
-    if ((lane & 7) == 0 && q == 0 && rin && i0 < nx) {
+    if constexpr (NK == 4) {  // the row's other block of 16 columns
+        a = fmin(a, dpp_mov<0x128>(a));  // lane ^ 8
+        b = fmin(b, dpp_mov<0x128>(b));
+        c = fmin(c, dpp_mov<0x128>(c));
+        d = fmin(d, dpp_mov<0x128>(d));
+    }
+    row_swap<32>(a, b);
+    row_swap<32>(c, d);
+    a = fmin(a, b);  // lanes 0..31: a, 32..63: b
+    c = fmin(c, d);
+    row_swap<16>(a, c);
+    const V r = fmin(a, c);  // the row's four values by q
+    // first column: group 0 holds it as s[0]
+    V x = sx[0], y = sy[0];
+    row_swap<16>(x, y);
+    V f = x;  // groups 0 and 1: ax and ay of the first column
+    y = x;
+    row_swap<32>(f, y);  // and groups 2 and 3
+    f = rin ? (q >= 2 ? -f : f) : inf;
+    if constexpr (NK == 4) f = (lane & 8) ? inf : f;
+    const V all = min8(r), col = min8(f);
+    if ((lane & 7) == 0 && (NK == 8 || (lane & 8) == 0) && rin && i0 < nx) {
         V* o = rec + ((size_t)((j0 + row) >> 3) * nbx + (i0 >> 5)) * kRec;
-        o[0] = A;
-        o[1] = B;
-        o[2] = C;
-        o[3] = D;
-        o[4] = a;
-        o[5] = b;
-        o[6] = c;
-        o[7] = d;
-        o[8] = fx0;
-        o[9] = fx1;
-        o[10] = fy0;
-        o[11] = fy1;
-        o[12] = sx[0];
-        o[13] = sy[0];
+        const int slot = 2 * (q & 1) + (q >> 1);
+        o[slot] = q >= 2 ? -all : all;
+        o[4 + slot] = q >= 2 ? -r : r;
+        o[8 + slot] = q >= 2 ? -col : col;
+        if (q == 0) {
+            o[12] = sx[0];
+            o[13] = sy[0];
+        }
     }
 }
 
-// Stores a wave's unit (layout of write_records) to the field planes.
-template <typename V>
+// Stores a wave's unit to a field plane.
+template <int NK, typename V>
 __device__ __forceinline__ void store_unit(const V* s, V* __restrict__ out, int i0, int j0, int nx, int ny, bool vec)
 {
-    const int lane = lane_id(), j = j0 + (lane & 15);
+    const int j = j0 + unit_row<NK>();
     if (j >= ny) return;
 #pragma unroll
-    for (int b = 0; b < 2; b++) {
-        const int i = i0 + 16 * b + 4 * (lane >> 4);
+    for (int b = 0; b < NK / 4; b++) {
+        const int i = i0 + unit_col<NK>(4 * b);
         V* o = out + (size_t)j * nx + i;
         if (vec && i + 3 < nx) {  // 16-byte stores: nx is a multiple of 16 / sizeof(V)
             constexpr int W = 16 / (int)sizeof(V);
@@ -374,14 +434,15 @@ struct IsoProfile {
         far_sum<FULL>(tab64, list, k0, k1, c1, c2, e1, e2, s1, s2);
     }
 
-    // Adds potential p at 8 nodes of one row (per lane): node-unit columns fi, row fj.
+    // Adds potential p at NK nodes of one row (per lane): node-unit columns fi, row fj.
+    template <int NK>
     __device__ __forceinline__ void near32(int p, const float* fi, float fj, float* sx, float* sy) const
     {
         const float* c = tab32 + (size_t)p * T32_STRIDE;
         const float nyv = (fj - c[T32_CYH]) - c[T32_CYL];
         const float4 rc =
             make_float4(c[T32_BP] * nyv, c[T32_CQ] * nyv, fmaf(c[T32_DQ] * nyv, nyv, c[T32_A2]), c[T32_RSK]);
-        field32_pot<8, 1>(c, &rc, fi, sx, sy);
+        field32_pot<NK, 1>(c, &rc, fi, sx, sy);
     }
     __device__ __forceinline__ void near64(int p, const double* t1, double t2, double* sx, double* sy) const
     {
@@ -446,7 +507,7 @@ struct Tile32 {
 //      then per node row the 8 coefficients in x (FP64, stored as FP32); the
 //      constant term is kept apart, so that what is interpolated is the
 //      variation over the tile and its rounding is relative to that;
-//   4. per unit of 32 x 16 nodes: interpolation in x as a matrix product
+//   4. per unit of 32 x 16 (T = 32: 32 x 8) nodes: interpolation in x as a matrix product
 //      (v_mfma_f32_16x16x4f32, x nodes by rows, inner index the coefficient),
 //      near potentials per node, the constant term last.
 template <int T, class P>
@@ -496,7 +557,7 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const P&
     {
         const int row = tid % T;
         double tb[8];
-        const double y = ((double)row - hw) / (double)hw;
+        const double y = ((double)row - hw) * (1.0 / (double)hw);
         tb[0] = 1.0;
         tb[1] = y;
 #pragma unroll
@@ -513,42 +574,69 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const P&
         }
     }
     __syncthreads();
-    constexpr int UX = T / 32, UNITS = UX * (T / 16);
+    // units of 32 x 16 nodes, or of 32 x 8 where the tile has only two of those for
+    // four waves
+    constexpr int NK = T == 32 ? 4 : 8;
+    constexpr int UX = T / 32, UNITS = UX * (T / (2 * NK));
     const int li = lane & 15, lk = lane >> 4;
     const bool vec = (g.nx & 3) == 0 && (((size_t)ax | (size_t)ay) & 15) == 0;
+    // (an invalid model's field is NaN)
+    const float cx = bad ? __builtin_nanf("") : L.c00[0], cy = bad ? __builtin_nanf("") : L.c00[1];
     for (int u = wt; u < UNITS; u += NW) {
-        const int cu = (u % UX) * 32, ru = (u / UX) * 16;
+        const int cu = (u % UX) * 32, ru = (u / UX) * 2 * NK;
         if (i0 + cu >= g.nx || j0 + ru >= g.ny) continue;
-        floatx4 acc[2][2];  // [component][column block]
+        float sx[NK], sy[NK], fi[NK];
+        if constexpr (NK == 8) {
+            floatx4 acc[2][2];  // [component][column block]
 #pragma unroll
-        for (int c = 0; c < 2; c++)
+            for (int c = 0; c < 2; c++)
+#pragma unroll
+                for (int b = 0; b < 2; b++) {
+                    acc[c][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int k = 1; k >= 0; k--)
+                        acc[c][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(L.cheb[4 * k + lk][cu + 16 * b + li],
+                                                                         L.g[8 * c + 4 * k + lk][ru + li], acc[c][b],
+                                                                         0, 0, 0);
+                }
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                sx[k] = acc[0][k >> 2][k & 3];
+                sy[k] = acc[1][k >> 2][k & 3];
+            }
+        } else {
+            // the product's 16 rows are 8 node rows of x, then of y: a lane gets one
+            // component of both column blocks and trades one with lane ^ 8
+            floatx4 acc[2];  // [column block]
 #pragma unroll
             for (int b = 0; b < 2; b++) {
-                acc[c][b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                acc[b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int k = 1; k >= 0; k--)
-                    acc[c][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(L.cheb[4 * k + lk][cu + 16 * b + li],
-                                                                     L.g[8 * c + 4 * k + lk][ru + li], acc[c][b], 0,
-                                                                     0, 0);
+                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(L.cheb[4 * k + lk][cu + 16 * b + li],
+                                                                  L.g[(li & 8) + 4 * k + lk][ru + (li & 7)], acc[b],
+                                                                  0, 0, 0);
             }
-        float sx[8], sy[8], fi[8];
+            const bool second = (li & 8) != 0;
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
-            sx[k] = acc[0][k >> 2][k & 3];
-            sy[k] = acc[1][k >> 2][k & 3];
-            fi[k] = (float)(i0 + cu + 16 * (k >> 2) + 4 * lk + (k & 3));
+            for (int k = 0; k < 4; k++) {
+                const float other = dpp_mov<0x128>(second ? acc[0][k] : acc[1][k]);
+                sx[k] = second ? other : acc[0][k];
+                sy[k] = second ? acc[1][k] : other;
+            }
         }
-        const float fj = (float)(j0 + ru + li);
-        for_list(L.lists.list, !all, nn, [&](int p) { prof.near32(p, fi, fj, sx, sy); });
-        const float cx = L.c00[0], cy = L.c00[1];
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
-            sx[k] = bad ? __builtin_nanf("") : sx[k] + cx;
-            sy[k] = bad ? __builtin_nanf("") : sy[k] + cy;
+        for (int k = 0; k < NK; k++) fi[k] = (float)(i0 + cu + unit_col<NK>(k));
+        const float fj = (float)(j0 + ru + unit_row<NK>());
+        for_list(L.lists.list, !all, nn, [&](int p) { prof.template near32<NK>(p, fi, fj, sx, sy); });
+#pragma unroll
+        for (int k = 0; k < NK; k++) {
+            sx[k] += cx;
+            sy[k] += cy;
         }
-        if (rec) write_records(sx, sy, i0 + cu, j0 + ru, g.nx, g.ny, nbx, rec);
-        store_unit(sx, ax, i0 + cu, j0 + ru, g.nx, g.ny, vec);
-        store_unit(sy, ay, i0 + cu, j0 + ru, g.nx, g.ny, vec);
+        if (rec) write_records<NK>(sx, sy, i0 + cu, j0 + ru, g.nx, g.ny, nbx, rec);
+        store_unit<NK>(sx, ax, i0 + cu, j0 + ru, g.nx, g.ny, vec);
+        store_unit<NK>(sy, ay, i0 + cu, j0 + ru, g.nx, g.ny, vec);
     }
 }
 
@@ -580,10 +668,10 @@ struct FieldSink64 {
         if (bad)
 #pragma unroll
             for (int k = 0; k < 8; k++) sx[k] = sy[k] = __builtin_nan("");
-        if (rec) write_records(sx, sy, i0, j0, nx, ny, (nx + 31) >> 5, rec);
+        if (rec) write_records<8>(sx, sy, i0, j0, nx, ny, (nx + 31) >> 5, rec);
         const bool vec = (nx & 1) == 0 && (((size_t)ax | (size_t)ay) & 15) == 0;
-        store_unit(sx, ax, i0, j0, nx, ny, vec);
-        store_unit(sy, ay, i0, j0, nx, ny, vec);
+        store_unit<8>(sx, ax, i0, j0, nx, ny, vec);
+        store_unit<8>(sy, ay, i0, j0, nx, ny, vec);
     }
 };
 
