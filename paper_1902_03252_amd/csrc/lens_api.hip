@@ -273,13 +273,13 @@ int head_buffers(lens_ctx* c, int np, const ObsPtrs& obs)
 }
 
 int head(lens_ctx* c, const lens_potentials* pot, const GridDesc& g, const ObsPtrs& obs, double* bx, double* by,
-         hipStream_t s)
+         int* status, hipStream_t s)
 {
     int rc;
     if ((rc = head_buffers(c, pot->n, obs))) return rc;
     if (launch_head(pot_ptrs(pot), g, obs, (double*)c->buf[B_TAB64], (float*)c->buf[B_TAB32],
                     (double*)c->buf[B_BTERM], bx, by, (double*)c->buf[B_SYS], (EvalState*)c->buf[B_STATE],
-                    s) != hipSuccess)
+                    status, s) != hipSuccess)
         return LENS_ERR_DEVICE;
     return LENS_OK;
 }
@@ -410,7 +410,7 @@ int lens_deflect(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* gri
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return LENS_ERR_DEVICE;
     const GridDesc g = grid_desc(grid);
-    int rc = head(ctx, pot, g, no_obs(), nullptr, nullptr, stream);
+    int rc = head(ctx, pot, g, no_obs(), nullptr, nullptr, status, stream);
     if (rc) return rc;
     const EvalState* st = (const EvalState*)ctx->buf[B_STATE];
     int slot;
@@ -433,8 +433,6 @@ int lens_deflect(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* gri
                            nullptr, 5, 1, ev, stream);
     if (e != hipSuccess) return LENS_ERR_DEVICE;
     timing_end(ctx, slot);
-    if (status && launch_export(nullptr, 0, st, nullptr, nullptr, status, stream) != hipSuccess)
-        return LENS_ERR_DEVICE;
     return LENS_OK;
 }
 
@@ -523,10 +521,9 @@ int lens_source_positions(lens_ctx* ctx, const lens_potentials* pot, const lens_
     g.h = 1.0;
     g.nx = 2;
     g.ny = 2;
-    int rc = head(ctx, pot, g, obs_ptrs(obs), beta_x, beta_y, stream);
+    int rc = head(ctx, pot, g, obs_ptrs(obs), beta_x, beta_y, status, stream);
     if (rc) return rc;
-    if (launch_export((const double*)ctx->buf[B_SYS], obs->n_sys, (const EvalState*)ctx->buf[B_STATE], bar_x,
-                      bar_y, status, stream) != hipSuccess)
+    if (launch_export((const double*)ctx->buf[B_SYS], obs->n_sys, bar_x, bar_y, stream) != hipSuccess)
         return LENS_ERR_DEVICE;
     return LENS_OK;
 }
@@ -651,7 +648,7 @@ int chi2_run(lens_ctx* ctx, const Chi2Plan& pl, const Chi2Bufs& b, const lens_po
     unsigned long long* flags = (unsigned long long*)b.p[CB_FLAGS];
     if (pl.fused) {
         if (launch_prep(pot_ptrs(pot), g, tab64, tab32, bterm, st, stream) != hipSuccess) return LENS_ERR_DEVICE;
-    } else if (launch_head(pot_ptrs(pot), g, o, tab64, tab32, bterm, bx, by, sysrow, st, stream) != hipSuccess) {
+    } else if (launch_head(pot_ptrs(pot), g, o, tab64, tab32, bterm, bx, by, sysrow, st, nullptr, stream) != hipSuccess) {
         return LENS_ERR_DEVICE;
     }
     int rc, slot = -1;

@@ -134,7 +134,8 @@ hipError_t launch_field32h(const float* tab32, int np, const GridDesc& g, float*
 hipError_t launch_field64h(const double* tab64, int np, const GridDesc& g, double* ax, double* ay, double* rr,
                            int tx_shift, int tiles_x, const HeadArgs& h, const KernelEvents* ev, hipStream_t s);
 hipError_t launch_head(const PotPtrs& pot, const GridDesc& g, const ObsPtrs& obs, double* tab64, float* tab32,
-                       double* bterm, double* bx, double* by, double* sysrow, EvalState* st, hipStream_t s);
+                       double* bterm, double* bx, double* by, double* sysrow, EvalState* st, int* status,
+                       hipStream_t s);
 hipError_t launch_field32(const float* tab32, int np, const GridDesc& g, float* ax, float* ay,
                           const EvalState* st, int npl, float* rr, int tx_shift, int tiles_x,
                           const KernelEvents* ev, hipStream_t s);
@@ -275,7 +276,6 @@ hipError_t launch_btail(const BatchPlan& bp, const ObsPtrs& obs, const BatchStat
 hipError_t launch_bstats(const unsigned long long* agg, long long n_tests, long long* stats, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s);
 hipError_t launch_dls(double zl, const double* zs, int n, double om, double ol, double* out, hipStream_t s);
-hipError_t launch_export(const double* sysrow, int nsys, const EvalState* st, double* bar_x, double* bar_y,
-                         int* status, hipStream_t s);
+hipError_t launch_export(const double* sysrow, int nsys, double* bar_x, double* bar_y, hipStream_t s);
 
 }  // namespace lens

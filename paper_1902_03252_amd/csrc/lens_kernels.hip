@@ -217,7 +217,8 @@ __device__ __forceinline__ void head_finish(HeadLds& L, int np, const GridDesc& 
 __global__ __launch_bounds__(256) void k_head(PotPtrs pot, GridDesc g, ObsPtrs obs, double* __restrict__ tab64,
                                               float* __restrict__ tab32, double* __restrict__ bterm,
                                               double* __restrict__ beta_x, double* __restrict__ beta_y,
-                                              double* __restrict__ sysrow, EvalState* __restrict__ st)
+                                              double* __restrict__ sysrow, EvalState* __restrict__ st,
+                                              int* __restrict__ status)
 {
     __shared__ int last;
     __shared__ HeadLds hl;
@@ -226,6 +227,9 @@ __global__ __launch_bounds__(256) void k_head(PotPtrs pot, GridDesc g, ObsPtrs o
     head_images<false>(pot, nullptr, obs, beta_x, beta_y, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4);
     if (!last_workgroup(&st->head_ticket, &last)) return;
     head_finish(hl, pot.n, g, obs, bterm, beta_x, beta_y, sysrow, st);
+    // the caller's status word, where one is asked for (a launch after the field
+    // for it alone cost 5 us of a small deflection's 47)
+    if (status && threadIdx.x == 0) *status = st->status;
 }
 
 // Constants of every potential only (the fused field kernels do the rest of
@@ -979,11 +983,10 @@ __global__ __launch_bounds__(256) void k_dls(double zl, const double* __restrict
 
 // ============================================================== exports
 
-__global__ void k_export(const double* __restrict__ sysrow, int nsys, const EvalState* __restrict__ st,
-                         double* __restrict__ bar_x, double* __restrict__ bar_y, int* __restrict__ status)
+__global__ void k_export(const double* __restrict__ sysrow, int nsys, double* __restrict__ bar_x,
+                         double* __restrict__ bar_y)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s == 0 && status) *status = st->status;
     if (s < nsys && bar_x) {
         bar_x[s] = sysrow[(size_t)s * SYS_STRIDE + SYS_BX];
         bar_y[s] = sysrow[(size_t)s * SYS_STRIDE + SYS_BY];
@@ -997,11 +1000,12 @@ static inline unsigned cdiv(long long a, long long b) { return (unsigned)((a + b
 static inline unsigned clampu(long long v, long long lo, long long hi) { return (unsigned)(v < lo ? lo : v > hi ? hi : v); }
 
 hipError_t launch_head(const PotPtrs& pot, const GridDesc& g, const ObsPtrs& obs, double* tab64, float* tab32,
-                       double* bterm, double* bx, double* by, double* sysrow, EvalState* st, hipStream_t s)
+                       double* bterm, double* bx, double* by, double* sysrow, EvalState* st, int* status,
+                       hipStream_t s)
 {
     long long nb = cdiv(obs.n_img, 4);
     if (nb < cdiv(pot.n, 256)) nb = cdiv(pot.n, 256);
-    k_head<<<clampu(nb, 1, 1024), 256, 0, s>>>(pot, g, obs, tab64, tab32, bterm, bx, by, sysrow, st);
+    k_head<<<clampu(nb, 1, 1024), 256, 0, s>>>(pot, g, obs, tab64, tab32, bterm, bx, by, sysrow, st, status);
     return hipGetLastError();
 }
 
@@ -1316,10 +1320,9 @@ hipError_t launch_dls(double zl, const double* zs, int n, double om, double ol, 
     return hipGetLastError();
 }
 
-hipError_t launch_export(const double* sysrow, int nsys, const EvalState* st, double* bar_x, double* bar_y,
-                         int* status, hipStream_t s)
+hipError_t launch_export(const double* sysrow, int nsys, double* bar_x, double* bar_y, hipStream_t s)
 {
-    k_export<<<cdiv(nsys > 0 ? nsys : 1, 256), 256, 0, s>>>(sysrow, nsys, st, bar_x, bar_y, status);
+    if (nsys > 0) k_export<<<cdiv(nsys, 256), 256, 0, s>>>(sysrow, nsys, bar_x, bar_y);
     return hipGetLastError();
 }
 
