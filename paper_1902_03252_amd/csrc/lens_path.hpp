@@ -636,12 +636,6 @@ __device__ __forceinline__ unsigned test_cell(const GridDesc& g, int gi, int gj,
     const float d10x = fmaf(-r, a[1], ex1), d10y = fmaf(-r, a[5], ey0);
     const float d01x = fmaf(-r, a[2], ex0), d01y = fmaf(-r, a[6], ey1);
     const float d11x = fmaf(-r, a[3], ex1), d11y = fmaf(-r, a[7], ey1);
-    // most cells' boxes exclude the barycentre, and with them both triangles'
-    // (decide32 then returns a miss and counts nothing; mode 1 tests unwidened)
-    const float e = mode == 1 ? 0.0f : y.e;
-    const float xl = fminf(fminf(d00x, d10x), fminf(d01x, d11x)), xh = fmaxf(fmaxf(d00x, d10x), fmaxf(d01x, d11x));
-    const float yl = fminf(fminf(d00y, d10y), fminf(d01y, d11y)), yh = fmaxf(fmaxf(d00y, d10y), fmaxf(d01y, d11y));
-    if (xl > e || xh < -e || yl > e || yh < -e) return 0;
     const float tx[3] = {d00x, d10x, d01x}, ty[3] = {d00y, d10y, d01y};
     const float ux[3] = {d11x, d01x, d10x}, uy[3] = {d11y, d01y, d10y};
     const int r0 = decide32(tx, ty, y.e, mode, tau, nbbox);
