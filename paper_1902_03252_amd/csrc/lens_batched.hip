@@ -21,17 +21,6 @@ namespace lens {
 
 static_assert(kBatchMax == kTailStage, "the batch tail stages one sample's hits in LDS");
 
-// Upper bound of the index k with off[k] <= v among off[0..n] (off[0] = 0).
-__device__ __forceinline__ int find_segment(const long long* __restrict__ off, int n, long long v)
-{
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (off[mid] <= v) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
 // ============================================================== head
 
 __global__ __launch_bounds__(256) void k_bhead(BatchPlan bp, PotPtrs pot, ObsPtrs obs, double* __restrict__ tab64,

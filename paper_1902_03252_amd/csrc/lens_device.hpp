@@ -87,18 +87,6 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-__device__ __forceinline__ float wave_max(float v)
-{
-    for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
-    return v;
-}
-
-__device__ __forceinline__ float wave_min(float v)
-{
-    for (int m = 32; m >= 1; m >>= 1) v = fminf(v, __shfl_xor(v, m, 64));
-    return v;
-}
-
 // FP64 coordinate of grid node i on one axis, x0 + i h, with the product and
 // the sum rounded separately (no fused multiply-add): every FP64 node
 // position of the library is formed this way, so that FP64 offsets

@@ -2,14 +2,15 @@
 //
 // One chi^2 evaluation (Rexroth et al. 2019, Sec. 2.2.1-2.2.2, Fig. 1):
 //   k_prep    per-potential constants (FP64 and FP32 tables), domain terms
-//   k_field*h deflection at every grid node (FP32 or FP64) and the per-tile
-//             deflection ranges; its first rows of workgroups run the head:
-//             observed images -> source plane in FP64, then (last of them)
-//             the barycentres, the FP32 error bound, one row per system and
-//             the counters                                       <- the time
-//   k_cull    one wave per tile of cells: the tile's deflection range bounds
-//             its source-plane vertices; every system whose barycentre the
-//             bound admits gives a (tile, system) pair
+//   k_tiled*  deflection at every grid node (FP32 or FP64) by tiles
+//             (lens_tiles.hpp), with the range records that the culling reads;
+//             its first workgroups run the head: observed images -> source
+//             plane in FP64, then (last of them) the barycentres, the FP32
+//             error bound, one row per system and the counters   <- the time
+//   k_field*h the same by a direct sum, for small problems (tiled_side)
+//   k_cull    lane = tile of cells: the tile's deflection range bounds its
+//             source-plane vertices; every system whose barycentre the bound
+//             admits gives a (tile, system) pair
 //   k_pairs   persistent waves over the pairs: triangle containment (FP32
 //             certified signs or FP64 exact); hits and undecided tests
 //             appended
@@ -40,7 +41,9 @@ namespace lens {
 //     (64 u w_p bounds the rounding of one potential's FP32 evaluation --
 //     about 30 u w_p by operation count, doubled -- (P-1) u W the sequential
 //     FP32 sum over potentials, sum_p j_p the Jacobian-amplified absolute
-//     offset error), and writes one row per system: barycentre (unweighted
+//     offset error; a far potential of a tiled field stays within the same
+//     64 u w_p: truncation 8.7, the estimates' 4 times the interpolation's norm
+//     5.3, the FP32 coefficients and their sums), and writes one row per system: barycentre (unweighted
 //     mean of its beta_ij), its node-unit split, D_LS/D_OS and the FP32 error
 //     bound of source-plane offsets
 //       E_B = r E_alpha + 4u Theta + 2u r (W + E_alpha) + 2^-25 h + 1e-9,

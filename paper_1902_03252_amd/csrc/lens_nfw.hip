@@ -218,7 +218,8 @@ __global__ __launch_bounds__(256) void k_nfw64(const double* __restrict__ t64, i
 
 // The NFW halos as a tile's summand (lens_tiles.hpp): the profile is analytic
 // away from the centre like the isothermal one (x = 1 is a removable point), so
-// the same criterion with core 0 holds.
+// the same criterion with core 0 holds.  The profile's logarithms and roots bound
+// it, by vector issue: 4096^2 x 702 in FP32 21.6 ms by the direct sum, 0.43 by tiles.
 struct NfwProfile {
     const double* t64;
     const float* t32;
@@ -277,12 +278,13 @@ struct NfwProfile {
         }
     }
 
+    template <int NK>
     __device__ __forceinline__ void near64(int p, const double* t1, double t2, double* sx, double* sy) const
     {
         const double* c = t64 + (size_t)p * N64_STRIDE;
         const double d2 = t2 - c[N64_YC];
 #pragma unroll
-        for (int k = 0; k < 8; k++) {
+        for (int k = 0; k < NK; k++) {
             const double d1 = t1[k] - c[N64_XC];
             const double m1 = c[N64_A] * d1 + c[N64_B] * d2, m2 = c[N64_B] * d1 + c[N64_C] * d2;
             const double R2 = d1 * m1 + d2 * m2;

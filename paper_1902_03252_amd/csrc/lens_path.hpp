@@ -384,11 +384,6 @@ __device__ __forceinline__ double bcast(double v, int l)
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-__device__ __forceinline__ unsigned long long hit_key(int s, int tid)
-{
-    return ((unsigned long long)(unsigned)s << 32) | (unsigned)tid;
-}
-
 // FP32 containment decision with a certified sign (mixed path).  d* are the
 // vertex offsets B_k - barycentre; each component is within E of the exact
 // FP64 value.  Returns kMiss / kHit when certain, kFlag otherwise.

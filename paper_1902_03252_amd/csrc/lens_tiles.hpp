@@ -444,23 +444,24 @@ struct IsoProfile {
             make_float4(c[T32_BP] * nyv, c[T32_CQ] * nyv, fmaf(c[T32_DQ] * nyv, nyv, c[T32_A2]), c[T32_RSK]);
         field32_pot<NK, 1>(c, &rc, fi, sx, sy);
     }
+    template <int NK>
     __device__ __forceinline__ void near64(int p, const double* t1, double t2, double* sx, double* sy) const
     {
         const Far64 c = load_far(tab64 + (size_t)p * T64_STRIDE);
         if (__double_as_longlong(c.rs) == 0)
-            near64_nodes<false>(c, t1, t2, sx, sy);
+            near64_nodes<NK, false>(c, t1, t2, sx, sy);
         else
-            near64_nodes<true>(c, t1, t2, sx, sy);
+            near64_nodes<NK, true>(c, t1, t2, sx, sy);
     }
-    // add_alpha64 at 8 nodes, the profile kind decided once, four nodes' chains
+    // add_alpha64 at NK nodes, the profile kind decided once, four nodes' chains
     // interleaved at a time (all eight would cost the occupancy its registers).
-    template <bool CUT>
+    template <int NK, bool CUT>
     __device__ __forceinline__ static void near64_nodes(const Far64& c, const double* t1, double t2, double* sx,
                                                         double* sy)
     {
         const double d2 = t2 - c.yc, bd2 = c.B * d2, cd2 = c.C * d2;
 #pragma unroll
-        for (int q = 0; q < 8; q += 4) {
+        for (int q = 0; q < NK; q += 4) {
 #pragma unroll
             for (int k = q; k < q + 4; k++) {
                 const double d1 = t1[k] - c.xc;
@@ -502,7 +503,7 @@ struct Tile32 {
 // The FP32 field of the tile at node (i0, j0) by a workgroup of 256 threads.
 //   1. lists (FP32 criterion, one potential per thread);
 //   2. far sum at the 8 x 8 Chebyshev points, lane = point, the waves sharing
-//      the far list, in FP64 with unrefined estimates (add_alpha_est);
+//      the far list, in FP64 with unrefined estimates (add_far<false>);
 //   3. Chebyshev coefficients (two 8-point transforms per component, FP64),
 //      then per node row the 8 coefficients in x (FP64, stored as FP32); the
 //      constant term is kept apart, so that what is interpolated is the
@@ -510,6 +511,11 @@ struct Tile32 {
 //   4. per unit of 32 x 16 (T = 32: 32 x 8) nodes: interpolation in x as a matrix product
 //      (v_mfma_f32_16x16x4f32, x nodes by rows, inner index the coefficient),
 //      near potentials per node, the constant term last.
+// Bound by vector issue (256 chains of 512^2 x 50, T = 32: vector instructions in
+// 76 % of the cycles, of them a third of the time FP64, the far sums) once there
+// are tiles enough, by one tile's chain before that.  Against the direct FP32 sum
+// (kernel times): 4096^2 x 200 1402 -> 90 us, 1024^2 x 50 34.3 -> 14.3, the
+// 96-sample batch 4800 -> 800, the 256 chains 1230 -> 537.
 template <int T, class P>
 __device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const P& prof, int np, const GridDesc& g,
                                             int i0, int j0, float* __restrict__ ax, float* __restrict__ ay,
@@ -645,7 +651,10 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const P&
 // The same in FP64 with 16 x 16 Chebyshev points (one per thread of the
 // workgroup) and v_mfma_f64_16x16x4f64.  The row coefficients (16 per row and
 // component) are formed by the lanes that feed them to the matrix product, once
-// per group of 16 rows, so they need no LDS.
+// per group of 16 rows, so they need no LDS.  Bound by FP64 issue (48 % of the
+// cycles at 1000 x 777 x 75, where 800 tiles leave a third of the CUs' time idle;
+// 62 % at 2047 x 1531 x 120).  Against the direct FP64 sum: 1000 x 777 x 75
+// 106 -> 51 us, the call of 2047 x 1531 x 120 484 -> 115 (90 in the kernel).
 template <int T>
 struct Tile64 {
     struct Lds {
@@ -655,23 +664,28 @@ struct Tile64 {
     };
 };
 
-// Where a tile's units of 32 x 16 nodes go: to the field planes, with the range
+// Where a tile's units go: to the field planes, with the range
 // records where asked for.
 struct FieldSink64 {
     double *ax, *ay, *rec;
     int nx, ny;
     bool bad;  // the whole field is NaN
 
-    __device__ __forceinline__ bool wants(int, int) const { return true; }  // wave-uniform
+    template <int NK>
+    __device__ __forceinline__ bool wants(int, int) const  // wave-uniform
+    {
+        return true;
+    }
+    template <int NK>
     __device__ __forceinline__ void put(double* sx, double* sy, int i0, int j0) const
     {
         if (bad)
 #pragma unroll
-            for (int k = 0; k < 8; k++) sx[k] = sy[k] = __builtin_nan("");
-        if (rec) write_records<8>(sx, sy, i0, j0, nx, ny, (nx + 31) >> 5, rec);
+            for (int k = 0; k < NK; k++) sx[k] = sy[k] = __builtin_nan("");
+        if (rec) write_records<NK>(sx, sy, i0, j0, nx, ny, (nx + 31) >> 5, rec);
         const bool vec = (nx & 1) == 0 && (((size_t)ax | (size_t)ay) & 15) == 0;
-        store_unit<8>(sx, ax, i0, j0, nx, ny, vec);
-        store_unit<8>(sy, ay, i0, j0, nx, ny, vec);
+        store_unit<NK>(sx, ax, i0, j0, nx, ny, vec);
+        store_unit<NK>(sy, ay, i0, j0, nx, ny, vec);
     }
 };
 
@@ -740,10 +754,13 @@ __device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P&
     // output value r of lane l of the matrix product is row l / 16 + 4 r: the x
     // nodes are assigned so that a lane holds four consecutive ones
     const int xi = 4 * (li & 3) + (li >> 2);
-    for (int ru = 16 * wt; ru < T; ru += 64) {
+    constexpr int NK = T == 32 ? 4 : 8, RU = 2 * NK;  // units of 32 x RU nodes, as Tile32
+    constexpr int NC = NK == 8 ? 2 : 1;  // components per lane of the product (NK = 4: one, by li / 8)
+    const int row = unit_row<NK>();
+    for (int ru = RU * wt; ru < T; ru += 4 * RU) {
         if (j0 + ru >= g.ny) break;
-        const double t2 = node_coord(g.y0, j0 + ru + li, g.h);
-        double B[2][4];  // coefficient 4 s + lk of row ru + li
+        const double t2 = node_coord(g.y0, j0 + ru + row, g.h);
+        double B[NC][4];  // coefficient 4 s + lk of row ru + row
         {
             const double y = (t2 - c2) * ihalf;
             double tb[16];
@@ -752,43 +769,58 @@ __device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P&
 #pragma unroll
             for (int b = 2; b < 16; b++) tb[b] = fma(2.0 * y, tb[b - 1], -tb[b - 2]);
 #pragma unroll
-            for (int c = 0; c < 2; c++)
+            for (int c = 0; c < NC; c++) {
+                const double* f = L.f[NK == 8 ? c : li >> 3];
 #pragma unroll
                 for (int s = 0; s < 4; s++) {
                     double v = 0.0;
 #pragma unroll
-                    for (int b = 15; b >= 0; b--) v = fma(L.f[c][16 * b + 4 * s + lk], tb[b], v);
+                    for (int b = 15; b >= 0; b--) v = fma(f[16 * b + 4 * s + lk], tb[b], v);
                     B[c][s] = v;
                 }
+            }
         }
         for (int cu = 0; cu < T; cu += 32) {
             if (i0 + cu >= g.nx) break;
-            if (!sink.wants(i0 + cu, j0 + ru)) continue;
-            doublex4 acc[2][2];
+            if (!sink.template wants<NK>(i0 + cu, j0 + ru)) continue;
+            doublex4 acc[NC][2];
 #pragma unroll
             for (int b = 0; b < 2; b++) {
-                acc[0][b] = acc[1][b] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int c = 0; c < NC; c++) acc[c][b] = doublex4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                 for (int s = 3; s >= 0; s--) {
                     const double A = L.cheb[4 * s + lk][cu + 16 * b + xi];
-                    acc[0][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(A, B[0][s], acc[0][b], 0, 0, 0);
-                    acc[1][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(A, B[1][s], acc[1][b], 0, 0, 0);
+#pragma unroll
+                    for (int c = 0; c < NC; c++)
+                        acc[c][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(A, B[c][s], acc[c][b], 0, 0, 0);
                 }
             }
-            double sx[8], sy[8], t1[8];
+            double sx[NK], sy[NK], t1[NK];
+            if constexpr (NK == 8) {
 #pragma unroll
-            for (int k = 0; k < 8; k++) {
-                sx[k] = acc[0][k >> 2][k & 3];
-                sy[k] = acc[1][k >> 2][k & 3];
-                t1[k] = node_coord(g.x0, i0 + cu + 16 * (k >> 2) + 4 * lk + (k & 3), g.h);
+                for (int k = 0; k < 8; k++) {
+                    sx[k] = acc[0][k >> 2][k & 3];
+                    sy[k] = acc[1][k >> 2][k & 3];
+                }
+            } else {
+                const bool second = (li & 8) != 0;
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const double other = dpp_mov<0x128>(second ? acc[0][0][k] : acc[0][1][k]);
+                    sx[k] = second ? other : acc[0][0][k];
+                    sy[k] = second ? acc[0][1][k] : other;
+                }
             }
-            for_list(L.lists.list, !all, nn, [&](int p) { prof.near64(p, t1, t2, sx, sy); });
 #pragma unroll
-            for (int k = 0; k < 8; k++) {
+            for (int k = 0; k < NK; k++) t1[k] = node_coord(g.x0, i0 + cu + unit_col<NK>(k), g.h);
+            for_list(L.lists.list, !all, nn, [&](int p) { prof.template near64<NK>(p, t1, t2, sx, sy); });
+#pragma unroll
+            for (int k = 0; k < NK; k++) {
                 sx[k] += r0;
                 sy[k] += r1;
             }
-            sink.put(sx, sy, i0 + cu, j0 + ru);
+            sink.template put<NK>(sx, sy, i0 + cu, j0 + ru);
         }
     }
 }
