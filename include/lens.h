@@ -329,7 +329,9 @@ int lens_mh_step_batched(lens_ctx *ctx, double *states, int32_t n_chains, int32_
  * max(nx, ny)), ceil(log2 of the potential count P)); for a batch the side is
  * the largest over the samples and P the rounded-up mean.  A call whose
  * opts->tile or opts->field_npl is 0 takes the table's choice for its bucket
- * when there is one, else the fixed default.  lens_create merges the JSON file
+ * when there is one, else the fixed default (field_npl acts on the direct field
+ * only: where the field is evaluated by tiles, as in every batch, its candidates
+ * run the same kernel).  lens_create merges the JSON file
  * named by the environment variable LENS_AUTOTUNE_CACHE, if it exists and
  * parses (otherwise the table starts empty).  Entries carry the GPU
  * architecture (e.g. gfx950); a file written on another one adds nothing. */

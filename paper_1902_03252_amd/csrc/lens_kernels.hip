@@ -398,13 +398,14 @@ __global__ __launch_bounds__(256) void k_field64h(const double* __restrict__ tab
 
 // ============================================================== tiled field
 
-// One workgroup per tile, in row-major order; the first head_blocks workgroups
-// run the head (as k_field32h's).
+// One workgroup per tile (tile_at); the first head_blocks workgroups run the head
+// (as k_field32h's).  The bound of four waves keeps the matrix products' results out
+// of the accumulation registers: 79 registers and six waves, not 95 and five.
 template <int T>
-__global__ __launch_bounds__(256) void k_tiled32(const double* __restrict__ tab64, const float* __restrict__ tab32,
-                                                 int np, GridDesc g, int ntx, float* __restrict__ ax,
-                                                 float* __restrict__ ay, const EvalState* __restrict__ st,
-                                                 float* __restrict__ rec, int nbx, HeadArgs h, int head_blocks)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_tiled32(
+    const double* __restrict__ tab64, const float* __restrict__ tab32, int np, GridDesc g, int ntx,
+    float* __restrict__ ax, float* __restrict__ ay, const EvalState* __restrict__ st, float* __restrict__ rec, int nbx,
+    HeadArgs h, int head_blocks)
 {
     using Lds = typename Tile32<T>::Lds;
     __shared__ FusedLds<fused_lds_bytes((int)sizeof(Lds))> lds;
@@ -412,7 +413,8 @@ __global__ __launch_bounds__(256) void k_tiled32(const double* __restrict__ tab6
         fused_head(*reinterpret_cast<HeadLds*>(lds.raw), h, blockIdx.x, head_blocks);
         return;
     }
-    const int tile = blockIdx.x - head_blocks, tj = tile / ntx, ti = tile - tj * ntx;
+    int ti, tj;
+    tile_at((int)blockIdx.x - head_blocks, ntx, ti, tj);
     const bool bad = st != nullptr && st->status != kStatusOk;
     tile32_body<T>(*reinterpret_cast<Lds*>(lds.raw), IsoProfile{tab64, tab32}, np, g, ti * T, tj * T, ax, ay, bad,
                    rec, nbx);
@@ -430,7 +432,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         fused_head(*reinterpret_cast<HeadLds*>(lds.raw), h, blockIdx.x, head_blocks);
         return;
     }
-    const int tile = blockIdx.x - head_blocks, tj = tile / ntx, ti = tile - tj * ntx;
+    int ti, tj;
+    tile_at((int)blockIdx.x - head_blocks, ntx, ti, tj);
     const bool bad = st != nullptr && st->status != kStatusOk;
     tile64_body<T>(*reinterpret_cast<Lds*>(lds.raw), IsoProfile{tab64, tab32}, np, g, ti * T, tj * T,
                    FieldSink64{ax, ay, rec, g.nx, g.ny, bad});

@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256) void k_nfw64(const double* __restrict__ t64, i
 // The NFW halos as a tile's summand (lens_tiles.hpp): the profile is analytic
 // away from the centre like the isothermal one (x = 1 is a removable point), so
 // the same criterion with core 0 holds.  The profile's logarithms and roots bound
-// it, by vector issue: 4096^2 x 702 in FP32 21.6 ms by the direct sum, 0.43 by tiles.
+// it, by vector issue: 4096^2 x 702 in FP32 21.6 ms by the direct sum, 0.35 by tiles.
 struct NfwProfile {
     const double* t64;
     const float* t32;
@@ -295,14 +295,15 @@ struct NfwProfile {
     }
 };
 
-template <int T>
-__global__ __launch_bounds__(256) void k_nfw_tiled32(const double* __restrict__ t64, const float* __restrict__ t32,
+template <int T, int NW>
+__global__ __launch_bounds__(64 * NW) void k_nfw_tiled32(const double* __restrict__ t64, const float* __restrict__ t32,
                                                      int np, GridDesc g, int ntx, float* __restrict__ ax,
                                                      float* __restrict__ ay, const int* __restrict__ st)
 {
-    __shared__ typename Tile32<T>::Lds lds;
-    const int tj = blockIdx.x / ntx, ti = blockIdx.x - tj * ntx;
-    tile32_body<T>(lds, NfwProfile{t64, t32}, np, g, ti * T, tj * T, ax, ay, *st != kStatusOk, (float*)nullptr, 0);
+    __shared__ typename Tile32<T, NW>::Lds lds;
+    int ti, tj;
+    tile_at((int)blockIdx.x, ntx, ti, tj);
+    tile32_body<T, NW>(lds, NfwProfile{t64, t32}, np, g, ti * T, tj * T, ax, ay, *st != kStatusOk, (float*)nullptr, 0);
 }
 
 template <int T>
@@ -311,7 +312,8 @@ __global__ __launch_bounds__(256) void k_nfw_tiled64(const double* __restrict__ 
                                                      double* __restrict__ ay, const int* __restrict__ st)
 {
     __shared__ typename Tile64<T>::Lds lds;
-    const int tj = blockIdx.x / ntx, ti = blockIdx.x - tj * ntx;
+    int ti, tj;
+    tile_at((int)blockIdx.x, ntx, ti, tj);
     tile64_body<T>(lds, NfwProfile{t64, t32}, np, g, ti * T, tj * T,
                    FieldSink64{ax, ay, nullptr, g.nx, g.ny, *st != kStatusOk});
 }
@@ -344,8 +346,11 @@ hipError_t launch_nfw(const NfwPtrs& h, const GridDesc& g, bool fp32, void* ax, 
         const dim3 grid((unsigned)(ntx * ((g.ny + side - 1) / side)));
         auto go = [&](auto t) {
             constexpr int T = decltype(t)::value;
+            // eight waves for the largest tile: its chain bounds a launch of few such tiles
+            // (4096^2 x 702: 425 us with four)
+            constexpr int NW = T == 128 ? 8 : 4;
             if (fp32)
-                return launch_ev(ev, k_nfw_tiled32<T>, grid, dim3(256), s, (const double*)t64, (const float*)t32, h.n, g,
+                return launch_ev(ev, k_nfw_tiled32<T, NW>, grid, dim3(64 * NW), s, (const double*)t64, (const float*)t32, h.n, g,
                                  ntx, (float*)ax, (float*)ay, (const int*)st);
             return launch_ev(ev, k_nfw_tiled64<T>, grid, dim3(256), s, (const double*)t64, (const float*)t32, h.n, g, ntx,
                              (double*)ax, (double*)ay, (const int*)st);

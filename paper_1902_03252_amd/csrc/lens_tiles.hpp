@@ -105,7 +105,7 @@ __device__ __forceinline__ bool tile_far(float dx, float dy, float A, float B, f
 }
 
 // Near/far lists of one tile: near potentials first (in order), then the far
-// ones (in order).  Called by all 256 threads of the workgroup (two
+// ones (in order).  Called by all NTH threads of the workgroup (two
 // barriers); isfar(p) is evaluated once per potential.
 struct TileLists {
     unsigned long long near[kTileMaxP / 64];
@@ -113,10 +113,9 @@ struct TileLists {
     int n_near;
 };
 
-template <class F>
+template <int NTH = 256, class F>
 __device__ __forceinline__ void tile_lists(TileLists& L, int np, F&& isfar)
 {
-    constexpr int NTH = 256;
     const int tid = threadIdx.x;
     const int words = (np + 63) >> 6;
     for (int p0 = 0; p0 < np; p0 += NTH) {  // uniform trip count
@@ -486,10 +485,9 @@ struct IsoProfile {
 
 // ---------------------------------------------------------------- FP32 tiles
 
-// One tile of T x T nodes per workgroup of 256 threads.
-template <int T>
+// One tile of T x T nodes per workgroup of NW waves.
+template <int T, int NW = 4>
 struct Tile32 {
-    static constexpr int NW = 4;  // waves
     struct Lds {
         TileLists lists;
         double part[NW][2][64];
@@ -500,7 +498,19 @@ struct Tile32 {
     };
 };
 
-// The FP32 field of the tile at node (i0, j0) by a workgroup of 256 threads.
+// Tile (ti, tj) of workgroup `tile`, ntx tiles a row, each row's tiles turned by one
+// more column.  Workgroups go to the CUs in turn, so a CU's tiles lie a few whole
+// rows apart: in one column without the turn, and a column through a lens's centre
+// then ends last (4096^2 x 200 FP32, four tiles a CU: they ended 37 to 87 us into
+// the launch, 60 on average; with the turn the kernel takes 79 instead of 89, in
+// another model 74 instead of 96).
+__device__ __forceinline__ void tile_at(int tile, int ntx, int& ti, int& tj)
+{
+    tj = tile / ntx;
+    ti = (tile - tj * ntx + tj) % ntx;
+}
+
+// The FP32 field of the tile at node (i0, j0) by a workgroup of NW waves.
 //   1. lists (FP32 criterion, one potential per thread);
 //   2. far sum at the 8 x 8 Chebyshev points, lane = point, the waves sharing
 //      the far list, in FP64 with unrefined estimates (add_far<false>);
@@ -514,21 +524,21 @@ struct Tile32 {
 // Bound by vector issue (256 chains of 512^2 x 50, T = 32: vector instructions in
 // 76 % of the cycles, of them a third of the time FP64, the far sums) once there
 // are tiles enough, by one tile's chain before that.  Against the direct FP32 sum
-// (kernel times): 4096^2 x 200 1402 -> 90 us, 1024^2 x 50 34.3 -> 14.3, the
-// 96-sample batch 4800 -> 800, the 256 chains 1230 -> 537.
-template <int T, class P>
-__device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const P& prof, int np, const GridDesc& g,
+// (kernel times): 4096^2 x 200 1402 -> 79 us, 1024^2 x 50 34.3 -> 14.0, the
+// 96-sample batch 4800 -> 750, the 256 chains 1230 -> 503.
+template <int T, int NW = 4, class P>
+__device__ __forceinline__ void tile32_body(typename Tile32<T, NW>::Lds& L, const P& prof, int np, const GridDesc& g,
                                             int i0, int j0, float* __restrict__ ax, float* __restrict__ ay,
                                             bool bad, float* __restrict__ rec, int nbx)
 {
-    constexpr int NW = Tile32<T>::NW, NTH = 64 * NW;
+    constexpr int NTH = 64 * NW;
     const int tid = threadIdx.x;
     constexpr float hw = 0.5f * (T - 1);
     const int lane = lane_id(), wt = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float xc = (float)i0 + hw, yc = (float)j0 + hw;
     // beyond the lists' capacity every potential counts as near, in order
     const bool all = np > kTileMaxP;
-    if (!all) tile_lists(L.lists, np, [&](int p) { return prof.far(p, xc, yc, hw, kFarC32); });
+    if (!all) tile_lists<NTH>(L.lists, np, [&](int p) { return prof.far(p, xc, yc, hw, kFarC32); });
     const int nn = all ? np : __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
     {
         const double c1 = g.x0 + (double)xc * g.h, c2 = g.y0 + (double)yc * g.h, half = (double)hw * g.h;
@@ -582,7 +592,7 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const P&
     __syncthreads();
     // units of 32 x 16 nodes, or of 32 x 8 where the tile has only two of those for
     // four waves
-    constexpr int NK = T == 32 ? 4 : 8;
+    constexpr int NK = T == 32 || NW == 8 ? 4 : 8;
     constexpr int UX = T / 32, UNITS = UX * (T / (2 * NK));
     const int li = lane & 15, lk = lane >> 4;
     const bool vec = (g.nx & 3) == 0 && (((size_t)ax | (size_t)ay) & 15) == 0;
@@ -654,7 +664,7 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T>::Lds& L, const P&
 // per group of 16 rows, so they need no LDS.  Bound by FP64 issue (48 % of the
 // cycles at 1000 x 777 x 75, where 800 tiles leave a third of the CUs' time idle;
 // 62 % at 2047 x 1531 x 120).  Against the direct FP64 sum: 1000 x 777 x 75
-// 106 -> 51 us, the call of 2047 x 1531 x 120 484 -> 115 (90 in the kernel).
+// 106 -> 51 us, the call of 2047 x 1531 x 120 484 -> 110 (85 in the kernel).
 template <int T>
 struct Tile64 {
     struct Lds {
