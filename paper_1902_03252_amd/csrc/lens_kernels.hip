@@ -24,6 +24,7 @@
 #include "lens_tiles.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace lens {
@@ -1132,7 +1133,11 @@ int tile_side_for(double nodes, double total, int np, const TileCost& k)
     for (int t = 32; t <= 128; t *= 2) {
         const double t2 = (double)t * t, units = std::max(1.0, t2 / 2048.0);  // units of 512 nodes per wave
         const double near = std::min((double)np, 1.0 + np * kPi * 0.25 * k.reach * k.reach * t2 / nodes);
-        const double all = total / 64.0 * (k.near * near + k.far * k.points * np / t2 + k.rest) / 1024.0;
+        // the CUs with one tile more than the others end last (3000^2 x 120, 2.2 tiles a
+        // CU at 128 and 8.6 at 64: FP32 60 us against 39, FP64 211 against 158)
+        const double per_cu = total / t2 / 256.0;
+        const double all = total / 64.0 * (k.near * near + k.far * k.points * np / t2 + k.rest) / 1024.0 *
+                           (std::ceil(per_cu) / per_cu);
         const double chain = 7000.0 + k.far * k.points / 120.0 * np + units * (700.0 + 8.0 * k.near * near);
         const double c = std::max(all, chain);
         if (!best || c < cost) {
