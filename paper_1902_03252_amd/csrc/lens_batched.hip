@@ -210,7 +210,8 @@ __device__ __forceinline__ double lane_val(double v, int l) { return bcast(v, l)
 // node, E_B, and room for this form's own rounding: 16 u (u = 2^-24 or 2^-53) of
 // the grid's and the barycentre's extent, where it is at most 6 u of them, and for
 // the deflection's part 4 E_B (E_B holds 2 u r W, the part is below 3 u r W); FP64:
-// 1e-9, as for the tiles.  A negative r is not cut.
+// 1e-9, as for the tiles, and 1e-8 E_B, which holds both (E_B >= 2^-22 of the farthest corner
+// and 2^-23 r W).  A negative r is not cut.
 template <typename V>
 struct CellCut {
     V r, above[2], below[2];
@@ -231,7 +232,7 @@ __device__ __forceinline__ CellCut<V> cell_cut(const GridDesc& g, const SysVals&
         c.r = y.r;
         o[0] = g.x0 - y.bx;
         o[1] = g.y0 - y.by;
-        w[0] = w[1] = 1e-9;
+        w[0] = w[1] = 1e-9 + 1e-8 * (double)y.e;
     }
 #pragma unroll
     for (int d = 0; d < 2; d++) {

@@ -590,17 +590,18 @@ __device__ __forceinline__ bool tile_box_contains(const GridDesc& g, const Tile&
 
 // A system's values as the containment tests read them.
 struct SysVals {
-    double r, bx, by;             // FP64 path
-    float r32, e, bxh, bxl, byh, byl;  // mixed path: FP32 bound, split barycentre in node units
+    double r, bx, by;               // FP64 path
+    float r32, bxh, bxl, byh, byl;  // mixed path: split barycentre in node units
+    float e;                        // FP32 bound
 };
 
 template <typename V>
 __device__ __forceinline__ SysVals sys_vals(const double* __restrict__ row)
 {
     SysVals v = {};
+    v.e = (float)row[SYS_EB];
     if constexpr (sizeof(V) == 4) {
         v.r32 = (float)row[SYS_R];
-        v.e = (float)row[SYS_EB];
         v.bxh = (float)row[SYS_BXH];
         v.bxl = (float)row[SYS_BXL];
         v.byh = (float)row[SYS_BYH];
