@@ -445,8 +445,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // Culling, one wave per (block of 64 consecutive tiles of S::TX x S::TY
 // cells, chunk of `sc` systems) with `tpw` blocks per wave, lane = tile: each
 // lane bounds its tile's source-plane vertices by the box [theta_min -
-// r alpha_max, theta_max - r alpha_min] from the field kernel's row partials
-// plus the halo column (consecutive tiles read consecutive partials), widened
+// r alpha_max, theta_max - r alpha_min] from the field kernel's range records
+// (REC) or row partials, with the halo (consecutive tiles read consecutive
+// ones), widened
 // by the FP32 bound E_B (mixed path) or 1e-9" (FP64 path), and tests the
 // barycentre of every system of its chunk (the chunk's rows loaded at once,
 // lane = system, then broadcast); every passing (tile, system) pair is

@@ -454,45 +454,9 @@ __device__ __forceinline__ Tile tile_of(const GridDesc& g, int tiles_x, int tile
     return T;
 }
 
-// Deflection range of tile T (with its halo) for every lane of a wave, from
-// the field kernel's row partials: lanes over the tile's node rows, then a
-// butterfly min/max.
-template <class S, typename V>
-__device__ __forceinline__ void tile_range_wave(const V* __restrict__ rr, int tiles_x, const Tile& T, double* rng)
-{
-    const int lane = lane_id();
-    const int col = T.ci0 / S::TX;
-    V mnx = V(INFINITY), mxx = V(-INFINITY), mny = V(INFINITY), mxy = V(-INFINITY);
-    if (lane <= T.ncy) {
-        const int j = T.cj0 + lane;
-        const V* q = rr + ((size_t)j * (tiles_x + 1) + col) * kRR;
-        mnx = q[0];
-        mxx = q[1];
-        mny = q[2];
-        mxy = q[3];
-        if (T.ncx == S::TX) {  // halo column: first node of the next column group
-            const V vx = q[kRR + 4], vy = q[kRR + 5];
-            mnx = fmin(mnx, vx);
-            mxx = fmax(mxx, vx);
-            mny = fmin(mny, vy);
-            mxy = fmax(mxy, vy);
-        }
-    }
-    for (int m = 32; m >= 1; m >>= 1) {
-        mnx = fmin(mnx, __shfl_xor(mnx, m, 64));
-        mxx = fmax(mxx, __shfl_xor(mxx, m, 64));
-        mny = fmin(mny, __shfl_xor(mny, m, 64));
-        mxy = fmax(mxy, __shfl_xor(mxy, m, 64));
-    }
-    rng[0] = mnx;
-    rng[1] = mxx;
-    rng[2] = mny;
-    rng[3] = mxy;
-}
-
-// Deflection range of one tile per lane (the lane's own tile T) from the
-// field kernel's row partials: the same minimum and maximum over the tile's node
-// rows and halo column as tile_range_wave.
+// Deflection range of one tile (with its halo) per lane, the lane's own tile T, from
+// the direct field kernels' row partials: minimum and maximum over the tile's node
+// rows and halo column.
 template <class S, typename V>
 __device__ __forceinline__ void tile_range_lane(const V* __restrict__ rr, int tiles_x, const Tile& T, double* rng)
 {
