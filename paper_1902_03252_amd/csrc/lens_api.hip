@@ -828,8 +828,8 @@ long long batch_field_budget()
 
 // Builds (or finds) the plan of a batch: chunks of consecutive samples within
 // the field-memory budget; inside a chunk the samples are ordered by cost
-// P * nx * ny, heaviest first, and the work items of the field (row segments)
-// and triangle (tile) stages are enumerated in that order.  New plans are
+// P * nx * ny, heaviest first, and the work items of the field (tiles)
+// and triangle (rows of tiles) stages are enumerated in that order.  New plans are
 // uploaded on `s` from pinned staging that stays alive with the plan.
 int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_grid* grids, int shape, bool fp32,
                 hipStream_t s, PlanEntry** out)
