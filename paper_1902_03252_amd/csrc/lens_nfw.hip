@@ -83,7 +83,10 @@ __global__ __launch_bounds__(256) void k_nfw_prep(NfwPtrs h, GridDesc g, double*
 // Roots and reciprocals are the hardware's in FP32 (1 ulp) and the refined
 // estimates in FP64 (about 1 ulp), quotients corrected by one residual; the
 // logarithm is the hardware's in FP32, and there atanh(s) = ln(1 + s) - ln(x),
-// whose terms do not cancel for s >= 0.44.
+// whose terms do not cancel for s >= 0.44.  x^2 may be as small as a product can
+// be (a node next to the centre, a large r_s): the hardware logarithm takes no
+// denormal, so ln4 scales a small argument first, and an x^2 that underflowed to
+// zero is taken as the smallest value whose quarter is not zero.
 template <typename V>
 struct NfwMath;
 
@@ -95,7 +98,13 @@ struct NfwMath<float> {
     __device__ __forceinline__ static float rcp(float v) { return __builtin_amdgcn_rcpf(v); }
     __device__ __forceinline__ static float atn(float v) { return atanf(v); }
     __device__ __forceinline__ static float ath(float s, float x2) { return fmaf(-0.5f, ln(x2), ln(1.0f + s)); }
-    static constexpr float tiny = 1.2e-38f;  // the smallest normal: the hardware logarithm takes no denormal
+    // ln(x2 / 4) for x2 below 1
+    __device__ __forceinline__ static float ln4(float x2)
+    {
+        const bool lo = x2 < 0x1p-100f;
+        return 0.69314718056f * (__builtin_amdgcn_logf(x2 * (lo ? 0x1p60f : 0.25f)) - (lo ? 62.0f : 0.0f));
+    }
+    static constexpr float tiny = 0x1p-149f;
 };
 
 template <>
@@ -106,7 +115,8 @@ struct NfwMath<double> {
     __device__ __forceinline__ static double rcp(double v) { return rcp_est64(v); }
     __device__ __forceinline__ static double atn(double v) { return atan(v); }
     __device__ __forceinline__ static double ath(double s, double) { return atanh(s); }
-    static constexpr double tiny = 1e-300;
+    __device__ __forceinline__ static double ln4(double x2) { return log(0.25 * x2); }
+    static constexpr double tiny = 0x1p-1072;
 };
 
 template <typename V>
@@ -127,7 +137,7 @@ __device__ __forceinline__ V nfw_gx2(V x2)
         V p = V(1) / V(M::kU);
 #pragma unroll
         for (int k = M::kU - 1; k >= 1; k--) p = fma(p, u, V(1) / V(k));
-        return nfw_quot(fma(V(-0.5) * M::ln(V(0.25) * x2), iq, -hq * p), s);
+        return nfw_quot(fma(V(-0.5) * M::ln4(x2), iq, -hq * p), s);
     }
     V F;
     if (fabs(z) <= V(0.2)) {
