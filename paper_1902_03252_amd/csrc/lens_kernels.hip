@@ -1114,6 +1114,7 @@ static int head_blocks_for(const ObsPtrs& obs) { return obs.n_img > 0 ? (int)cdi
 // against direct, FP32: 512^2 x 50 11.8 / 11.7 us, 1024^2 x 50 13.5 / 31.1, 411 x
 // 300 x 50 14.1 / 10.2; FP64: 512^2 x 50 27.6 / 29.9, 512^2 x 100 41 / 53,
 // 1024^2 x 50 38 / 82), and with fewer than 4 potentials there is nothing to share.
+// An FP64 field keeps the direct sum below kTileMinP64 potentials, for its rounding.
 // The side trades far work (P N^2 / T^2 profile evaluations per node) against
 // near work (potentials within about c + 1 half widths, taken as uniform over the
 // grid), and must leave enough workgroups: the longer of the chip's throughput
@@ -1122,7 +1123,7 @@ static int head_blocks_for(const ObsPtrs& obs) { return obs.n_img > 0 ? (int)cdi
 int tiled_side(const GridDesc& g, int np, bool fp32)
 {
     const double nodes = (double)g.nx * g.ny;
-    if (np < 4 || np > kTileMaxP || nodes * np < (double)(1 << 24)) return 0;
+    if (np < (fp32 ? 4 : kTileMinP64) || np > kTileMaxP || nodes * np < (double)(1 << 24)) return 0;
     return tile_side_for(nodes, nodes, np, fp32 ? kTileCost32 : kTileCost64);
 }
 

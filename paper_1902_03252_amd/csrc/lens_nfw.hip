@@ -231,6 +231,7 @@ __global__ __launch_bounds__(256) void k_nfw64(const double* __restrict__ t64, i
 // the same criterion with core 0 holds.  The profile's logarithms and roots bound
 // it, by vector issue: 4096^2 x 702 in FP32 21.6 ms by the direct sum, 0.35 by tiles.
 struct NfwProfile {
+    static constexpr int kMin64 = 0;  // (the profile's own rounding exceeds the interpolation's)
     const double* t64;
     const float* t32;
 

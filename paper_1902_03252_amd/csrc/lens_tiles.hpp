@@ -33,6 +33,13 @@
 namespace lens {
 
 constexpr int kTileMaxP = 2048;  // potentials of a tiled field (LDS lists)
+// Fewest isothermal potentials that an FP64 field takes far terms for.  The
+// interpolation has a rounding of its own, the direct sum one per potential:
+// against long double (24 models each, tiled over direct, rms and maximum) 4
+// potentials 1.02-1.03 and 1.18-1.22, 8 0.95-1.01 and 1.02-1.05, 12 0.90-0.97 and
+// 0.97-0.99, 120 0.62.  (An FP32 field's far part is in FP64 and the smaller
+// error at any count.)
+constexpr int kTileMinP64 = 12;
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
@@ -420,6 +427,7 @@ __device__ __forceinline__ void store_unit(const V* s, V* __restrict__ out, int 
 
 // The isothermal family of the tables (tab64, tab32) as a tile's summand.
 struct IsoProfile {
+    static constexpr int kMin64 = kTileMinP64;  // below, an FP64 tile takes every potential as near
     const double* tab64;
     const float* tab32;
 
@@ -713,7 +721,7 @@ __device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P&
     constexpr float hw = 0.5f * (T - 1);
     const int tid = threadIdx.x, lane = lane_id(), wt = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float xc = (float)i0 + hw, yc = (float)j0 + hw;
-    const bool all = np > kTileMaxP;
+    const bool all = np > kTileMaxP || np < P::kMin64;
     if (!all) tile_lists(L.lists, np, [&](int p) { return prof.far(p, xc, yc, hw, kFarC64); });
     const int nn = all ? np : __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
     const int lo = tid & 15, hi = tid >> 4;
