@@ -120,6 +120,7 @@ struct TileCost {
 constexpr TileCost kTileCost32 = {75.0, 116.0, 64.0, 60.0, 3.6};
 constexpr TileCost kTileCost64 = {200.0, 180.0, 256.0, 200.0, 5.1};
 int tile_side_for(double nodes, double total, int np, const TileCost& k);
+bool tiles_too_thin(const GridDesc& g, int side, int least);
 inline int rec_nbx(const GridDesc& g) { return (g.nx + 31) / 32; }
 inline int rec_nby(const GridDesc& g) { return (g.ny + 7) / 8; }
 hipError_t launch_tiled32(int side, const double* tab64, const float* tab32, int np, const GridDesc& g, float* ax,

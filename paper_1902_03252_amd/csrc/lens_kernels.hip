@@ -1124,7 +1124,21 @@ int tiled_side(const GridDesc& g, int np, bool fp32)
 {
     const double nodes = (double)g.nx * g.ny;
     if (np < (fp32 ? 4 : kTileMinP64) || np > kTileMaxP || nodes * np < (double)(1 << 24)) return 0;
-    return tile_side_for(nodes, nodes, np, fp32 ? kTileCost32 : kTileCost64);
+    const int side = tile_side_for(nodes, nodes, np, fp32 ? kTileCost32 : kTileCost64);
+    return tiles_too_thin(g, side, fp32 ? 160 : 352) ? 0 : side;
+}
+
+// Whether a grid is so thin that its tiles hold fewer than `least` nodes on average:
+// the direct sum at those nodes is then cheaper than the far sums at a tile's
+// Chebyshev points.  Narrow grids are not taken for thin, a direct kernel's workgroup
+// covers 512 columns of a row.  (Rows of a wide grid, direct against tiled: FP32, 64
+// points, 120000 x 2 x 100 29 / 42 us, x 4 37 / 41, 90000 x 6 x 60 30 / 26; FP64, 256
+// points, 90000 x 6 x 60 64 / 85, x 8 73 / 85, 60000 x 12 x 60 73 / 67; 8 x 60000 x 50
+// FP64 1764 / 61.)
+bool tiles_too_thin(const GridDesc& g, int side, int least)
+{
+    const long long tiles = (long long)cdiv(g.nx, side) * cdiv(g.ny, side);
+    return g.nx >= 512 && (long long)g.nx * g.ny < least * tiles;
 }
 
 // The best side for a grid of `nodes` nodes in a launch of `total` nodes.

@@ -350,9 +350,12 @@ hipError_t launch_nfw(const NfwPtrs& h, const GridDesc& g, bool fp32, void* ax, 
     // Tiled from 2^23 (FP32) or 2^24 (FP64) terms on, where its chain of 35 or 150 us
     // is repaid (tiled against direct: FP32 512 x 500 x 100 38 / 61 us, 2048^2 x 302
     // 85 / 1400, and the direct kernel before this function's rewriting 2490; FP64
-    // 300^2 x 60 159 / 155, 512 x 500 x 100 191 / 204, 2048^2 x 302 836 / 6890).
-    if (h.n >= 4 && h.n <= kTileMaxP && nodes * h.n >= (fp32 ? 8388608.0 : 16777216.0)) {
-        const int side = tile_side_for(nodes, nodes, h.n, fp32 ? kNfwCost32 : kNfwCost64);
+    // 300^2 x 60 159 / 155, 512 x 500 x 100 191 / 204, 2048^2 x 302 836 / 6890), but in
+    // FP64 not thin grids (65536 x 2 x 140 149 / 445, 90000 x 6 x 60 244 / 265, 60000 x 12
+    // x 60 318 / 201; in FP32 the tiles are the faster even at two rows).
+    const int side = tile_side_for(nodes, nodes, h.n, fp32 ? kNfwCost32 : kNfwCost64);
+    if (h.n >= 4 && h.n <= kTileMaxP && nodes * h.n >= (fp32 ? 8388608.0 : 16777216.0) &&
+        (fp32 || !tiles_too_thin(g, side, 256))) {
         const int ntx = (g.nx + side - 1) / side;
         const dim3 grid((unsigned)(ntx * ((g.ny + side - 1) / side)));
         auto go = [&](auto t) {
