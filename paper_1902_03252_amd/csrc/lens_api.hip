@@ -828,7 +828,7 @@ long long batch_field_budget()
 
 // Builds (or finds) the plan of a batch: chunks of consecutive samples within
 // the field-memory budget; inside a chunk the samples are ordered by cost
-// P * nx * ny, heaviest first, and the work items of the field (tiles)
+// P * nx * ny, heaviest first, and the work items of the field (tiles or units)
 // and triangle (rows of tiles) stages are enumerated in that order.  New plans are
 // uploaded on `s` from pinned staging that stays alive with the plan.
 int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_grid* grids, int shape, bool fp32,
@@ -928,8 +928,7 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
             h_no[k] = node;
             h_rr[k] = nrr;
             node += (long long)g.nx * g.ny;
-            h_side[k] = tile_side_for((double)g.nx * g.ny, (double)nodes, pot_off[s0 + k + 1] - pot_off[s0 + k],
-                                      fp32 ? kTileCost32 : kTileCost64);
+            h_side[k] = batch_side(h_grid[k], pot_off[s0 + k + 1] - pot_off[s0 + k], (double)nodes, fp32);
             nrr += (long long)rec_nbx(h_grid[k]) * rec_nby(h_grid[k]) * kRec;
             ch.n_tests += 2ll * (g.nx - 1) * (g.ny - 1);
         }
@@ -939,8 +938,7 @@ int batch_plan(lens_ctx* c, int n_samples, const int32_t* pot_off, const lens_gr
         for (int k = 0; k < n; k++) {
             const lens_grid& g = grids[s0 + perm[k]];
             h_perm[k] = perm[k];
-            const int side = h_side[perm[k]];
-            h_fo[k + 1] = h_fo[k] + (long long)((g.ny + side - 1) / side) * ((g.nx + side - 1) / side);
+            h_fo[k + 1] = h_fo[k] + batch_items(h_grid[perm[k]], h_side[perm[k]], h_pot[perm[k] + 1] - h_pot[perm[k]]);
             // triangle stage: one item per (tile row, kTriTiles tile columns)
             h_to[k + 1] = h_to[k] + (long long)(((g.nx - 2) / tx + kTriTiles) / kTriTiles) * ((g.ny - 2) / ty + 1);
         }

@@ -7,7 +7,7 @@
 //             counters
 //   k_bmap    work-item -> sample maps of the field and triangle stages
 //   k_btiled  FP32 or FP64 deflection, one workgroup per (sample, tile), heaviest
-//             samples first
+//             samples first; by a direct sum for the samples that batch_side says
 //   k_btri    one workgroup per (sample, 32 tiles of a row), heaviest samples first
 //   k_bfbpos  FP64 image positions of every hit (a workgroup per sample) and
 //             the FP64 re-test of every undecided FP32 test
@@ -16,6 +16,8 @@
 // functions, Rexroth et al. 2019, Sec. 2.2.1-2.2.2 and Algorithm 1).
 #include "lens_path.hpp"
 #include "lens_tiles.hpp"
+
+#include <type_traits>
 
 namespace lens {
 
@@ -136,9 +138,7 @@ __global__ __launch_bounds__(256) void k_bmap(BatchPlan bp, int* __restrict__ fm
 
 // One workgroup per (sample, tile); the map gives the sample (heaviest samples
 // first).  The tiled field of the single evaluation (lens_tiles.hpp) with each
-// sample's own tile side, for every sample: a batch fills the chip whatever its
-// samples' sizes, and a sample too small to have far potentials costs what the
-// direct sum would.
+// sample's own tile side, or, where that is 0 (batch_side), the direct sum.
 template <int T>
 __device__ __forceinline__ void btile(void* lds, const IsoProfile& prof, int np, const GridDesc& g, int tile, float* fx,
                                       float* fy, float* rec)
@@ -156,6 +156,286 @@ __device__ __forceinline__ void btile(void* lds, const IsoProfile& prof, int np,
                    FieldSink64{fx, fy, rec, g.nx, g.ny, false});
 }
 
+// The direct sum of the single evaluation in two forms.  Few potentials: the field is
+// memory traffic, and a wave takes 64 columns x 8 rows with no barrier (bdirect_few).
+// Otherwise (bdirect) one workgroup per unit of 64 columns x 8 rows (128 x 4 and 256 x 2
+// where the grid has no more rows): lane = column, two rows per wave.  The table rows
+// of 64 potentials at a time are staged in LDS: with thousands of potentials on few
+// nodes there are too few waves to hide a scalar load from beyond its cache per
+// potential.
+constexpr int kUnitY = 8;  // rows of a range record
+
+// LDS of a unit; v: range records by 32 columns and wave: range, first row, first column.
+template <typename V>
+struct DirectLds;
+template <>
+struct DirectLds<float> {
+    float v[2][4][12];
+    float4 rows[4][2][64];  // per wave: row parts of field32_pot
+    float c[64][T32_STRIDE];
+};
+template <>
+struct DirectLds<double> {
+    double v[2][4][12];
+    double c[64][10];
+};
+
+// Sums of the wave's rows j and j + 1 at column i; all threads call it, a wave whose
+// rows lie outside the grid with act = false.
+__device__ __forceinline__ void direct_rows(DirectLds<float>& L, const IsoProfile& prof, int np, const GridDesc&, int i,
+                                            int j, bool act, float* sx, float* sy)
+{
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const float fi = (float)i;
+    for (int b = 0; b < np; b += 64) {
+        const int cnt = min(64, np - b);
+        if (b) __syncthreads();  // the previous 64 potentials have been read
+        for (int q = threadIdx.x; q < cnt * T32_STRIDE; q += 256) (&L.c[0][0])[q] = prof.tab32[(size_t)b * T32_STRIDE + q];
+        __syncthreads();
+        if (!act) continue;
+        if (lane < cnt) {
+            const float* c = L.c[lane];
+#pragma unroll
+            for (int r = 0; r < 2; r++) {
+                const float nyv = ((float)(j + r) - c[T32_CYH]) - c[T32_CYL];
+                L.rows[wave][r][lane] =
+                    make_float4(c[T32_BP] * nyv, c[T32_CQ] * nyv, fmaf(c[T32_DQ] * nyv, nyv, c[T32_A2]), c[T32_RSK]);
+            }
+        }
+        wave_lds_sync();
+#pragma unroll 2
+        for (int k = 0; k < cnt; k++) {
+            const float4 rc[2] = {L.rows[wave][0][k], L.rows[wave][1][k]};
+            field32_pot<1, 2>(L.c[k], rc, &fi, sx, sy);
+        }
+    }
+}
+__device__ __forceinline__ void direct_rows(DirectLds<double>& L, const IsoProfile& prof, int np, const GridDesc& g,
+                                            int i, int j, bool act, double* sx, double* sy)
+{
+    const int lane = lane_id();
+    const double t1 = node_coord(g.x0, i, g.h), t2[2] = {node_coord(g.y0, j, g.h), node_coord(g.y0, j + 1, g.h)};
+    auto add = [&](int k, auto has) {
+        const Far64 c = load_far(L.c[k]);
+        const double d1 = t1 - c.xc;
+#pragma unroll
+        for (int r = 0; r < 2; r++) {
+            const double d2 = t2[r] - c.yc;
+            IsoProfile::node64<decltype(has)::value>(c, d1, d2, c.B * d2, c.C * d2, sx[r], sy[r]);
+        }
+    };
+    for (int b = 0; b < np; b += 64) {
+        const int cnt = min(64, np - b);
+        if (b) __syncthreads();
+        for (int q = threadIdx.x; q < cnt * 10; q += 256)
+            (&L.c[0][0])[q] = prof.tab64[(size_t)(b + q / 10) * T64_STRIDE + q % 10];
+        __syncthreads();
+        if (!act) continue;
+        const unsigned long long cut = __ballot(lane < cnt && __double_as_longlong(L.c[lane][T64_RS]) != 0);
+        for (int k = 0; k < cnt;) {  // two of a kind at a time: their chains interleave
+            const unsigned kinds = (unsigned)(cut >> k) & 3u;
+            const bool two = k + 1 < cnt;
+            if (two && kinds == 3u) {
+                add(k, std::true_type());
+                add(k + 1, std::true_type());
+                k += 2;
+            } else if (two && kinds == 0u) {
+                add(k, std::false_type());
+                add(k + 1, std::false_type());
+                k += 2;
+            } else {
+                if (kinds & 1u)
+                    add(k, std::true_type());
+                else
+                    add(k, std::false_type());
+                k++;
+            }
+        }
+    }
+}
+
+// Minimum over 32 columns of eight values per lane, in lane l the one of index
+// l / 16 % 2 + 2 (l / 8 % 2) + 4 (l / 4 % 2): half of the values change lanes at each of
+// the first three steps, so that there are 9 exchanges, not 40.
+template <typename V>
+__device__ __forceinline__ V min32x8(V* v)
+{
+    const int lane = lane_id();
+#pragma unroll
+    for (int k = 0; k < 8; k += 2) {
+        row_swap<16>(v[k], v[k + 1]);
+        v[k] = fmin(v[k], v[k + 1]);
+    }
+    const bool b3 = (lane & 8) != 0, b2 = (lane & 4) != 0;
+#pragma unroll
+    for (int k = 0; k < 8; k += 4) {
+        const V other = dpp_mov<0x128>(b3 ? v[k] : v[k + 2]);  // lane ^ 8
+        v[k] = fmin(b3 ? v[k + 2] : v[k], other);
+    }
+    const V other = dpp_mov<0x141>(b2 ? v[0] : v[4]);  // the other half of 8 lanes
+    V r = fmin(b2 ? v[4] : v[0], other);
+    r = fmin(r, dpp_mov<0xB1>(r));
+    return fmin(r, dpp_mov<0x4E>(r));
+}
+
+// Range records (write_records) of the unit at row j0 with nr rows, nwx waves to a
+// pair of rows: over the wave's rows and 32 columns, then over the waves of the
+// columns; the maxima as minima of the negatives.
+template <typename V>
+__device__ __forceinline__ void unit_records(DirectLds<V>& L, const V* sx, const V* sy, int nr, int i, int j0, int nwx,
+                                             int nx, int nbx, V* __restrict__ rec)
+{
+    const int lane = lane_id(), wave = threadIdx.x >> 6, half = lane >> 5, k0 = lane & 31;
+    const int row0 = 2 * (wave / nwx);  // of the unit
+    const V inf = V(INFINITY);
+    V v[8], c[4];
+#pragma unroll
+    for (int k = 0; k < 8; k++) v[k] = inf;
+    if (i < nx) {
+#pragma unroll
+        for (int r = 0; r < 2; r++)
+            if (row0 + r < nr) {
+                v[0] = fmin(v[0], sx[r]);
+                v[1] = fmin(v[1], -sx[r]);
+                v[2] = fmin(v[2], sy[r]);
+                v[3] = fmin(v[3], -sy[r]);
+            }
+        if (row0 == 0) {
+            v[4] = sx[0];
+            v[5] = -sx[0];
+            v[6] = sy[0];
+            v[7] = -sy[0];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) c[k] = v[k];
+    const V m = min32x8(v);
+    if ((lane & 3) == 0) L.v[half][wave][((lane >> 4) & 1) + ((lane >> 2) & 2) + (lane & 4)] = m;
+    if (k0 == 0)  // the first column's rows
+#pragma unroll
+        for (int k = 0; k < 4; k++) L.v[half][wave][8 + k] = c[k];
+    __syncthreads();
+    if (row0 == 0 && i - k0 < nx) {
+        V* o = rec + ((size_t)(j0 >> 3) * nbx + (i >> 5)) * kRec;
+        if (k0 < 12) {
+            V q = L.v[half][wave][k0];
+            for (int w = wave + nwx; w < 4; w += nwx) q = fmin(q, L.v[half][w][k0]);
+            o[k0] = (k0 & 1) ? -q : q;
+        }
+        if (k0 == 0) {
+            o[12] = sx[0];
+            o[13] = sy[0];
+        }
+    }
+}
+
+// Rows R0 .. R0 + 3 of a column of the unit at row j0: potential p's part.
+template <int R0>
+__device__ __forceinline__ void add_rows(const IsoProfile& prof, int p, const GridDesc&, int i, int j0, float* sx,
+                                         float* sy)
+{
+    const float* c = prof.tab32 + (size_t)p * T32_STRIDE;
+    const float fi = (float)i;
+    float4 rc[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        const float nyv = ((float)(j0 + R0 + r) - c[T32_CYH]) - c[T32_CYL];
+        rc[r] = make_float4(c[T32_BP] * nyv, c[T32_CQ] * nyv, fmaf(c[T32_DQ] * nyv, nyv, c[T32_A2]), c[T32_RSK]);
+    }
+    field32_pot<1, 4>(c, rc, &fi, sx + R0, sy + R0);
+}
+template <int R0>
+__device__ __forceinline__ void add_rows(const IsoProfile& prof, int p, const GridDesc& g, int i, int j0, double* sx,
+                                         double* sy)
+{
+    const Far64 c = load_far(prof.tab64 + (size_t)p * T64_STRIDE);
+    const double d1 = node_coord(g.x0, i, g.h) - c.xc;
+    auto rows = [&](auto has) {
+#pragma unroll
+        for (int r = R0; r < R0 + 4; r++) {
+            const double d2 = node_coord(g.y0, j0 + r, g.h) - c.yc;
+            IsoProfile::node64<decltype(has)::value>(c, d1, d2, c.B * d2, c.C * d2, sx[r], sy[r]);
+        }
+    };
+    if (__double_as_longlong(c.rs) == 0)
+        rows(std::false_type());
+    else
+        rows(std::true_type());
+}
+
+constexpr int kFewP = 12;  // potentials below which a wave takes a unit by itself
+
+template <typename V>
+__device__ __forceinline__ void bdirect_few(const IsoProfile& prof, int np, const GridDesc& g, int item,
+                                            V* __restrict__ fx, V* __restrict__ fy, V* __restrict__ rec)
+{
+    const int nux = (g.nx + 63) / 64, unit = 4 * item + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int uj = unit / nux, lane = lane_id(), i = (unit - uj * nux) * 64 + lane, j0 = uj * kUnitY;
+    if (j0 >= g.ny) return;  // the last workgroup's spare waves
+    const int nr = min(kUnitY, g.ny - j0);
+    V sx[kUnitY] = {}, sy[kUnitY] = {};
+    for (int p = 0; p < np; p++) {
+        add_rows<0>(prof, p, g, i, j0, sx, sy);
+        if (nr > 4) add_rows<4>(prof, p, g, i, j0, sx, sy);
+    }
+    // records as unit_records, of one wave
+    V v[8], c[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const V* s = k < 2 ? sx : sy;
+        c[k] = (k & 1) ? -s[0] : s[0];
+        v[4 + k] = i < g.nx ? c[k] : V(INFINITY);
+#pragma unroll
+        for (int r = 1; r < kUnitY; r++)
+            if (r < nr) c[k] = fmin(c[k], (k & 1) ? -s[r] : s[r]);
+        v[k] = i < g.nx ? c[k] : V(INFINITY);
+    }
+    const V m = min32x8(v);
+    if ((i & ~31) < g.nx) {
+        V* o = rec + ((size_t)uj * ((g.nx + 31) >> 5) + (i >> 5)) * kRec;
+        if ((lane & 3) == 0) {
+            const int k = ((lane >> 4) & 1) + ((lane >> 2) & 2) + (lane & 4);
+            o[k] = (k & 1) ? -m : m;
+        }
+        if ((lane & 31) == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) o[8 + k] = (k & 1) ? -c[k] : c[k];
+            o[12] = sx[0];
+            o[13] = sy[0];
+        }
+    }
+    if (i >= g.nx) return;
+#pragma unroll
+    for (int r = 0; r < kUnitY; r++)
+        if (r < nr) {
+            fx[(size_t)(j0 + r) * g.nx + i] = sx[r];
+            fy[(size_t)(j0 + r) * g.nx + i] = sy[r];
+        }
+}
+
+// Waves of a unit along x: the grid's few rows (2, 4) leave them columns.
+__host__ __device__ inline int unit_waves_x(const GridDesc& g) { return g.ny <= 2 ? 4 : g.ny <= 4 ? 2 : 1; }
+
+template <typename V>
+__device__ __forceinline__ void bdirect(DirectLds<V>& L, const IsoProfile& prof, int np, const GridDesc& g, int unit,
+                                        V* __restrict__ fx, V* __restrict__ fy, V* __restrict__ rec)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nwx = unit_waves_x(g);
+    const int ux = 64 * nwx, nux = (g.nx + ux - 1) / ux, uj = unit / nux, wy = wave / nwx;
+    const int ib = (unit - uj * nux) * ux + 64 * (wave - wy * nwx), i = ib + lane_id();
+    const int j0 = uj * kUnitY, j = j0 + 2 * wy;
+    V sx[2] = {}, sy[2] = {};
+    direct_rows(L, prof, np, g, i, j, j < g.ny && ib < g.nx, sx, sy);
+    unit_records(L, sx, sy, min(kUnitY, g.ny - j0), i, j0, nwx, g.nx, (g.nx + 31) >> 5, rec);
+    if (i >= g.nx) return;
+#pragma unroll
+    for (int r = 0; r < 2; r++)
+        if (j + r < g.ny) {
+            fx[(size_t)(j + r) * g.nx + i] = sx[r];
+            fy[(size_t)(j + r) * g.nx + i] = sy[r];
+        }
+}
+
 template <typename V>
 __device__ __forceinline__ void bfield(void* lds, const BatchPlan& bp, const int* __restrict__ fmap,
                                        const double* __restrict__ tab64, const float* __restrict__ tab32,
@@ -164,16 +444,22 @@ __device__ __forceinline__ void bfield(void* lds, const BatchPlan& bp, const int
     const int k = fmap[blockIdx.x];
     const int s = bp.perm[k];
     const GridDesc g = bp.grid[s];
-    const int tile = (int)(blockIdx.x - bp.fitem_off[k]);
+    const int item = (int)(blockIdx.x - bp.fitem_off[k]);
     const int q0 = bp.pot_off[s] - bp.pot_off[0], np = bp.pot_off[s + 1] - bp.pot_off[s];
     const IsoProfile prof{tab64 + (size_t)q0 * T64_STRIDE, tab32 + (size_t)q0 * T32_STRIDE};
     V* ox = fx + bp.node_off[s];
     V* oy = fy + bp.node_off[s];
     V* r = rec + bp.rr_off[s];
     switch (bp.side[s]) {  // uniform over the workgroup
-    case 32: btile<32>(lds, prof, np, g, tile, ox, oy, r); break;
-    case 64: btile<64>(lds, prof, np, g, tile, ox, oy, r); break;
-    default: btile<128>(lds, prof, np, g, tile, ox, oy, r); break;
+    case 0:
+        if (np < kFewP)
+            bdirect_few(prof, np, g, item, ox, oy, r);
+        else
+            bdirect(*static_cast<DirectLds<V>*>(lds), prof, np, g, item, ox, oy, r);
+        break;
+    case 32: btile<32>(lds, prof, np, g, item, ox, oy, r); break;
+    case 64: btile<64>(lds, prof, np, g, item, ox, oy, r); break;
+    default: btile<128>(lds, prof, np, g, item, ox, oy, r); break;
     }
 }
 
@@ -184,6 +470,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
                                                   float* __restrict__ rec)
 {
     __shared__ __align__(16) unsigned char lds[sizeof(Tile32<128>::Lds)];
+    static_assert(sizeof lds >= sizeof(DirectLds<float>));
     bfield<float>(lds, bp, fmap, tab64, tab32, fx, fy, rec);
 }
 
@@ -192,6 +479,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     double* __restrict__ fx, double* __restrict__ fy, double* __restrict__ rec)
 {
     __shared__ __align__(16) unsigned char lds[sizeof(Tile64<128>::Lds)];
+    static_assert(sizeof lds >= sizeof(DirectLds<double>));
     bfield<double>(lds, bp, fmap, tab64, tab32, fx, fy, rec);
 }
 
@@ -625,6 +913,27 @@ hipError_t launch_bmap(const BatchPlan& bp, int* fmap, int* tmap, hipStream_t s)
 {
     k_bmap<<<bp.n, 256, 0, s>>>(bp, fmap, tmap);
     return hipGetLastError();
+}
+
+// Tile side of a sample's field in a launch of `total` nodes, 0 for the direct sum:
+// where a single evaluation would never be tiled, whatever its size (tiled_side).
+// Whole calls with such samples tiled (all their potentials near) / by the direct sum:
+// FP64 64 of 512^2 x 3 283 / 169 us, 8 of 120^2 x 2100 1422 / 655 (mixed 1006 / 398),
+// 2 of 100000 x 2 x 100 312 / 106.
+int batch_side(const GridDesc& g, int np, double total, bool fp32)
+{
+    if (np < (fp32 ? 4 : kTileMinP64) || np > kTileMaxP) return 0;
+    const int side = tile_side_for((double)g.nx * g.ny, total, np, fp32 ? kTileCost32 : kTileCost64);
+    return tiles_too_thin(g, side, fp32 ? kThinNodes32 : kThinNodes64) ? 0 : side;
+}
+
+// Work items of a sample's field (workgroups).
+long long batch_items(const GridDesc& g, int side, int np)
+{
+    if (side) return (long long)((g.nx + side - 1) / side) * ((g.ny + side - 1) / side);
+    const int ux = np < kFewP ? 64 : 64 * unit_waves_x(g);
+    const long long units = (long long)((g.nx + ux - 1) / ux) * ((g.ny + kUnitY - 1) / kUnitY);
+    return np < kFewP ? (units + 3) / 4 : units;
 }
 
 hipError_t launch_bfield(bool fp32, const BatchPlan& bp, const int* fmap, long long n_items, const double* tab64,

@@ -55,8 +55,8 @@ struct BatchPlan {
     const int* pot_off;           // [n+1] parameter columns of each sample (absolute)
     const GridDesc* grid;         // [n]
     const int* perm;              // [n] plan position -> sample (heaviest first)
-    const int* side;              // [n] nodes per side of the sample's field tiles
-    const long long* fitem_off;   // [n+1] field work items (tiles), in plan order
+    const int* side;              // [n] nodes per side of the sample's field tiles, 0: direct sum
+    const long long* fitem_off;   // [n+1] field work items (tiles, or units of the direct sum), in plan order
     const long long* titem_off;   // [n+1] triangle-stage items (tile row x kTriTiles columns), in plan order
     const long long* node_off;    // [n] offset of each sample's field (nodes)
     const long long* rr_off;      // [n] offset of each sample's range records (values)
@@ -121,6 +121,9 @@ constexpr TileCost kTileCost32 = {75.0, 116.0, 64.0, 60.0, 3.6};
 constexpr TileCost kTileCost64 = {200.0, 180.0, 256.0, 200.0, 5.1};
 int tile_side_for(double nodes, double total, int np, const TileCost& k);
 bool tiles_too_thin(const GridDesc& g, int side, int least);
+constexpr int kThinNodes32 = 160, kThinNodes64 = 352;  // nodes per tile below which it is too thin
+int batch_side(const GridDesc& g, int np, double total, bool fp32);
+long long batch_items(const GridDesc& g, int side, int np);
 inline int rec_nbx(const GridDesc& g) { return (g.nx + 31) / 32; }
 inline int rec_nby(const GridDesc& g) { return (g.ny + 7) / 8; }
 hipError_t launch_tiled32(int side, const double* tab64, const float* tab32, int np, const GridDesc& g, float* ax,

@@ -1125,7 +1125,7 @@ int tiled_side(const GridDesc& g, int np, bool fp32)
     const double nodes = (double)g.nx * g.ny;
     if (np < (fp32 ? 4 : kTileMinP64) || np > kTileMaxP || nodes * np < (double)(1 << 24)) return 0;
     const int side = tile_side_for(nodes, nodes, np, fp32 ? kTileCost32 : kTileCost64);
-    return tiles_too_thin(g, side, fp32 ? 160 : 352) ? 0 : side;
+    return tiles_too_thin(g, side, fp32 ? kThinNodes32 : kThinNodes64) ? 0 : side;
 }
 
 // Whether a grid is so thin that its tiles hold fewer than `least` nodes on average:

@@ -467,7 +467,26 @@ struct IsoProfile {
         else
             near64_nodes<NK, true>(c, t1, t2, sx, sy);
     }
-    // add_alpha64 at NK nodes, the profile kind decided once, four nodes' chains
+    // add_alpha64 at a node: offset (d1, d2) from the centre, B d2 and C d2.
+    template <bool CUT>
+    __device__ __forceinline__ static void node64(const Far64& c, double d1, double d2, double bd2, double cd2,
+                                                  double& sx, double& sy)
+    {
+        const double m1 = fma(c.A, d1, bd2), m2 = fma(c.B, d1, cd2);
+        const double R2 = fma(d1, m1, d2 * m2);
+        const double qa = sqrt_est64(fmax(fabs(c.a2 + R2), 1e-300)) + c.ra;
+        double f;
+        if constexpr (CUT) {
+            const double qs = sqrt_est64(c.s2 + R2) + c.rs;
+            f = (qs - qa) * rcp_est64(qa * qs);
+        } else {
+            f = rcp_est64(qa);
+        }
+        const double kf = c.K * f;
+        sx = fma(kf, m1, sx);
+        sy = fma(kf, m2, sy);
+    }
+    // NK nodes of a row, the profile kind decided once, four nodes' chains
     // interleaved at a time (all eight would cost the occupancy its registers).
     template <int NK, bool CUT>
     __device__ __forceinline__ static void near64_nodes(const Far64& c, const double* t1, double t2, double* sx,
@@ -477,22 +496,7 @@ struct IsoProfile {
 #pragma unroll
         for (int q = 0; q < NK; q += 4) {
 #pragma unroll
-            for (int k = q; k < q + 4; k++) {
-                const double d1 = t1[k] - c.xc;
-                const double m1 = fma(c.A, d1, bd2), m2 = fma(c.B, d1, cd2);
-                const double R2 = fma(d1, m1, d2 * m2);
-                const double qa = sqrt_est64(fmax(fabs(c.a2 + R2), 1e-300)) + c.ra;
-                double f;
-                if constexpr (CUT) {
-                    const double qs = sqrt_est64(c.s2 + R2) + c.rs;
-                    f = (qs - qa) * rcp_est64(qa * qs);
-                } else {
-                    f = rcp_est64(qa);
-                }
-                const double kf = c.K * f;
-                sx[k] = fma(kf, m1, sx[k]);
-                sy[k] = fma(kf, m2, sy[k]);
-            }
+            for (int k = q; k < q + 4; k++) node64<CUT>(c, t1[k] - c.xc, d2, bd2, cd2, sx[k], sy[k]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
