@@ -453,7 +453,7 @@ int lens_deflect_mixed(lens_ctx* ctx, const lens_potentials* pot, const lens_gri
     int rc;
     if ((rc = ensure(ctx, B_TAB64, np * T64_STRIDE * 8)) || (rc = ensure(ctx, B_TAB32, np * T32_STRIDE * 4)) ||
         (rc = ensure(ctx, B_BTERM, np * 3 * 8)) || (rc = ensure(ctx, B_MIX, sizeof(MixState))) ||
-        (rc = ensure(ctx, B_MCOUNT, mixed_counts(g) * sizeof(uint2))) ||
+        (rc = ensure(ctx, B_MCOUNT, mixed_counts(g) * sizeof(uint2) + np * sizeof(int2))) ||
         (!mask && (rc = ensure(ctx, B_MMASK, (size_t)nn))))
         return rc;
     MixedLaunch ml;
@@ -465,6 +465,7 @@ int lens_deflect_mixed(lens_ctx* ctx, const lens_potentials* pot, const lens_gri
     ml.ay = ay;
     ml.mask = mask ? mask : (unsigned char*)ctx->buf[B_MMASK];
     ml.counts = (uint2*)ctx->buf[B_MCOUNT];
+    ml.corner = (int2*)(ml.counts + mixed_counts(g));
     ml.stats = (long long*)stats;
     ml.n_cluster = opts->n_cluster;
     ml.pc = opts->patch_cluster;

@@ -234,6 +234,7 @@ struct MixedLaunch {
     double *ax, *ay;       // [ny*nx] output
     unsigned char* mask;   // [ny*nx] 0 FP32, 1 DP block, 2 DP by the criteria
     uint2* counts;         // [mixed_counts] block and criteria pixels per scan workgroup
+    int2* corner;          // [n] first pixel of every halo's block
     long long* stats;      // [4] block pixels, criteria pixels, DP pixels, status
     int n_cluster, pc, pg;
     double t12, t34;

@@ -6,8 +6,8 @@
 // that field, ask for it.
 //
 // Launch sequence (one call, the caller's stream):
-//   k_mix_prep     constants of every potential (one workgroup), SIE check,
-//                  counters reset
+//   k_mix_prep     constants of every potential and the corner of its block (one
+//                  workgroup), SIE check
 //   k_mix_field32  FP32 field at every node (SIE form alpha = K m / R with
 //                  R = sqrt(d . M d): one reciprocal square root per
 //                  potential), written as double; mask cleared
@@ -30,8 +30,12 @@ namespace lens {
 
 // ---------------------------------------------------------------- constants
 
-__global__ __launch_bounds__(256) void k_mix_prep(PotPtrs pot, GridDesc g, double* __restrict__ tab64,
-                                                  float* __restrict__ tab32, double* __restrict__ bterm,
+// The block of halo p: `size` x `size` pixels (pc for the first n_cluster halos, pg
+// for the others) spanning node indices [k - size/2, k - size/2 + size) on each axis,
+// k = (x_c - x0)/h rounded half away from zero.  corner[p] = k - size/2.
+__global__ __launch_bounds__(256) void k_mix_prep(PotPtrs pot, GridDesc g, int n_cluster, int pc, int pg,
+                                                  double* __restrict__ tab64, float* __restrict__ tab32,
+                                                  double* __restrict__ bterm, int2* __restrict__ corner,
                                                   MixState* __restrict__ st)
 {
     __shared__ int s_bad;
@@ -42,7 +46,13 @@ __global__ __launch_bounds__(256) void k_mix_prep(PotPtrs pot, GridDesc g, doubl
         double row[T64_STRIDE], terms[3];
         prep_one(pot, g, p, p, tab64, tab32, bterm, row, terms);
         // the criteria and blocks are derived for the SIE (Sec. 3.2): no core, no cut
-        bad |= terms[2] != 0.0 || pot.r_core[p] != 0.0 || !isinf(pot.r_cut[p]) || pot.r_cut[p] < 0.0;
+        const bool out = terms[2] != 0.0 || pot.r_core[p] != 0.0 || !isinf(pot.r_cut[p]) || pot.r_cut[p] < 0.0;
+        bad |= out;
+        const int half = (p < n_cluster ? pc : pg) / 2;
+        // (a valid centre is within 2^22 nodes)
+        corner[p] = out ? make_int2(0, 0)
+                        : make_int2((int)llround((pot.x[p] - g.x0) / g.h) - half,
+                                    (int)llround((pot.y[p] - g.y0) / g.h) - half);
     }
     if (bad) atomicOr(&s_bad, 1);
     __syncthreads();
@@ -202,38 +212,78 @@ __device__ __forceinline__ void sie64_add(const double* __restrict__ t, double t
     s2 = fma(kr, m2, s2);
 }
 
-// The FP64 blocks of halos [p0, p0 + gridDim.x): `size` x `size` pixels spanning
-// node indices [k - size/2, k - size/2 + size) on each axis, k = (x_c - x0)/h
-// rounded half away from zero, clipped to the grid.  The workgroups of column
-// blockIdx.x mark halo blockIdx.x's pixels in the mask and write their FP64
-// gradient, 256 pixels at a time (a pixel of two blocks is written twice with
-// the same value).
-__global__ __launch_bounds__(256) void k_mix_blocks(PotPtrs pot, GridDesc g, int p0, int size_,
-                                                    const double* __restrict__ tab64, double* __restrict__ ax,
-                                                    double* __restrict__ ay, unsigned char* __restrict__ mask,
-                                                    const MixState* __restrict__ st)
+// The FP64 blocks of halos [p0, p0 + gridDim.x), side `size`, clipped to the grid: the
+// workgroups of column blockIdx.x mark halo blockIdx.x's pixels in the mask and write
+// their FP64 gradient, 256 pixels at a time.  A pixel of several blocks belongs to the
+// first of those halos, whatever the launch (side `size0` for the first n0 halos): the
+// blocks that come before and touch the 256 pixels' rows are listed in LDS, 256 halos
+// at a time, and the pixels that are left are packed into whole waves.  Bound by FP64
+// issue (6730^2 x 702: 428 us in both launches, 426 without the lists, which
+// repeated shared pixels: 100 x 64 x 702 504 us a call, now 320; 300 x 211 x 100
+// with blocks of 400 375, now 98).
+__global__ __launch_bounds__(256) void k_mix_blocks(int np, GridDesc g, int p0, int size, int n0, int size0,
+                                                    const int2* __restrict__ corner, const double* __restrict__ tab64,
+                                                    double* __restrict__ ax, double* __restrict__ ay,
+                                                    unsigned char* __restrict__ mask, const MixState* __restrict__ st)
 {
+    __shared__ int4 touch[256];  // blocks [x, z) x [y, w)
+    __shared__ unsigned short left[256];
+    __shared__ int s_n[4];
     if (st->status != kStatusOk) return;
-    const int p = p0 + blockIdx.x;
-    const long long size = size_;
-    const long long ki = llround((pot.x[p] - g.x0) / g.h), kj = llround((pot.y[p] - g.y0) / g.h);
-    long long i0 = ki - size / 2, i1 = ki - size / 2 + size, j0 = kj - size / 2, j1 = kj - size / 2 + size;
-    i0 = i0 < 0 ? 0 : i0;
-    j0 = j0 < 0 ? 0 : j0;
-    i1 = i1 > g.nx ? g.nx : i1;
-    j1 = j1 > g.ny ? g.ny : j1;
+    const int p = p0 + blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
+    const int2 c = corner[p];
+    const int i0 = max(c.x, 0), j0 = max(c.y, 0), i1 = min(c.x + size, g.nx), j1 = min(c.y + size, g.ny);
     if (i0 >= i1 || j0 >= j1) return;
     const unsigned w = (unsigned)(i1 - i0), n = w * (unsigned)(j1 - j0);
-    for (unsigned q = blockIdx.y * 256 + threadIdx.x; q < n; q += gridDim.y * 256) {
-        const int j = (int)(j0 + q / w), i = (int)(i0 + q % w);
-        const double t1 = node_coord(g.x0, i, g.h), t2 = node_coord(g.y0, j, g.h);
-        double s1 = 0.0, s2 = 0.0;
+    // entries of the workgroup's lists: `in` of every thread in order
+    auto pack = [&](bool in, int& total) {
+        const unsigned long long m = __ballot(in);
+        if (lane == 0) s_n[wave] = __popcll(m);
+        __syncthreads();
+        int at = __popcll(m & ((1ull << lane) - 1ull));
+        for (int k = 0; k < wave; k++) at += s_n[k];
+        total = s_n[0] + s_n[1] + s_n[2] + s_n[3];
+        return at;
+    };
+    for (unsigned q0 = blockIdx.y * 256; q0 < n; q0 += gridDim.y * 256) {
+        const unsigned q = q0 + threadIdx.x;
+        const int j = j0 + (int)(q / w), i = i0 + (int)(q % w);
+        const int ja = j0 + (int)(q0 / w), jb = j0 + (int)((min(q0 + 256u, n) - 1) / w);  // rows of the 256
+        bool mine = q < n;
+        for (int b = 0; b < p && __syncthreads_or(mine); b += 256) {
+            const int h = b + (int)threadIdx.x;
+            int4 t = make_int4(0, 0, 0, 0);
+            bool in = false;
+            if (h < p) {
+                const int2 d = corner[h];
+                const int sz = h < n0 ? size0 : size;
+                t = make_int4(d.x, d.y, d.x + sz, d.y + sz);
+                in = t.x < i1 && t.z > i0 && t.y <= jb && t.w > ja;
+            }
+            int cnt;
+            const int at = pack(in, cnt);
+            if (in) touch[at] = t;
+            __syncthreads();
+            for (int k = 0; k < cnt && mine; k++)
+                mine = !(i >= touch[k].x && i < touch[k].z && j >= touch[k].y && j < touch[k].w);
+        }
+        int cnt;
+        const int at = pack(mine, cnt);
+        if (mine) left[at] = (unsigned short)threadIdx.x;
+        __syncthreads();
+        if ((int)threadIdx.x < cnt) {
+            const unsigned r = q0 + left[threadIdx.x];
+            const int jr = j0 + (int)(r / w), ir = i0 + (int)(r % w);
+            const double t1 = node_coord(g.x0, ir, g.h), t2 = node_coord(g.y0, jr, g.h);
+            double s1 = 0.0, s2 = 0.0;
 #pragma unroll 4
-        for (int m = 0; m < pot.n; m++) sie64_add(tab64 + (size_t)m * T64_STRIDE, t1, t2, s1, s2);
-        const size_t o = (size_t)j * g.nx + i;
-        ax[o] = s1;
-        ay[o] = s2;
-        mask[o] = 1;
+            for (int m = 0; m < np; m++) sie64_add(tab64 + (size_t)m * T64_STRIDE, t1, t2, s1, s2);
+            const size_t o = (size_t)jr * g.nx + ir;
+            ax[o] = s1;
+            ay[o] = s2;
+            mask[o] = 1;
+        }
+        __syncthreads();  // the lists are read
     }
 }
 
@@ -392,7 +442,7 @@ size_t mixed_counts(const GridDesc& g) { return (size_t)scan_grid(g).x * scan_gr
 hipError_t launch_mixed(const PotPtrs& pot, const GridDesc& g, const MixedLaunch& ml, hipStream_t s)
 {
     const long long n_nodes = (long long)g.nx * g.ny;
-    k_mix_prep<<<1, 256, 0, s>>>(pot, g, ml.tab64, ml.tab32, ml.bterm, ml.st);
+    k_mix_prep<<<1, 256, 0, s>>>(pot, g, ml.n_cluster, ml.pc, ml.pg, ml.tab64, ml.tab32, ml.bterm, ml.corner, ml.st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // FP32 field layout: two columns of four rows per thread once there are
@@ -413,7 +463,8 @@ hipError_t launch_mixed(const PotPtrs& pot, const GridDesc& g, const MixedLaunch
         if (n <= 0 || size <= 0) return hipSuccess;
         const long long px = (long long)std::min(size, g.nx) * std::min(size, g.ny);
         const unsigned ny = (unsigned)std::min(std::max(1ll, 16384ll / n), (px + 255) / 256);
-        k_mix_blocks<<<dim3((unsigned)n, ny), 256, 0, s>>>(pot, g, p0, size, ml.tab64, ml.ax, ml.ay, ml.mask, ml.st);
+        k_mix_blocks<<<dim3((unsigned)n, ny), 256, 0, s>>>(pot.n, g, p0, size, ml.n_cluster, ml.pc, ml.corner, ml.tab64,
+                                                          ml.ax, ml.ay, ml.mask, ml.st);
         return hipGetLastError();
     };
     if ((e = blocks(0, ml.n_cluster, ml.pc)) != hipSuccess) return e;
