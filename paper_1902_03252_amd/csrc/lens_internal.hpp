@@ -119,7 +119,7 @@ struct TileCost {
 };
 constexpr TileCost kTileCost32 = {75.0, 116.0, 64.0, 60.0, 3.6};
 constexpr TileCost kTileCost64 = {200.0, 180.0, 256.0, 200.0, 5.1};
-int tile_side_for(double nodes, double total, int np, const TileCost& k);
+int tile_side_for(double nodes, double total, int np, const TileCost& k, double* cycles = nullptr);
 bool tiles_too_thin(const GridDesc& g, int side, int least);
 constexpr int kThinNodes32 = 160, kThinNodes64 = 352;  // nodes per tile below which it is too thin
 int batch_side(const GridDesc& g, int np, double total, bool fp32);
@@ -222,7 +222,8 @@ hipError_t launch_hmc_small(double* state, int n, const ObsPtrs& obs, const doub
 // Device state of the mixed-precision SIE gradient (set by its first kernel).
 struct MixState {
     int status;
-    int pad[3];
+    unsigned n_crit;  // criteria pixels
+    int pad[2];
 };
 
 // Arguments of the mixed-precision SIE gradient.

@@ -1141,8 +1141,9 @@ bool tiles_too_thin(const GridDesc& g, int side, int least)
     return g.nx >= 512 && (long long)g.nx * g.ny < least * tiles;
 }
 
-// The best side for a grid of `nodes` nodes in a launch of `total` nodes.
-int tile_side_for(double nodes, double total, int np, const TileCost& k)
+// The best side for a grid of `nodes` nodes in a launch of `total` nodes, and what the
+// launch takes with it.
+int tile_side_for(double nodes, double total, int np, const TileCost& k, double* cycles)
 {
     int best = 0;
     double cost = 0.0;
@@ -1161,6 +1162,7 @@ int tile_side_for(double nodes, double total, int np, const TileCost& k)
             cost = c;
         }
     }
+    if (cycles) *cycles = cost;
     return best;
 }
 

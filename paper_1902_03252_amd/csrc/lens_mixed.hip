@@ -14,8 +14,9 @@
 //   k_mix_blocks   FP64 gradient of the cluster-scale halos' blocks, then of the
 //                  others' (two launches), marked 1
 //   k_mix_scan     criteria on the field so far, pixels marked 2; counts
-//   k_mix_dp       FP64 gradient of the pixels marked 2, by tiles
 //   k_mix_stats    counts and status to the caller's stats
+//   k_mix_pixels   FP64 gradient of the pixels marked 2 one by one, or
+//   k_mix_dp       by tiles
 // The FP32 field decides which pixels the criteria take, so it is summed over
 // the potentials at every pixel; the FP64 gradient of the criteria pixels (a
 // fifth of the benchmark image) goes through the tiled field: 0.4 ms against 4.2
@@ -191,15 +192,23 @@ __global__ __launch_bounds__(256) void k_mix_field32(const float* __restrict__ t
 
 // 1/sqrt(x) in FP64 for a positive normal x: the hardware estimate (relative
 // error below 2^-24 on gfx950, measured) refined by one Newton-Raphson step
-// y <- y (3/2 - x y^2 / 2), which squares the error: ~2^-47 relative.
+// y <- y (3/2 - x y^2 / 2), which squares the error: ~2^-47 relative.  FULL: with
+// the next term of the series, y (1 + e/2 + 3 e^2/8), e = 1 - x y^2: ~1 ulp, as the
+// tiles' terms.
+template <bool FULL>
 __device__ __forceinline__ double rsq64(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
+    if constexpr (FULL) {
+        const double e = fma(-(x * y), y, 1.0);
+        return fma(y * e, fma(0.375, e, 0.5), y);
+    }
     return fma(y, fma(-0.5 * x * y, y, 0.5), y);
 }
 
 // FP64 SIE contribution of table row t at (t1, t2): alpha += K m / R, m = M d,
 // R^2 = d . m, clamped below at 1e-300 (the centre, where m = 0, contributes 0).
+template <bool FULL>
 __device__ __forceinline__ void sie64_add(const double* __restrict__ t, double t1, double t2, double& s1,
                                           double& s2)
 {
@@ -207,9 +216,23 @@ __device__ __forceinline__ void sie64_add(const double* __restrict__ t, double t
     const double m1 = fma(t[T64_A], d1, t[T64_B] * d2);
     const double m2 = fma(t[T64_B], d1, t[T64_C] * d2);
     const double R2 = fmax(fma(d1, m1, d2 * m2), 1e-300);
-    const double kr = t[T64_K] * rsq64(R2);
+    const double kr = t[T64_K] * rsq64<FULL>(R2);
     s1 = fma(kr, m1, s1);
     s2 = fma(kr, m2, s2);
+}
+
+// FP64 gradient of pixel (i, j) by the sum over all halos.
+template <bool FULL>
+__device__ __forceinline__ void pixel64(const double* __restrict__ tab64, int np, const GridDesc& g, int i, int j,
+                                        double* __restrict__ ax, double* __restrict__ ay)
+{
+    const double t1 = node_coord(g.x0, i, g.h), t2 = node_coord(g.y0, j, g.h);
+    double s1 = 0.0, s2 = 0.0;
+#pragma unroll 4
+    for (int m = 0; m < np; m++) sie64_add<FULL>(tab64 + (size_t)m * T64_STRIDE, t1, t2, s1, s2);
+    const size_t o = (size_t)j * g.nx + i;
+    ax[o] = s1;
+    ay[o] = s2;
 }
 
 // The FP64 blocks of halos [p0, p0 + gridDim.x), side `size`, clipped to the grid: the
@@ -274,14 +297,8 @@ __global__ __launch_bounds__(256) void k_mix_blocks(int np, GridDesc g, int p0, 
         if ((int)threadIdx.x < cnt) {
             const unsigned r = q0 + left[threadIdx.x];
             const int jr = j0 + (int)(r / w), ir = i0 + (int)(r % w);
-            const double t1 = node_coord(g.x0, ir, g.h), t2 = node_coord(g.y0, jr, g.h);
-            double s1 = 0.0, s2 = 0.0;
-#pragma unroll 4
-            for (int m = 0; m < np; m++) sie64_add(tab64 + (size_t)m * T64_STRIDE, t1, t2, s1, s2);
-            const size_t o = (size_t)jr * g.nx + ir;
-            ax[o] = s1;
-            ay[o] = s2;
-            mask[o] = 1;
+            pixel64<false>(tab64, np, g, ir, jr, ax, ay);
+            mask[(size_t)jr * g.nx + ir] = 1;
         }
         __syncthreads();  // the lists are read
     }
@@ -386,17 +403,67 @@ struct CriteriaSink {
     }
 };
 
-// FP64 gradient of the criteria pixels: the tiled FP64 field (lens_tiles.hpp) on
-// the tiles that hold any (6730^2 x 702, 8.8M pixels: 445 us against 4117 pixel by
-// pixel).
+// FP64 gradient of the criteria pixels one by one, where the image has no more than
+// `few` of them: a workgroup takes every so-many-th run of 512 pixels and collects their
+// criteria pixels in LDS first, so that whole waves work on them.  As many workgroups
+// as give each two waves of them take part, for balance, and enough to read the mask.
+constexpr int kRun = 512;
+__global__ __launch_bounds__(256) void k_mix_pixels(const double* __restrict__ tab64, int np, GridDesc g, unsigned few,
+                                                    const unsigned char* __restrict__ mask, double* __restrict__ ax,
+                                                    double* __restrict__ ay, const MixState* __restrict__ st)
+{
+    __shared__ struct {
+        unsigned list[kRun + 256];
+        unsigned n;
+    } L;
+    if (st->status != kStatusOk || st->n_crit == 0 || st->n_crit > few) return;
+    const unsigned nn = (unsigned)g.nx * (unsigned)g.ny, runs = (nn + kRun - 1) / kRun, t = threadIdx.x;
+    const unsigned step = min(gridDim.x, max(1024u, st->n_crit / 128));
+    if (blockIdx.x >= step) return;
+    if (t == 0) L.n = 0;
+    __syncthreads();
+    for (unsigned r = blockIdx.x; r < runs; r += step) {
+#pragma unroll
+        for (int k = 0; k < kRun / 256; k++) {
+            const unsigned q = r * kRun + k * 256 + t;
+            const bool in = q < nn && mask[q] == 2;
+            const unsigned long long m = __ballot(in);
+            if (m == 0) continue;
+            unsigned at = 0;
+            if (lane_id() == 0) at = atomicAdd(&L.n, (unsigned)__popcll(m));
+            at = (unsigned)__builtin_amdgcn_readfirstlane((int)at) +
+                 __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            if (in) L.list[at] = q;
+        }
+        __syncthreads();
+        const unsigned n = L.n;
+        const bool last = r + step >= runs;
+        const unsigned done = last ? n : n & ~255u;
+        for (unsigned e = t; e < done; e += 256) {
+            const unsigned q = L.list[e], j = q / (unsigned)g.nx;
+            pixel64<true>(tab64, np, g, (int)(q - j * (unsigned)g.nx), (int)j, ax, ay);
+        }
+        __syncthreads();
+        if (done) {  // uniform: the rest, fewer than 256, to the front
+            const unsigned keep = t < n - done ? L.list[done + t] : 0u;
+            __syncthreads();
+            if (t < n - done) L.list[t] = keep;
+            if (t == 0) L.n = n - done;
+            __syncthreads();
+        }
+    }
+}
+
+// The same by the tiled FP64 field (lens_tiles.hpp) on the tiles that hold any, where
+// there are more (6730^2 x 702, 8.8M pixels: 440 us against 4117 pixel by pixel).
 template <int T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_mix_dp(
-    const double* __restrict__ tab64, const float* __restrict__ tab32, int np, GridDesc g, int ntx,
+    const double* __restrict__ tab64, const float* __restrict__ tab32, int np, GridDesc g, int ntx, unsigned few,
     const unsigned char* __restrict__ mask, double* __restrict__ ax, double* __restrict__ ay,
     const MixState* __restrict__ st)
 {
     __shared__ typename Tile64<T>::Lds lds;
-    if (st->status != kStatusOk) return;
+    if (st->status != kStatusOk || st->n_crit <= few) return;
     const int tj = blockIdx.x / ntx, ti = blockIdx.x - tj * ntx;
     const int i = ti * T + (int)(threadIdx.x % T);
     bool any = false;
@@ -407,7 +474,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 }
 
 // Totals and status.
-__global__ __launch_bounds__(1024) void k_mix_stats(const MixState* __restrict__ st, const uint2* __restrict__ counts,
+__global__ __launch_bounds__(1024) void k_mix_stats(MixState* __restrict__ st, const uint2* __restrict__ counts,
                                                     int n, long long* __restrict__ stats)
 {
     __shared__ unsigned long long s_n[2];
@@ -427,6 +494,7 @@ __global__ __launch_bounds__(1024) void k_mix_stats(const MixState* __restrict__
         stats[1] = ok ? (long long)s_n[1] : 0;
         stats[2] = ok ? (long long)(s_n[0] + s_n[1]) : 0;
         stats[3] = st->status;
+        st->n_crit = ok ? (unsigned)s_n[1] : 0u;
     }
 }
 
@@ -472,20 +540,34 @@ hipError_t launch_mixed(const PotPtrs& pot, const GridDesc& g, const MixedLaunch
     const dim3 sg = scan_grid(g);
     k_mix_scan<<<sg, 256, 0, s>>>(ml.ax, ml.ay, g, ml.t12, ml.t34, ml.mask, ml.counts, ml.st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int side = tile_side_for((double)n_nodes, (double)n_nodes, pot.n, kTileCost64);
+    k_mix_stats<<<1, 1024, 0, s>>>(ml.st, ml.counts, (int)mixed_counts(g), ml.stats);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // Criteria pixels one by one where that is cheaper (their number is known on the
+    // device only, hence both launches, of which one does the work): kPixel cycles per 64
+    // of them and halo, against the tiles' cost and kTile cycles per 64 of them for the
+    // masked loads and stores (whole calls, us, by tiles / one by one: 3000^2 x 3 with
+    // 7.8 M of them 257 / 111, 1500^2 x 15 with 1.9 M 98 / 69, 1200 x 900 x 200 with 4000
+    // 258 / 214 and with 0.67 M 270 / 330).  More halos than a tile's lists hold: one by
+    // one (2000^2 x 2060 12200 / 7570).
+    double cost;
+    const int side = tile_side_for((double)n_nodes, (double)n_nodes, pot.n, kTileCost64, &cost);
+    constexpr double kPixel = 125.0, kTile = 2500.0;
+    const double each = (kPixel * pot.n - kTile) / (64.0 * 1024.0);
+    const bool all = pot.n > kTileMaxP || each * (double)n_nodes <= cost;
+    const unsigned few = all ? ~0u : (unsigned)(cost / each);
+    k_mix_pixels<<<(unsigned)std::min<long long>((n_nodes + kRun - 1) / kRun, 8192), 256, 0, s>>>(
+        ml.tab64, pot.n, g, few, ml.mask, ml.ax, ml.ay, ml.st);
+    if ((e = hipGetLastError()) != hipSuccess || all) return e;
     auto dp = [&](auto t) {
         constexpr int T = decltype(t)::value;
         const int ntx = (g.nx + T - 1) / T;
-        k_mix_dp<T><<<(unsigned)(ntx * ((g.ny + T - 1) / T)), 256, 0, s>>>(ml.tab64, ml.tab32, pot.n, g, ntx, ml.mask,
+        k_mix_dp<T><<<(unsigned)(ntx * ((g.ny + T - 1) / T)), 256, 0, s>>>(ml.tab64, ml.tab32, pot.n, g, ntx, few, ml.mask,
                                                                           ml.ax, ml.ay, ml.st);
         return hipGetLastError();
     };
-    e = side == 32   ? dp(std::integral_constant<int, 32>())
-        : side == 64 ? dp(std::integral_constant<int, 64>())
-                     : dp(std::integral_constant<int, 128>());
-    if (e != hipSuccess) return e;
-    k_mix_stats<<<1, 1024, 0, s>>>(ml.st, ml.counts, (int)mixed_counts(g), ml.stats);
-    return hipGetLastError();
+    return side == 32   ? dp(std::integral_constant<int, 32>())
+           : side == 64 ? dp(std::integral_constant<int, 64>())
+                        : dp(std::integral_constant<int, 128>());
 }
 
 }  // namespace lens

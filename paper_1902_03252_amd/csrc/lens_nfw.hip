@@ -231,7 +231,6 @@ __global__ __launch_bounds__(256) void k_nfw64(const double* __restrict__ t64, i
 // the same criterion with core 0 holds.  The profile's logarithms and roots bound
 // it, by vector issue: 4096^2 x 702 in FP32 21.6 ms by the direct sum, 0.35 by tiles.
 struct NfwProfile {
-    static constexpr int kMin64 = 0;  // (the profile's own rounding exceeds the interpolation's)
     const double* t64;
     const float* t32;
 
@@ -248,7 +247,7 @@ struct NfwProfile {
                                            double e2, double& s1, double& s2) const
     {
         double r1 = 0.0, r2 = 0.0;  // two partial sums, taken in turn
-        for_list(list + k0, true, k1 - k0, [&](int p) {
+        for_list(list + k0, k1 - k0, [&](int p) {
             const double* c = t64 + (size_t)p * N64_STRIDE;
             const double d1 = (c1 - c[N64_XC]) + e1, d2 = (c2 - c[N64_YC]) + e2;
             const double m1 = fma(c[N64_A], d1, c[N64_B] * d2), m2 = fma(c[N64_B], d1, c[N64_C] * d2);

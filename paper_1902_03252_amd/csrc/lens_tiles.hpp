@@ -118,8 +118,8 @@ __device__ __forceinline__ bool tile_far(float dx, float dy, float A, float B, f
     return qv >= A * lim && qh >= C * lim && A > 0.0f && C > 0.0f;
 }
 
-// Near/far lists of one tile: near potentials first (in order), then the far
-// ones (in order).  Called by all NTH threads of the workgroup (two
+// Near/far lists of one tile of at most kTileMaxP potentials: near ones first (in
+// order), then the far ones (in order).  Called by all NTH threads of the workgroup (two
 // barriers); isfar(p) is evaluated once per potential.
 struct TileLists {
     unsigned long long near[kTileMaxP / 64];
@@ -156,15 +156,14 @@ __device__ __forceinline__ void tile_lists(TileLists& L, int np, F&& isfar)
     __syncthreads();
 }
 
-// Runs f(p) for the list entries [0, n), or for p = 0 .. n - 1 without a list,
-// with a wave-uniform p; all 64 lanes call it.  64 entries are loaded at a
-// time, one per lane.
+// Runs f(p) for the list entries [0, n) with a wave-uniform p; all 64 lanes call
+// it.  64 entries are loaded at a time, one per lane.
 template <class F>
-__device__ __forceinline__ void for_list(const unsigned short* list, bool has_list, int n, F&& f)
+__device__ __forceinline__ void for_list(const unsigned short* list, int n, F&& f)
 {
     for (int b = 0; b < n; b += 64) {
         const int cnt = min(64, n - b);
-        const int mine = has_list && lane_id() < cnt ? (int)list[b + lane_id()] : b + lane_id();
+        const int mine = lane_id() < cnt ? (int)list[b + lane_id()] : 0;
         for (int k = 0; k < cnt; k++) f(__builtin_amdgcn_readlane(mine, k));
     }
 }
@@ -427,7 +426,6 @@ __device__ __forceinline__ void store_unit(const V* s, V* __restrict__ out, int 
 
 // The isothermal family of the tables (tab64, tab32) as a tile's summand.
 struct IsoProfile {
-    static constexpr int kMin64 = kTileMinP64;  // below, an FP64 tile takes every potential as near
     const double* tab64;
     const float* tab32;
 
@@ -555,10 +553,8 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T, NW>::Lds& L, cons
     constexpr float hw = 0.5f * (T - 1);
     const int lane = lane_id(), wt = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float xc = (float)i0 + hw, yc = (float)j0 + hw;
-    // beyond the lists' capacity every potential counts as near, in order
-    const bool all = np > kTileMaxP;
-    if (!all) tile_lists<NTH>(L.lists, np, [&](int p) { return prof.far(p, xc, yc, hw, kFarC32); });
-    const int nn = all ? np : __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
+    tile_lists<NTH>(L.lists, np, [&](int p) { return prof.far(p, xc, yc, hw, kFarC32); });
+    const int nn = __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
     {
         const double c1 = g.x0 + (double)xc * g.h, c2 = g.y0 + (double)yc * g.h, half = (double)hw * g.h;
         double s1 = 0.0, s2 = 0.0;
@@ -663,7 +659,7 @@ __device__ __forceinline__ void tile32_body(typename Tile32<T, NW>::Lds& L, cons
 #pragma unroll
         for (int k = 0; k < NK; k++) fi[k] = (float)(i0 + cu + unit_col<NK>(k));
         const float fj = (float)(j0 + ru + unit_row<NK>());
-        for_list(L.lists.list, !all, nn, [&](int p) { prof.template near32<NK>(p, fi, fj, sx, sy); });
+        for_list(L.lists.list, nn, [&](int p) { prof.template near32<NK>(p, fi, fj, sx, sy); });
 #pragma unroll
         for (int k = 0; k < NK; k++) {
             sx[k] += cx;
@@ -725,9 +721,8 @@ __device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P&
     constexpr float hw = 0.5f * (T - 1);
     const int tid = threadIdx.x, lane = lane_id(), wt = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float xc = (float)i0 + hw, yc = (float)j0 + hw;
-    const bool all = np > kTileMaxP || np < P::kMin64;
-    if (!all) tile_lists(L.lists, np, [&](int p) { return prof.far(p, xc, yc, hw, kFarC64); });
-    const int nn = all ? np : __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
+    tile_lists(L.lists, np, [&](int p) { return prof.far(p, xc, yc, hw, kFarC64); });
+    const int nn = __builtin_amdgcn_readfirstlane(L.lists.n_near), nf = np - nn;
     const int lo = tid & 15, hi = tid >> 4;
     // The polynomial is in (t - c)/half, t the nodes' rounded FP64 coordinates
     // (node_coord) and c the tile centre's: nodes then keep their own position
@@ -843,7 +838,7 @@ __device__ __forceinline__ void tile64_body(typename Tile64<T>::Lds& L, const P&
             }
 #pragma unroll
             for (int k = 0; k < NK; k++) t1[k] = node_coord(g.x0, i0 + cu + unit_col<NK>(k), g.h);
-            for_list(L.lists.list, !all, nn, [&](int p) { prof.template near64<NK>(p, t1, t2, sx, sy); });
+            for_list(L.lists.list, nn, [&](int p) { prof.template near64<NK>(p, t1, t2, sx, sy); });
 #pragma unroll
             for (int k = 0; k < NK; k++) {
                 sx[k] += r0;
