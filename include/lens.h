@@ -330,15 +330,15 @@ int lens_mh_step_batched(lens_ctx *ctx, double *states, int32_t n_chains, int32_
  * the largest over the samples and P the rounded-up mean.  A call whose
  * opts->tile or opts->field_npl is 0 takes the table's choice for its bucket
  * when there is one, else the fixed default (field_npl acts on the direct field
- * only: where the field is evaluated by tiles, as in every batch, its candidates
- * run the same kernel).  lens_create merges the JSON file
+ * of a single call only).  lens_create merges the JSON file
  * named by the environment variable LENS_AUTOTUNE_CACHE, if it exists and
  * parses (otherwise the table starts empty).  Entries carry the GPU
  * architecture (e.g. gfx950); a file written on another one adds nothing. */
 
 /* Times the candidates on the caller's problem -- the default configuration
- * first, then the other nodes per thread 1, 2, 4, 8 (MIXED only) with tile
- * shape 1, then the other tile shapes with the best of those -- each by one
+ * first, then the other nodes per thread 1, 2, 4, 8 (MIXED with a direct field
+ * only; otherwise the bucket's entry keeps its field_npl, or gets the default) with
+ * tile shape 1, then the other tile shapes with the best of those -- each by one
  * warm-up and `reps` (1..100) timed calls (median, HIP events on `stream`).  A
  * candidate replaces the best so far only when it is more than 2 % faster
  * (timing noise keeps the default).  Records the choice in the table and
@@ -351,7 +351,7 @@ int lens_autotune_chi2(lens_ctx *ctx, const lens_potentials *pot, const lens_gri
                        const lens_chi2_opts *opts, lens_chi2_out *out, int32_t reps, int32_t *tile,
                        int32_t *field_npl, hipStream_t stream);
 
-/* The same for lens_image_chi2_batched (nodes per thread 1, 2, 4). */
+/* The same for lens_image_chi2_batched (tile shapes only). */
 int lens_autotune_chi2_batched(lens_ctx *ctx, const lens_potentials *all, int32_t n_samples,
                                const int32_t *pot_off, const lens_grid *grids, const lens_obs *obs,
                                const lens_chi2_opts *opts, lens_batch_out *out, int32_t reps, int32_t *tile,

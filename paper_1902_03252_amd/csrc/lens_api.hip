@@ -301,6 +301,14 @@ int lens_default_field_npl(int nx, int ny)
     return field_npl(g);
 }
 
+bool lens_field_tiled(int nx, int ny, int np, lens_precision prec)
+{
+    GridDesc g = {};
+    g.nx = nx;
+    g.ny = ny;
+    return tiled_side(g, np, prec != LENS_FP64) != 0;
+}
+
 extern "C" {
 
 int lens_create(lens_ctx** ctx, int device)

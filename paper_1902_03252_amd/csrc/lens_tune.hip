@@ -334,15 +334,17 @@ int time_call(Call call, int reps, hipStream_t s, hipEvent_t a, hipEvent_t b, do
 }
 
 // Tries the default configuration first, then the other nodes per thread
-// (mixed only) with the default tile, then the other tile shapes with the
-// best nodes per thread.  A candidate replaces the best so far only when it is
+// (`layouts`: where the call's field has them) with the default tile, then the
+// other tile shapes with the best nodes per thread.  Without layouts the bucket's
+// nodes per thread stay, or the default is recorded: a call of the same bucket may
+// have a direct field.  A candidate replaces the best so far only when it is
 // faster by more than kMargin, so timing noise leaves the default in place;
 // records and returns the choice.
 constexpr double kMargin = 0.02;
 
 template <typename Run>
-int tune(lens_ctx* ctx, int prec, int batched, int n_log2, int p_log2, int default_npl, int reps, hipStream_t s,
-         Run run, int32_t* tile_out, int32_t* npl_out)
+int tune(lens_ctx* ctx, int prec, int batched, int n_log2, int p_log2, int default_npl, bool layouts, int reps,
+         hipStream_t s, Run run, int32_t* tile_out, int32_t* npl_out)
 {
     if (reps < 1 || reps > 100) return LENS_ERR_INVALID;
     TuneTable* table = lens_ctx_tune(ctx);
@@ -356,7 +358,9 @@ int tune(lens_ctx* ctx, int prec, int batched, int n_log2, int p_log2, int defau
     int rc = LENS_OK;
     if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) rc = LENS_ERR_DEVICE;
     const bool mixed = prec == LENS_MIXED;
-    int best_tile = 1, best_npl = mixed ? default_npl : 0;
+    int best_tile = 1, best_npl = mixed ? default_npl : 0, old_tile, old_npl;
+    if (mixed && !layouts && tune_lookup(table, prec, batched, n_log2, p_log2, &old_tile, &old_npl) && old_npl)
+        best_npl = old_npl;
     double best = INFINITY;
     auto trial = [&](int tile, int npl) {
         if (rc) return;
@@ -374,11 +378,10 @@ int tune(lens_ctx* ctx, int prec, int batched, int n_log2, int p_log2, int defau
         }
     };
     trial(best_tile, best_npl);
-    if (mixed) {  // FP32 field layouts: nodes of one row, then blocks of rows x columns
+    if (mixed && layouts) {  // FP32 field layouts: nodes of one row, then blocks of rows x columns
         const int npls[9] = {1, 2, 4, 8, 0x21, 0x22, 0x24, 0x41, 0x42};
         for (int k = 0; k < 9; k++)
-            if (npls[k] != default_npl && (batched ? bfield_code_ok(npls[k]) : field_code_ok(npls[k])))
-                trial(1, npls[k]);
+            if (npls[k] != default_npl) trial(1, npls[k]);
     }
     const int npl = best_npl;
     for (int tile = 2; tile <= 4; tile++) trial(tile, npl);
@@ -419,8 +422,8 @@ int lens_autotune_chi2(lens_ctx* ctx, const lens_potentials* pot, const lens_gri
             o.field_npl = npl;
             return lens_image_chi2(ctx, pot, grid, obs, &o, out, stream);
         };
-        return tune(ctx, opts->prec, 0, n_log2, p_log2, lens_default_field_npl(grid->nx, grid->ny), reps, stream, run,
-                    tile, field_npl);
+        return tune(ctx, opts->prec, 0, n_log2, p_log2, lens_default_field_npl(grid->nx, grid->ny),
+                    !lens_field_tiled(grid->nx, grid->ny, pot->n, opts->prec), reps, stream, run, tile, field_npl);
     } catch (...) {
         return LENS_ERR_DEVICE;
     }
@@ -442,7 +445,8 @@ int lens_autotune_chi2_batched(lens_ctx* ctx, const lens_potentials* all, int32_
             o.field_npl = npl;
             return lens_image_chi2_batched(ctx, all, n_samples, pot_off, grids, obs, &o, out, stream);
         };
-        return tune(ctx, opts->prec, 1, tune_log2(side), tune_log2(mean_p), 0x41, reps, stream, run, tile, field_npl);
+        return tune(ctx, opts->prec, 1, tune_log2(side), tune_log2(mean_p), 0x41, false, reps, stream, run, tile,
+                    field_npl);
     } catch (...) {
         return LENS_ERR_DEVICE;
     }

@@ -32,3 +32,4 @@ lens::TuneTable* lens_ctx_tune(lens_ctx* ctx);
 int lens_ctx_device(lens_ctx* ctx);
 int lens_ctx_timing(lens_ctx* ctx);  // whether field-kernel timing is on
 int lens_default_field_npl(int nx, int ny);  // FP32 field nodes per thread of an untuned single call
+bool lens_field_tiled(int nx, int ny, int np, lens_precision prec);  // a single call's field has no such layout
