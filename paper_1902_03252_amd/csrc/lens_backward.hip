@@ -791,8 +791,12 @@ __global__ __launch_bounds__(1024) void k_hmc_small(double* __restrict__ state, 
 }
 
 // Whether k_hmc_small takes a model: its LDS fits 64 KB and its work is small
-// enough for one compute unit (about 2.2 us + 2.1 us per 1024 image-potential
-// terms a gradient, against 17 us for the two launches of the general path).
+// enough for one compute unit (with systems of a few images about 2.2 us + 2.1 us per
+// 1024 image-potential terms a gradient, against 17 us for the two launches of the
+// general path).  Both walk a system's images in one thread per image or system, so
+// large systems do not move the line: one of 900 images with 3 potentials, 10
+// leapfrogs, 1871 us here and 4706 by the general path; 128 potentials with 16
+// systems of 3 images, at the limit, 185 and 192.
 bool hmc_small_fits(int n, const ObsPtrs& obs)
 {
     return obs.n_img > 0 && (long long)n * obs.n_img <= 6144 && obs.n_sys <= 4096 &&

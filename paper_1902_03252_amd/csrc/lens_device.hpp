@@ -226,12 +226,6 @@ __device__ __forceinline__ void alpha64_all_wg(const double* __restrict__ tab, i
     }
 }
 
-__device__ __forceinline__ void alpha64_all_wg(const double* __restrict__ tab, int np, double t1, double t2,
-                                               double& s1, double& s2)
-{
-    alpha64_all_wg<1>(tab, np, &t1, t2, &s1, &s2);
-}
-
 // grad Psi at one point with the potentials split over the 64 lanes of a
 // wave and a fixed butterfly reduction (deterministic).  All lanes return the
 // same value.
