@@ -104,16 +104,18 @@ __device__ __forceinline__ void wave_lds_sync()
 // large terms when eps is near 1 and the centre far away along the long axis: its
 // rounding (a unit roundoff of each coefficient, two of the offset, counted twice
 // in the square, and four of the operations, on the sum of the terms' sizes; 8 u,
-// taken as 10) is subtracted, so that a potential it could decide stays near.
+// taken as 10) is subtracted, so that a potential it could decide stays near.  (a^2,
+// which only adds, has its rounding in lim's factor; the bound stays finite, so that
+// terms beyond FP32 are far.)
 __device__ __forceinline__ bool tile_far(float dx, float dy, float A, float B, float C, float a2, float hw, float c)
 {
     const float t = fminf(fmaxf(-B * dx * __builtin_amdgcn_rcpf(C), dy - hw), dy + hw);
     const float u = fminf(fmaxf(-B * dy * __builtin_amdgcn_rcpf(A), dx - hw), dx + hw);
-    constexpr float r = 6e-7f;
+    constexpr float r = 6e-7f, big = 3e38f;
     const float v1 = A * dx * dx, v2 = 2.0f * B * dx * t, v3 = C * t * t;
     const float h1 = A * u * u, h2 = 2.0f * B * dy * u, h3 = C * dy * dy;
-    const float qv = (v1 + v2) + (v3 + a2) - r * ((v1 + fabsf(v2)) + (v3 + a2));
-    const float qh = (h1 + h2) + (h3 + a2) - r * ((h1 + fabsf(h2)) + (h3 + a2));
+    const float qv = ((v1 + v2) + (v3 + a2)) - fminf(r * ((v1 + fabsf(v2)) + v3), big);
+    const float qh = ((h1 + h2) + (h3 + a2)) - fminf(r * ((h1 + fabsf(h2)) + h3), big);
     const float lim = c * c * hw * hw * 1.0001f;
     return qv >= A * lim && qh >= C * lim && A > 0.0f && C > 0.0f;
 }

@@ -82,3 +82,20 @@ def test_flat_potentials_far_along_their_axes(lens, flat, nodes, prec):
     err = max(float(np.abs(a.double().cpu().numpy()[j, i] - b).max()) for a, b in zip(got, want))
     print(f"  1 - eps = {flat:.0e}, {nodes:.0e} nodes, {prec}: max err {err:.2e} (bar {tol:.2e})", flush=True)
     assert err <= tol
+
+
+@pytest.mark.parametrize("core,cut", [(1e19, np.inf), (3e19, np.inf), (1e20, 1e21), (1e25, np.inf)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_core_whose_square_leaves_fp32(lens, core, cut, prec):
+    """A core radius beyond the square root of FP32's largest number: far from every tile, its deflection in FP64."""
+    grid = S.Grid(-30.0, -29.0, 0.1, 601, 585)
+    g = np.random.default_rng(5)
+    prm = S.draw_galaxies(g, 60, 20.0)
+    prm[:, 3] = (5.0, -3.0, 0.3, 0.4, core, cut, 1000.0)
+    i, j = g.integers(0, grid.nx, 3000), g.integers(0, grid.ny, 3000)
+    want = alpha(prm, (grid.x0 + i * grid.h).astype(LD), (grid.y0 + j * grid.h).astype(LD))
+    got = lens.lens_deflect(dev(prm), grid, prec)
+    assert all(torch.isfinite(a).all() for a in got)
+    err = max(float(np.abs(a.double().cpu().numpy()[j, i] - b).max()) for a, b in zip(got, want))
+    kk = 4 * np.pi * (prm[6] / 299792.458) ** 2 * 206264.806 * (1 + prm[2]) / np.sqrt(1 - prm[2]) * 1.2
+    assert err <= (1e-10 if prec == "fp64" else 2.0 ** -24 * (64 + 60) * kk.sum())
