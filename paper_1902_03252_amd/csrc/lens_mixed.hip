@@ -121,8 +121,6 @@ __global__ __launch_bounds__(256) void k_mix_field32(const float* __restrict__ t
                                                      unsigned char* __restrict__ mask,
                                                      const MixState* __restrict__ st)
 {
-    __shared__ float4 srow[NR * 256];
-    __shared__ unsigned long long sclamp[4];
     const int j0 = blockIdx.y * NR;
     const int ib = blockIdx.x * 256 * NPL, i0 = ib + threadIdx.x * NPL;
     float fi[NPL], sx[NR * NPL], sy[NR * NPL];
@@ -131,45 +129,55 @@ __global__ __launch_bounds__(256) void k_mix_field32(const float* __restrict__ t
 #pragma unroll
     for (int q = 0; q < NR * NPL; q++) sx[q] = sy[q] = 0.0f;
     const bool bad = st->status != kStatusOk;
-    for (int p0 = 0; p0 < np && !bad; p0 += 256) {  // uniform over the launch
-        const int pc = min(256, np - p0);
-        if (p0 > 0) __syncthreads();  // the previous chunk has been read
-        bool clamp = false;
-        if ((int)threadIdx.x < pc) {
-            const float* c = tab32 + (size_t)(p0 + threadIdx.x) * T32_STRIDE;
-            const float A = c[T32_A], B = c[T32_B], C = c[T32_C];
+    if constexpr (NPL * NR == 1) {
+        // few waves: the plain loop over the potentials, whose loads the compiler groups
+        // (643 x 569 x 284: 53 us against 76 in runs by the clamp)
+        if (!bad)
+            pots_wg<T32_STRIDE, T32_CYH, T32_CYL, T32_B, T32_C>(
+                tab32, np, (float)j0, [&](const float* c, float4 rc) { sie32_pot<1, 1, true>(c, &rc, fi, sx, sy); });
+    } else {
+        __shared__ float4 srow[NR * 256];
+        __shared__ unsigned long long sclamp[4];
+        for (int p0 = 0; p0 < np && !bad; p0 += 256) {  // uniform over the launch
+            const int pc = min(256, np - p0);
+            if (p0 > 0) __syncthreads();  // the previous chunk has been read
+            bool clamp = false;
+            if ((int)threadIdx.x < pc) {
+                const float* c = tab32 + (size_t)(p0 + threadIdx.x) * T32_STRIDE;
+                const float A = c[T32_A], B = c[T32_B], C = c[T32_C];
 #pragma unroll
-            for (int r = 0; r < NR; r++) {
-                const float nyv = ((float)(j0 + r) - c[T32_CYH]) - c[T32_CYL];
-                srow[r * 256 + threadIdx.x] = make_float4(nyv, B * nyv, C * nyv, 0.0f);
+                for (int r = 0; r < NR; r++) {
+                    const float nyv = ((float)(j0 + r) - c[T32_CYH]) - c[T32_CYL];
+                    srow[r * 256 + threadIdx.x] = make_float4(nyv, B * nyv, C * nyv, 0.0f);
+                }
+                const float cx = c[T32_CXH], cy = c[T32_CYH], det = A * C - B * B, tr = A + C;
+                const bool inside = cx >= (float)(ib - 2) && cx <= (float)(ib + 256 * NPL + 1) && cy >= (float)(j0 - 2) &&
+                                    cy <= (float)(j0 + NR + 1);
+                // smallest eigenvalue of M h^2 >= det / tr; R^2 >= that / 4 outside
+                clamp = inside || !(det > 1e-4f * tr * tr) || !(det > 1e-27f * tr);
             }
-            const float cx = c[T32_CXH], cy = c[T32_CYH], det = A * C - B * B, tr = A + C;
-            const bool inside = cx >= (float)(ib - 2) && cx <= (float)(ib + 256 * NPL + 1) && cy >= (float)(j0 - 2) &&
-                                cy <= (float)(j0 + NR + 1);
-            // smallest eigenvalue of M h^2 >= det / tr; R^2 >= that / 4 outside
-            clamp = inside || !(det > 1e-4f * tr * tr) || !(det > 1e-27f * tr);
-        }
-        const unsigned long long b = __ballot(clamp);
-        if (lane_id() == 0) sclamp[threadIdx.x >> 6] = b;
-        __syncthreads();
-        for (int w = 0; w * 64 < pc; w++) {
-            const unsigned long long lw = sclamp[w];
-            const unsigned long long cl =
-                ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(lw >> 32)) << 32) |
-                (unsigned)__builtin_amdgcn_readfirstlane((int)lw);
-            const int n = min(64, pc - 64 * w);
-            auto add = [&](int q, auto clamped) {
-                const int p = 64 * w + q;
-                float4 rc[NR];
+            const unsigned long long b = __ballot(clamp);
+            if (lane_id() == 0) sclamp[threadIdx.x >> 6] = b;
+            __syncthreads();
+            for (int w = 0; w * 64 < pc; w++) {
+                const unsigned long long lw = sclamp[w];
+                const unsigned long long cl =
+                    ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(lw >> 32)) << 32) |
+                    (unsigned)__builtin_amdgcn_readfirstlane((int)lw);
+                const int n = min(64, pc - 64 * w);
+                auto add = [&](int q, auto clamped) {
+                    const int p = 64 * w + q;
+                    float4 rc[NR];
 #pragma unroll
-                for (int r = 0; r < NR; r++) rc[r] = srow[r * 256 + p];
-                sie32_pot<NPL, NR, decltype(clamped)::value>(tab32 + (size_t)(p0 + p) * T32_STRIDE, rc, fi, sx, sy);
-            };
-            for (int q = 0; q < n; q++) {  // a run without the clamp, then one with it
-                const unsigned long long rest = cl >> q;
-                const int stop = rest ? min(n, q + __builtin_ctzll(rest)) : n;
-                for (; q < stop; q++) add(q, std::false_type());
-                if (q < n) add(q, std::true_type());
+                    for (int r = 0; r < NR; r++) rc[r] = srow[r * 256 + p];
+                    sie32_pot<NPL, NR, decltype(clamped)::value>(tab32 + (size_t)(p0 + p) * T32_STRIDE, rc, fi, sx, sy);
+                };
+                for (int q = 0; q < n; q++) {  // a run without the clamp, then one with it
+                    const unsigned long long rest = cl >> q;
+                    const int stop = rest ? min(n, q + __builtin_ctzll(rest)) : n;
+                    for (; q < stop; q++) add(q, std::false_type());
+                    if (q < n) add(q, std::true_type());
+                }
             }
         }
     }
@@ -516,14 +524,15 @@ hipError_t launch_mixed(const PotPtrs& pot, const GridDesc& g, const MixedLaunch
     // FP32 field layout: two columns of four rows per thread once there are
     // workgroups enough (6730^2 x 702: 5.93 ms against 6.97 for 1 x 4, 6.35 for 2 x 2,
     // 6.07 for 4 x 4, and 8.12 for the former 4 x 1 with the clamp everywhere), one
-    // column below (1200 x 900 x 200: 76 us against 86), single nodes for small images.
+    // column below (1200 x 900 x 200: 76 us against 86), single nodes for small images
+    // (643 x 569 x 284: 53 us against 76 for 1 x 4; 900 x 1000 x 500 178, 141 for 1 x 4).
     auto field = [&](auto kern, int c, int r) {
         return launch_ev(ml.ev, kern, dim3((unsigned)((g.nx + 256 * c - 1) / (256 * c)), (unsigned)((g.ny + r - 1) / r)),
                          dim3(256), s, (const float*)ml.tab32, pot.n, g.nx, g.ny, ml.ax, ml.ay, ml.mask,
                          (const MixState*)ml.st);
     };
     e = n_nodes >= (4ll << 20)   ? field(k_mix_field32<2, 4>, 2, 4)
-        : n_nodes >= (1ll << 18) ? field(k_mix_field32<1, 4>, 1, 4)
+        : n_nodes >= (1ll << 19) ? field(k_mix_field32<1, 4>, 1, 4)
                                  : field(k_mix_field32<1, 1>, 1, 1);
     if (e != hipSuccess) return e;
     // blocks: 256 pixels per workgroup, a few workgroups per CU in all at least
