@@ -11,8 +11,7 @@
 //   k_mix_field32  FP32 field at every node (SIE form alpha = K m / R with
 //                  R = sqrt(d . M d): one reciprocal square root per
 //                  potential), written as double; mask cleared
-//   k_mix_blocks   FP64 gradient of the cluster-scale halos' blocks, then of the
-//                  others' (two launches), marked 1
+//   k_mix_blocks   FP64 gradient of the halos' blocks, marked 1
 //   k_mix_scan     criteria on the field so far, pixels marked 2; counts
 //   k_mix_stats    counts and status to the caller's stats
 //   k_mix_pixels   FP64 gradient of the pixels marked 2 one by one, or
@@ -229,30 +228,32 @@ __device__ __forceinline__ void sie64_add(const double* __restrict__ t, double t
     s2 = fma(kr, m2, s2);
 }
 
-// FP64 gradient of pixel (i, j) by the sum over all halos.
+// FP64 gradient of pixel (i, j) by the sum over all halos, eight at a time: their
+// scalar loads, from beyond the scalar cache for some hundred halos, are in flight
+// together (6730^2 x 702 blocks 398 us, four at a time 409, one 451).
 template <bool FULL>
 __device__ __forceinline__ void pixel64(const double* __restrict__ tab64, int np, const GridDesc& g, int i, int j,
                                         double* __restrict__ ax, double* __restrict__ ay)
 {
     const double t1 = node_coord(g.x0, i, g.h), t2 = node_coord(g.y0, j, g.h);
     double s1 = 0.0, s2 = 0.0;
-#pragma unroll 4
+#pragma unroll 8
     for (int m = 0; m < np; m++) sie64_add<FULL>(tab64 + (size_t)m * T64_STRIDE, t1, t2, s1, s2);
     const size_t o = (size_t)j * g.nx + i;
     ax[o] = s1;
     ay[o] = s2;
 }
 
-// The FP64 blocks of halos [p0, p0 + gridDim.x), side `size`, clipped to the grid: the
-// workgroups of column blockIdx.x mark halo blockIdx.x's pixels in the mask and write
-// their FP64 gradient, 256 pixels at a time.  A pixel of several blocks belongs to the
-// first of those halos, whatever the launch (side `size0` for the first n0 halos): the
-// blocks that come before and touch the 256 pixels' rows are listed in LDS, 256 halos
-// at a time, and the pixels that are left are packed into whole waves.  Bound by FP64
-// issue (6730^2 x 702: 428 us in both launches, 426 without the lists, which
-// repeated shared pixels: 100 x 64 x 702 504 us a call, now 320; 300 x 211 x 100
-// with blocks of 400 375, now 98).
-__global__ __launch_bounds__(256) void k_mix_blocks(int np, GridDesc g, int p0, int size, int n0, int size0,
+// The FP64 blocks of the halos, side size0 for the first n0 and size1 for the others,
+// clipped to the grid: per0 (per1) workgroups mark a halo's pixels in the mask and
+// write their FP64 gradient, 256 pixels at a time.  A pixel of several blocks belongs to
+// the first of those halos: the blocks that come before and touch the 256 pixels' rows
+// are listed in LDS, 256 halos at a time, and the pixels that are left are packed into
+// whole waves.  One launch for both kinds, so that the few pixels left to the second
+// do not add a chain of their own.  Bound by FP64 issue (6730^2 x 702: 398 us; 426
+// without the lists, which repeated shared pixels: 100 x 64 x 702 504 us a call, now 277;
+// 300 x 211 x 100 with blocks of 400 375, now 72; 600 x 500 x 702 749, now 481).
+__global__ __launch_bounds__(256) void k_mix_blocks(int np, GridDesc g, int n0, int size0, int per0, int size1, int per1,
                                                     const int2* __restrict__ corner, const double* __restrict__ tab64,
                                                     double* __restrict__ ax, double* __restrict__ ay,
                                                     unsigned char* __restrict__ mask, const MixState* __restrict__ st)
@@ -261,7 +262,11 @@ __global__ __launch_bounds__(256) void k_mix_blocks(int np, GridDesc g, int p0, 
     __shared__ unsigned short left[256];
     __shared__ int s_n[4];
     if (st->status != kStatusOk) return;
-    const int p = p0 + blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
+    const int lane = lane_id(), wave = threadIdx.x >> 6, b0 = n0 * per0;
+    const bool first = (int)blockIdx.x < b0;
+    const int rest = first ? (int)blockIdx.x : (int)blockIdx.x - b0, per = first ? per0 : per1;
+    const int p = (first ? 0 : n0) + rest / per, size = first ? size0 : size1;
+    const unsigned chunk = (unsigned)(rest % per);  // of `per` workgroups of the halo
     const int2 c = corner[p];
     const int i0 = max(c.x, 0), j0 = max(c.y, 0), i1 = min(c.x + size, g.nx), j1 = min(c.y + size, g.ny);
     if (i0 >= i1 || j0 >= j1) return;
@@ -276,7 +281,7 @@ __global__ __launch_bounds__(256) void k_mix_blocks(int np, GridDesc g, int p0, 
         total = s_n[0] + s_n[1] + s_n[2] + s_n[3];
         return at;
     };
-    for (unsigned q0 = blockIdx.y * 256; q0 < n; q0 += gridDim.y * 256) {
+    for (unsigned q0 = chunk * 256; q0 < n; q0 += (unsigned)per * 256) {
         const unsigned q = q0 + threadIdx.x;
         const int j = j0 + (int)(q / w), i = i0 + (int)(q % w);
         const int ja = j0 + (int)(q0 / w), jb = j0 + (int)((min(q0 + 256u, n) - 1) / w);  // rows of the 256
@@ -287,7 +292,7 @@ __global__ __launch_bounds__(256) void k_mix_blocks(int np, GridDesc g, int p0, 
             bool in = false;
             if (h < p) {
                 const int2 d = corner[h];
-                const int sz = h < n0 ? size0 : size;
+                const int sz = h < n0 ? size0 : size1;
                 t = make_int4(d.x, d.y, d.x + sz, d.y + sz);
                 in = t.x < i1 && t.z > i0 && t.y <= jb && t.w > ja;
             }
@@ -412,10 +417,10 @@ struct CriteriaSink {
 };
 
 // FP64 gradient of the criteria pixels one by one, where the image has no more than
-// `few` of them: a workgroup takes every so-many-th run of 512 pixels and collects their
+// `few` of them: a workgroup takes every so-many-th run of 256 pixels and collects their
 // criteria pixels in LDS first, so that whole waves work on them.  As many workgroups
 // as give each two waves of them take part, for balance, and enough to read the mask.
-constexpr int kRun = 512;
+constexpr int kRun = 256;
 __global__ __launch_bounds__(256) void k_mix_pixels(const double* __restrict__ tab64, int np, GridDesc g, unsigned few,
                                                     const unsigned char* __restrict__ mask, double* __restrict__ ax,
                                                     double* __restrict__ ay, const MixState* __restrict__ st)
@@ -426,7 +431,7 @@ __global__ __launch_bounds__(256) void k_mix_pixels(const double* __restrict__ t
     } L;
     if (st->status != kStatusOk || st->n_crit == 0 || st->n_crit > few) return;
     const unsigned nn = (unsigned)g.nx * (unsigned)g.ny, runs = (nn + kRun - 1) / kRun, t = threadIdx.x;
-    const unsigned step = min(gridDim.x, max(1024u, st->n_crit / 128));
+    const unsigned step = min(gridDim.x, max(2048u, st->n_crit / 128));
     if (blockIdx.x >= step) return;
     if (t == 0) L.n = 0;
     __syncthreads();
@@ -536,16 +541,17 @@ hipError_t launch_mixed(const PotPtrs& pot, const GridDesc& g, const MixedLaunch
                                  : field(k_mix_field32<1, 1>, 1, 1);
     if (e != hipSuccess) return e;
     // blocks: 256 pixels per workgroup, a few workgroups per CU in all at least
-    auto blocks = [&](int p0, int n, int size) {
-        if (n <= 0 || size <= 0) return hipSuccess;
+    auto per = [&](int n, int size) {
+        if (n <= 0 || size <= 0) return 0;
         const long long px = (long long)std::min(size, g.nx) * std::min(size, g.ny);
-        const unsigned ny = (unsigned)std::min(std::max(1ll, 16384ll / n), (px + 255) / 256);
-        k_mix_blocks<<<dim3((unsigned)n, ny), 256, 0, s>>>(pot.n, g, p0, size, ml.n_cluster, ml.pc, ml.corner, ml.tab64,
-                                                          ml.ax, ml.ay, ml.mask, ml.st);
-        return hipGetLastError();
+        return (int)std::min(std::max(1ll, 16384ll / n), (px + 255) / 256);
     };
-    if ((e = blocks(0, ml.n_cluster, ml.pc)) != hipSuccess) return e;
-    if ((e = blocks(ml.n_cluster, pot.n - ml.n_cluster, ml.pg)) != hipSuccess) return e;
+    const int n0 = ml.n_cluster, n1 = pot.n - n0, per0 = per(n0, ml.pc), per1 = per(n1, ml.pg);
+    if (per0 || per1) {
+        k_mix_blocks<<<(unsigned)(n0 * per0 + n1 * per1), 256, 0, s>>>(pot.n, g, n0, ml.pc, per0, ml.pg, per1, ml.corner,
+                                                                      ml.tab64, ml.ax, ml.ay, ml.mask, ml.st);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     const dim3 sg = scan_grid(g);
     k_mix_scan<<<sg, 256, 0, s>>>(ml.ax, ml.ay, g, ml.t12, ml.t34, ml.mask, ml.counts, ml.st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -555,9 +561,9 @@ hipError_t launch_mixed(const PotPtrs& pot, const GridDesc& g, const MixedLaunch
     // device only, hence both launches, of which one does the work): kPixel cycles per 64
     // of them and halo, against the tiles' cost and kTile cycles per 64 of them for the
     // masked loads and stores (whole calls, us, by tiles / one by one: 3000^2 x 3 with
-    // 7.8 M of them 257 / 111, 1500^2 x 15 with 1.9 M 98 / 69, 1200 x 900 x 200 with 4000
-    // 258 / 214 and with 0.67 M 270 / 330).  More halos than a tile's lists hold: one by
-    // one (2000^2 x 2060 12200 / 7570).
+    // 7.8 M of them 257 / 113, 1500^2 x 15 with 1.9 M 98 / 69, 1200 x 900 x 200 with 4000
+    // 258 / 203 and with 0.67 M 270 / 330).  More halos than a tile's lists hold: one by
+    // one (2000^2 x 2060 12200 / 7580).
     double cost;
     const int side = tile_side_for((double)n_nodes, (double)n_nodes, pot.n, kTileCost64, &cost);
     constexpr double kPixel = 125.0, kTile = 2500.0;
