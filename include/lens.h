@@ -240,7 +240,9 @@ int lens_image_chi2(lens_ctx *ctx, const lens_potentials *pot, const lens_grid *
  * set in opts), and calls no hipMalloc, hipFree or allocating routine.  Its
  * scratch is one fixed array of LENS_NOALLOC_SCRATCH_BYTES in device memory
  * that the library holds on every device it runs on until the process ends
- * (512 MiB holds a 4096^2 grid with 100 systems in either precision).
+ * (512 MiB holds a 4096^2 grid with 100 systems in either precision).  Near its
+ * limit a direct FP64 field goes by tiles, whose records are smaller (the same to
+ * rounding).
  * An input that needs more returns LENS_ERR_SCRATCH before anything is
  * enqueued.  The array's address on a device is looked up once, on the first
  * call on that device or by lens_create for it; that lookup is not a stream

@@ -578,6 +578,16 @@ int chi2_check(const lens_potentials* pot, const lens_grid* grid, const lens_obs
     return LENS_OK;
 }
 
+// The field by tiles of `side` nodes (0: direct), and what hangs on it: the head's
+// source-plane part runs inside the field launch when the grid allows.
+void chi2_field(Chi2Plan& pl, int side)
+{
+    pl.side = side;
+    pl.fused = side || fused_head_fits(pl.g, pl.o, pl.npl, pl.mixed) != 0;
+    pl.bytes[CB_RR] = side ? (size_t)rec_nbx(pl.g) * rec_nby(pl.g) * kRec * pl.vbytes
+                           : (size_t)pl.g.ny * (pl.tiles_x + 1) * kRR * pl.vbytes;
+}
+
 // Shape of the launches and bytes of every scratch buffer; flag_cap is the
 // capacity of the undecided-test list (mixed path).
 int chi2_plan(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* grid, const lens_obs* obs,
@@ -606,9 +616,7 @@ int chi2_plan(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* grid, 
     if (pl.region * pl.n_cull > (1ll << 28)) return LENS_ERR_CAPACITY;  // 2 GiB of pair keys
     pl.vbytes = pl.mixed ? 4 : 8;
     pl.flag_cap = pl.mixed ? flag_cap : 0;
-    // the head's source-plane part runs inside the field launch when the grid allows
-    pl.side = tiled_side(pl.g, pl.np, pl.mixed);
-    pl.fused = pl.side || fused_head_fits(pl.g, pl.o, pl.npl, pl.mixed) != 0;
+    chi2_field(pl, tiled_side(pl.g, pl.np, pl.mixed));
     size_t* b = pl.bytes;
     b[CB_STATE] = sizeof(EvalState);
     b[CB_TAB64] = (size_t)pl.np * T64_STRIDE * 8;
@@ -623,8 +631,6 @@ int chi2_plan(lens_ctx* ctx, const lens_potentials* pot, const lens_grid* grid, 
     b[CB_POS] = (size_t)kHitScratch * 4 * 8;
     b[CB_FLAGS] = (size_t)(pl.mixed ? pl.flag_cap : 1) * 8;
     b[CB_PART] = (size_t)pl.n_parts * 2 * 4;
-    b[CB_RR] = pl.side ? (size_t)rec_nbx(pl.g) * rec_nby(pl.g) * kRec * pl.vbytes
-                       : (size_t)pl.g.ny * (pl.tiles_x + 1) * kRR * pl.vbytes;
     b[CB_PAIRS] = (size_t)pl.region * pl.n_cull * 8 + (size_t)pl.n_cull * 4;
     return LENS_OK;
 }
@@ -805,11 +811,22 @@ int lens_image_chi2_noalloc(const lens_potentials* pot, const lens_grid* grid, c
     if ((rc = chi2_plan(nullptr, pot, grid, obs, opts, kFlagScratch, pl))) return rc;
     // the context path's buffers, carved in order from the fixed array
     Chi2Bufs b;
-    size_t off = 0;
-    for (int k = 0; k < CB_N; k++) {
-        b.p[k] = base + off;
-        off += (std::max(pl.bytes[k], (size_t)1) + 255) & ~(size_t)255;
-        if (off > (size_t)LENS_NOALLOC_SCRATCH_BYTES) return LENS_ERR_SCRATCH;
+    auto carve = [&] {
+        size_t off = 0;
+        for (int k = 0; k < CB_N; k++) {
+            b.p[k] = base + off;
+            off += (std::max(pl.bytes[k], (size_t)1) + 255) & ~(size_t)255;
+            if (off > (size_t)LENS_NOALLOC_SCRATCH_BYTES) return false;
+        }
+        return true;
+    };
+    if (!carve()) {
+        // a direct field's range partials are four times a tiled one's records (5500^2
+        // FP64: 61 MB of 545, 15 of 499): by tiles wherever only they fit
+        const int side = pl.side ? 0 : tileable_side(pl.g, pl.np, pl.mixed);
+        if (!side) return LENS_ERR_SCRATCH;
+        chi2_field(pl, side);
+        if (!carve()) return LENS_ERR_SCRATCH;
     }
     // The evaluation state sits at the start of the array in every call; its
     // head ticket must be zero when the head kernel starts.  The fused path's

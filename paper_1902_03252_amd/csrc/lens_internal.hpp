@@ -111,6 +111,7 @@ inline bool bfield_code_ok(int code)
 // Field by tiles of side x side nodes (lens_tiles.hpp); rec: 32 x 8 block
 // records or null; h: the head's arguments (fused head) or null.
 int tiled_side(const GridDesc& g, int np, bool fp32);  // 0: direct field
+int tileable_side(const GridDesc& g, int np, bool fp32);
 // Cost of a tiled field in cycles per 64 nodes and potential (near: per node; far:
 // per Chebyshev point, `points` of them; rest: per node whatever P), and the
 // near region's radius in half widths.

@@ -1122,10 +1122,17 @@ static int head_blocks_for(const ObsPtrs& obs) { return obs.n_img > 0 ? (int)cdi
 // the instruction counts: FP32 116 far, 75 near, 60 for the rest; FP64 180, 200, 200.
 int tiled_side(const GridDesc& g, int np, bool fp32)
 {
+    const int side = !fp32 && np < kTileMinP64 ? 0 : tileable_side(g, np, fp32);
+    return side && tiles_too_thin(g, side, fp32 ? kThinNodes32 : kThinNodes64) ? 0 : side;
+}
+
+// The side for any field of the size and potential counts that tiles are for, also one
+// that keeps the direct sum for its rounding or as a thin grid; 0 for the others.
+int tileable_side(const GridDesc& g, int np, bool fp32)
+{
     const double nodes = (double)g.nx * g.ny;
-    if (np < (fp32 ? 4 : kTileMinP64) || np > kTileMaxP || nodes * np < (double)(1 << 24)) return 0;
-    const int side = tile_side_for(nodes, nodes, np, fp32 ? kTileCost32 : kTileCost64);
-    return tiles_too_thin(g, side, fp32 ? kThinNodes32 : kThinNodes64) ? 0 : side;
+    if (np < 4 || np > kTileMaxP || nodes * np < (double)(1 << 24)) return 0;
+    return tile_side_for(nodes, nodes, np, fp32 ? kTileCost32 : kTileCost64);
 }
 
 // Whether a grid is so thin that its tiles hold fewer than `least` nodes on average:
